@@ -453,6 +453,12 @@ HostAttnSched build_attn_schedule(const nsp_worklist *wl) {
   const int D = wl->head_dim;
   int64_t qo = 0, ko = 0, lo = 0;
   std::vector<int64_t> fcost;
+  int64_t small_blocks = 0;
+  for (int j = 0; j < wl->n_items; ++j)
+    if (selected(wl, j))
+      small_blocks += (int64_t)(wl->q_heads[2 * j + 1] - wl->q_heads[2 * j]) *
+                      ((wl->cu_seqlens[j + 1] - wl->cu_seqlens[j] + nsp::kPreSmallRows - 1) / nsp::kPreSmallRows);
+  const int pre_rows = small_blocks > nsp::kPreFewBlocks ? nsp::kPreBlockRows : nsp::kPreSmallRows;
   ItemGangs item_gangs;
   for (int j = 0; j < wl->n_items; ++j) {
     const int L = wl->cu_seqlens[j + 1] - wl->cu_seqlens[j];
@@ -470,8 +476,8 @@ HostAttnSched build_attn_schedule(const nsp_worklist *wl) {
     s.items.push_back(d);
     if (L > 0 && d.active) {
       for (int i = 0; i < hq; ++i)
-        for (int t = 0; t < L; t += nsp::kPreBlockRows)
-          s.pre_blocks.push_back(nsp::PreBlock{j, i, t, std::min(nsp::kPreBlockRows, L - t)});
+        for (int t = 0; t < L; t += pre_rows)
+          s.pre_blocks.push_back(nsp::PreBlock{j, i, t, std::min(pre_rows, L - t)});
       const int nq = (L + nsp::kFwdBM - 1) / nsp::kFwdBM;
       for (int m = 0; m < nq; ++m)
         for (int i = 0; i < hq; ++i) {

@@ -30,7 +30,16 @@ struct PreBlock {
   int32_t t0;
   int32_t ntok;     // at most kPreBlockRows
 };
+// Tokens of a preprocess block.  The pass is bound by HBM latency until about
+// eight 256-thread workgroups a compute unit are in flight, so short lists
+// take small blocks (one 4096-token sequence, 32 heads: 32.8 us with 512
+// tokens a block, 14.2 with 128, 13.8 with 64; the 24-item short share 265,
+// 222 and 224 us).  Lists of more than kPreFewBlocks small blocks fill the
+// chip either way and take the large ones, which keep their schedule small
+// (the long-tail share: 900, 912 and 937 us).
 constexpr int kPreBlockRows = 512;
+constexpr int kPreSmallRows = 128;
+constexpr int64_t kPreFewBlocks = 32768;
 
 // Tile geometry shared by host scheduling and the kernels.
 constexpr int kFwdWaves = 8;  // waves per forward / dQ workgroup (two per SIMD)
