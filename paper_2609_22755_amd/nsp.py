@@ -262,7 +262,8 @@ def nsp_varlen_attn_fwd(wl, q, k, v, o, lse, softmax_scale: float, causal: int =
 
 def nsp_varlen_attn_bwd_workspace(wl) -> int:
     lib = load_library()
-    return int(lib.nsp_varlen_attn_bwd_workspace(_WL(wl, with_sp=False).ref))
+    w = _WL(wl, with_sp=False)
+    return int(lib.nsp_varlen_attn_bwd_workspace(w.ref))
 
 
 def nsp_varlen_attn_bwd(wl, q, k, v, o, dout, lse, dq, dk, dv, workspace, softmax_scale: float,
@@ -301,14 +302,16 @@ def nsp_varlen_attn_bwd_noalloc(wl, q, k, v, o, dout, lse, dq, dk, dv, softmax_s
 
 def nsp_ulysses_pack(wl, kind: int, x_seq, x_head, stream=None):
     lib = load_library()
-    st = lib.nsp_ulysses_pack(_WL(wl).ref, int(kind), _dtype_code(x_seq), _ptr(x_seq), _ptr(x_head),
+    w = _WL(wl)
+    st = lib.nsp_ulysses_pack(w.ref, int(kind), _dtype_code(x_seq), _ptr(x_seq), _ptr(x_head),
                               _stream(stream))
     _check(st, "nsp_ulysses_pack")
 
 
 def nsp_ulysses_unpack(wl, kind: int, replica: int, x_head, x_seq, stream=None):
     lib = load_library()
-    st = lib.nsp_ulysses_unpack(_WL(wl).ref, int(kind), _dtype_code(x_head), int(replica), _ptr(x_head),
+    w = _WL(wl)
+    st = lib.nsp_ulysses_unpack(w.ref, int(kind), _dtype_code(x_head), int(replica), _ptr(x_head),
                                 _ptr(x_seq), _stream(stream))
     _check(st, "nsp_ulysses_unpack")
 
