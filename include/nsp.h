@@ -132,8 +132,11 @@ nsp_status nsp_varlen_attn_fwd(const nsp_worklist *wl, float softmax_scale, int3
 
 /* Bytes of device workspace nsp_varlen_attn_bwd needs for this work list (0
  * if the work list is invalid): -Delta[t] = -<dO[t], O[t]> and lse*log2(e)
- * (float32, laid out like lse, each part 256-byte aligned) and 256 bytes of
- * unit-queue heads for the persistent passes.  A call uses the workspace
+ * (float32, laid out like lse, each part 256-byte aligned), 256 bytes of
+ * unit-queue heads for the persistent passes and room for float32 partial
+ * sums of dK/dV (512 KiB * head_dim, the same for every list: a list whose
+ * dK/dV units would leave compute units idle has them cut into pieces; decided
+ * from every item, whatever item_mask).  A call uses the workspace
  * from its first kernel to its last, so two calls that run at the same time
  * need two workspaces. */
 size_t nsp_varlen_attn_bwd_workspace(const nsp_worklist *wl);
@@ -246,8 +249,10 @@ nsp_status nsp_recompute_plan(const nsp_worklist *wl, int64_t budget_bytes, nsp_
                               int64_t *saved_bytes);
 
 /*
- * The work units the attention calls launch for a work list, in launch
- * order (host only; no device work).  This is the schedule step between the
+ * The work units of the attention calls for a work list, in launch order
+ * (host only; no device work).  A dK/dV pass that is split (see
+ * nsp_varlen_attn_bwd_workspace) runs the same key tiles cut into pieces of
+ * equal shares instead, one share per compute unit.  This is the schedule step between the
  * work list and the kernels: it balances items of very different L_j over
  * the compute units (Design, NSP Executor: the per-GPU compute of one SP-tree
  * share; Background: the quadratic cost of long sequences), and it is

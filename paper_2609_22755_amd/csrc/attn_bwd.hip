@@ -760,30 +760,30 @@ __device__ __forceinline__ void kv_drain(KvState<D> &st) {
                  : "+a"(st.dk[0]), "+a"(st.dk[1]), "+a"(st.dv[0]), "+a"(st.dv[1]));
 }
 
-// One dK/dV unit (launch slot `slot` of the unit list) on the workgroup's
-// four LDS pipeline stages.
-template <int D, bool G_F32>
-__device__ __forceinline__ void dkdv_unit(const AttnArgs &a, int slot, bf16 *stg0, bf16 *stg1, bf16 *stg2,
+// One dK/dV unit on the workgroup's four LDS pipeline stages: all steps of key
+// tile `tile` (down from the item end if desc), or, for a piece, `count` steps
+// from step `first` on, whose sums go to `part` unless that is null.
+template <int D, bool G_F32, bool PIECE>
+__device__ __forceinline__ void dkdv_unit(const AttnArgs &a, int item, int tile, bool desc, int heads, int g,
+                                          int first, int count, float *part, bf16 *stg0, bf16 *stg1, bf16 *stg2,
                                           bf16 *stg3) {
   using C = KvCfg<D>;
-  const int4 u = a.units[slot];
-  const ItemDesc it = a.items[u.x];
+  const ItemDesc it = a.items[item];
   const int L = it.L;
-  const int n0 = (u.y & kKvTileMask) * C::BN;
-  const bool desc = (u.y & kKvDescending) != 0;
-  const int i_lo = u.z & 0xffff, i_hi = u.z >> 16;
+  const int n0 = tile * C::BN;
+  const int i_lo = heads & 0xffff, i_hi = heads >> 16;
   const int wave = wave_id(), lane = threadIdx.x & 63;
   const int l32 = lane & 31, h = lane >> 5;
   const int64_t qs = (int64_t)it.hq * D;
   const int64_t ks = (int64_t)it.hkv * D;
-  const int64_t kvhead = it.kv_off + (int64_t)u.w * D;
+  const int64_t kvhead = it.kv_off + (int64_t)g * D;
 
   const int kbase = n0 + wave * 32;           // first key of this wave
   const int key = kbase + l32;                // this lane's key (MFMA column)
   const int mt0 = n0 / C::BM;                     // first query tile touching the keys
   const int mt_end = (L + C::BM - 1) / C::BM;
   const int nh = i_hi - i_lo;
-  const int n_iter = nh * (mt_end - mt0);
+  const int n_iter = PIECE ? count : nh * (mt_end - mt0);
 
   KvState<D> st;
   {
@@ -808,17 +808,22 @@ __device__ __forceinline__ void dkdv_unit(const AttnArgs &a, int slot, bf16 *stg
   // A group without query heads (n_iter = 0) still runs the prologue: its
   // fills are empty (zeros, nothing fetched) and the steps that follow are
   // skipped, so the unit writes zero gradients.
-  const int m_first = (desc ? mt_end - 1 : mt0) * C::BM;
+  int h0 = 0, t0 = 0;                             // first head and query tile of a piece
+  if (PIECE && nh > 0) {
+    t0 = first / nh;
+    h0 = first - t0 * nh;
+  }
+  const int m_first = (desc ? mt_end - 1 : mt0 + t0) * C::BM;
   const int dm = desc ? -C::BM : C::BM;
   const int row_bytes = (int)qs * 2;
   KvCursor<D> cu{TileLoader<D, C::BM>((const bf16 *)a.q, qs, wave, lane),
                  TileLoader<D, C::BM>((const bf16 *)a.dout, qs, wave, lane)};
-  cu.pq = (const bf16 *)a.q + it.q_off + (int64_t)m_first * qs + (int64_t)i_lo * D;
-  cu.pg = (const bf16 *)a.dout + it.q_off + (int64_t)m_first * qs + (int64_t)i_lo * D;
-  cu.pl = a.lse2 + it.lse_off + (int64_t)i_lo * L + m_first;
-  cu.pd = a.delta + it.lse_off + (int64_t)i_lo * L + m_first;
+  cu.pq = (const bf16 *)a.q + it.q_off + (int64_t)m_first * qs + (int64_t)(i_lo + h0) * D;
+  cu.pg = (const bf16 *)a.dout + it.q_off + (int64_t)m_first * qs + (int64_t)(i_lo + h0) * D;
+  cu.pl = a.lse2 + it.lse_off + (int64_t)(i_lo + h0) * L + m_first;
+  cu.pd = a.delta + it.lse_off + (int64_t)(i_lo + h0) * L + m_first;
   cu.m = m_first;
-  cu.hh = 0;
+  cu.hh = h0;
   cu.nh = nh;
   cu.dm = dm;
   cu.tq = (int64_t)dm * qs - (int64_t)(nh - 1) * D;
@@ -846,7 +851,7 @@ __device__ __forceinline__ void dkdv_unit(const AttnArgs &a, int slot, bf16 *stg
 #pragma unroll
     for (int f = 0; f < kKvPf; ++f) st.op0[f] = kv_operand<D>(f, stg0, stg0 + C::SUB * D, lane);
   }
-  int m0 = m_first, mh = 0;
+  int m0 = m_first, mh = h0;
   for (int i = 0; i < n_iter;) {
 #define NSP_KV_STEP(CUR, NXT)                                                                     \
     {                                                                                             \
@@ -875,7 +880,19 @@ __device__ __forceinline__ void dkdv_unit(const AttnArgs &a, int slot, bf16 *stg
   }
 
   kv_drain<D>(st);
-  if (key < L) {
+  if (PIECE && part) {
+    // accumulator order: lane by lane, 16 bytes each, so that every store and
+    // the sum pass's loads are whole contiguous runs
+#pragma unroll
+    for (int md = 0; md < C::MB; ++md)
+#pragma unroll
+      for (int gq = 0; gq < 4; ++gq) {
+        float *p = part + 4 * ((md * 4 + gq) * 256 + (int)threadIdx.x);
+        *(f32x4 *)p = f32x4{st.dk[md][4 * gq], st.dk[md][4 * gq + 1], st.dk[md][4 * gq + 2], st.dk[md][4 * gq + 3]};
+        *(f32x4 *)(p + C::BN * D) =
+            f32x4{st.dv[md][4 * gq], st.dv[md][4 * gq + 1], st.dv[md][4 * gq + 2], st.dv[md][4 * gq + 3]};
+      }
+  } else if (key < L) {
     const int64_t obase = kvhead + (int64_t)key * ks;
 #pragma unroll
     for (int md = 0; md < C::MB; ++md)
@@ -914,9 +931,70 @@ __global__ void __launch_bounds__(256, 1) bwd_dkdv_kernel(AttnArgs a, int *heads
   for (int iter = 0;; ++iter) {
     const int slot = heads ? next_range_slot(heads, a.qoff, own, &s_slot) : (iter == 0 ? (int)blockIdx.x : -1);
     if (slot < 0) break;
-    dkdv_unit<D, G_F32>(a, slot, stg0, stg1, stg2, stg3);
+    const int4 u = a.units[slot];
+    dkdv_unit<D, G_F32, false>(a, u.x, u.y & kKvTileMask, (u.y & kKvDescending) != 0, u.z, u.w, 0, 0, nullptr, stg0,
+                               stg1, stg2, stg3);
     // nothing may still be loading into the stages when the next unit fills them
     __builtin_amdgcn_s_waitcnt(0);
+  }
+}
+
+// Split dK/dV pass: workgroup b runs the pieces of its share in turn.  The
+// shares are balanced on the host, so the grid is one workgroup per compute
+// unit and needs no queues.  One 4096-token sequence (32 / 4 heads, D = 128):
+// 128 whole tiles took 655 us, the shares 250 us and the sum pass 10 us (its
+// 48 MB of partial sums stay in the last-level cache); a 16384-token item of
+// 4 / 1 heads 1265 us against 478 + 10 us.
+template <int D, bool G_F32>
+__global__ void __launch_bounds__(256, 1) bwd_dkdv_split_kernel(AttnArgs a) {
+  using C = KvCfg<D>;
+  __shared__ __attribute__((aligned(16))) bf16 stg0[C::STAGE];
+  __shared__ __attribute__((aligned(16))) bf16 stg1[C::STAGE];
+  __shared__ __attribute__((aligned(16))) bf16 stg2[C::STAGE];
+  __shared__ __attribute__((aligned(16))) bf16 stg3[C::STAGE];
+  const int2 r = a.wgs[blockIdx.x];
+  for (int i = r.x; i < r.y; ++i) {
+    const KvPiece p = a.pieces[i];
+    dkdv_unit<D, G_F32, true>(a, p.item, p.tile, false, p.heads, p.g, p.first, p.count,
+                              p.slot < 0 ? nullptr : a.part + p.slot * kv_slot_floats(D), stg0, stg1, stg2, stg3);
+    // nothing may still be loading into the stages, and no wave still reading
+    // them, when the next piece fills them
+    __builtin_amdgcn_s_waitcnt(0);
+    stage_barrier();
+  }
+}
+
+// Sums of the pieces of a split key tile, in piece order, and the stores.
+// Workgroup (tile, dK or dV, 32-wide head_dim block); lane layout of the
+// accumulators.  Bound by memory: each partial sum read once.
+template <int D, bool G_F32>
+__global__ void __launch_bounds__(256) bwd_kv_reduce_kernel(AttnArgs a) {
+  constexpr int MB = D / 32;
+  const KvReduce r = a.reduce[blockIdx.x / (2 * MB)];
+  const int md = blockIdx.x % MB;
+  const bool dv = (blockIdx.x / MB) & 1;
+  const ItemDesc it = a.items[r.item];
+  const int lane = threadIdx.x & 63, h = lane >> 5;
+  const int key = r.tile * kBwdBN + (int)(threadIdx.x >> 6) * 32 + (lane & 31);
+  const float *p = a.part + r.slot * kv_slot_floats(D) + (dv ? (int64_t)kBwdBN * D : 0) + 4 * (md * 4 * 256 + (int)threadIdx.x);
+  f32x4 acc[4];
+#pragma unroll
+  for (int gq = 0; gq < 4; ++gq) acc[gq] = *(const f32x4 *)(p + 4 * 256 * gq);
+#pragma unroll 4
+  for (int k = 1; k < r.count; ++k) {
+    p += kv_slot_floats(D);
+#pragma unroll
+    for (int gq = 0; gq < 4; ++gq) acc[gq] += *(const f32x4 *)(p + 4 * 256 * gq);
+  }
+  if (key >= it.L) return;
+  const float scale = dv ? 1.f : a.scale;
+  void *out = dv ? a.dv : a.dk;
+  const int64_t o = it.kv_off + (int64_t)key * it.hkv * D + (int64_t)r.g * D + 32 * md + 4 * h;
+#pragma unroll
+  for (int gq = 0; gq < 4; ++gq) {
+    const f32x4 v = {acc[gq][0] * scale, acc[gq][1] * scale, acc[gq][2] * scale, acc[gq][3] * scale};
+    if constexpr (G_F32) *(f32x4 *)((float *)out + o + 8 * gq) = v;
+    else *(bf16x4 *)((bf16 *)out + o + 8 * gq) = bf16x4{(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]};
   }
 }
 
@@ -965,8 +1043,19 @@ hipError_t launch_bwd_dq(int head_dim, bool g_f32, const AttnArgs &a, int n_unit
   return hipGetLastError();
 }
 
+template <int D, bool G_F32>
+static hipError_t launch_split(const AttnArgs &a, int n_wgs, hipStream_t s) {
+  bwd_dkdv_split_kernel<D, G_F32><<<dim3(n_wgs), dim3(256), 0, s>>>(a);
+  if (a.n_reduce > 0) bwd_kv_reduce_kernel<D, G_F32><<<dim3(a.n_reduce * 2 * (D / 32)), dim3(256), 0, s>>>(a);
+  return hipGetLastError();
+}
+
 hipError_t launch_bwd_dkdv(int head_dim, bool g_f32, const AttnArgs &a, int n_units, hipStream_t s) {
   if (n_units == 0) return hipSuccess;
+  if (a.wgs) {
+    if (head_dim == 128) return g_f32 ? launch_split<128, true>(a, n_units, s) : launch_split<128, false>(a, n_units, s);
+    return g_f32 ? launch_split<64, true>(a, n_units, s) : launch_split<64, false>(a, n_units, s);
+  }
   dim3 grid, block(256);
   int *heads = nullptr;
   hipError_t e = pass_grid(n_units, a.queue + kKvQueue0, &grid, &heads);

@@ -150,6 +150,9 @@ struct HostAttnSched {
   std::vector<int4> fwd_units, kv_units;
   std::vector<int> kv_qoff;     // kXcdQueues + 1 entries: the dK/dV queue of XCD x is kv_units[kv_qoff[x] ..)
   std::vector<nsp::PreBlock> pre_blocks;
+  std::vector<nsp::KvPiece> kv_pieces;   // split dK/dV (empty: not split)
+  std::vector<int2> kv_wgs;
+  std::vector<nsp::KvReduce> kv_reduce;
   int64_t q_rows = 0;
 };
 
@@ -448,6 +451,174 @@ void kv_balance(ItemGangs &items, const nsp_worklist *wl) {
   add_kv_gangs(items[big].second, wl, j, L, best_k);
 }
 
+// ---------------------------------------------------------- split dK/dV --
+
+// A list of few or long units leaves compute units idle in the dK/dV pass: one
+// 4096-token sequence (32 / 4 heads) has 128 key tiles for 256 compute units,
+// the longest with twice the mean's steps.  kv_split then cuts the steps of
+// all key tiles, in order, into one share per compute unit of about equal
+// cost; a tile cut by a share's end is in several pieces, whose float32 sums a
+// short pass adds up in piece order.
+//
+// The decision and the cuts are made from every item of the list, whatever
+// the call's item mask: a masked call runs the same pieces of its items, so
+// that its results are those of the unmasked call bit for bit.
+struct KvSplit {
+  std::vector<nsp::KvPiece> pieces;     // share by share
+  std::vector<int> share;               // pieces[share[i]] .. pieces[share[i+1]-1]: share i
+  std::vector<nsp::KvReduce> reduce;
+  int slots = 0;
+};
+
+// kPieceCost: steps (about 1.7 us at head_dim 128) that a piece costs beside
+// its own -- the K / V rows, the first tiles of the ring, the stores.  Measured
+// whole backward at 2, 4, 8, 12 and 20 steps: 477, 472, 463, 456 and 459 us
+// (one 4096-token sequence), 1655, 1637, 1618, 1586 and - us (8192 tokens).
+// kMinPiece: the least steps worth a piece of their own (2, 4 and 8: 34.1,
+// 33.6 and 38.0 us on four items of 64 .. 512 tokens, 55.4 whole).
+// kSplitGain: the steps that the split has to gain beside a sixteenth of the
+// pass, for the sum pass; at 12 steps' gain (20 items of 300 tokens) the
+// backward takes 167 us against 176, at none (4 items of 4000) 1616 against
+// 1614.  Lists of more than kMaxSplitTiles key tiles fill the chip without.
+constexpr int64_t kPieceCost = 12, kMinPiece = 4, kSplitGain = 4;
+constexpr size_t kMaxSplitTiles = 4096;
+
+// Key tiles of one local KV head of an item, longest first: their query heads
+// (first | end << 16) and steps a query tile.
+struct KvGroup {
+  int item, g, heads;
+  int64_t w;
+};
+
+std::vector<KvGroup> kv_groups(const nsp_worklist *wl, int j) {
+  std::vector<KvGroup> out;
+  const int ql = wl->q_heads[2 * j], hq = wl->q_heads[2 * j + 1] - ql;
+  const int kl = wl->kv_heads[2 * j], hkv = wl->kv_heads[2 * j + 1] - kl;
+  for (int g = 0; g < hkv; ++g) {
+    int i0 = hq, i1 = 0;
+    for (int i = 0; i < hq; ++i)
+      if ((int)(((int64_t)(ql + i) * wl->hkv_total) / wl->hq_total) - kl == g) {
+        i0 = std::min(i0, i);
+        i1 = std::max(i1, i + 1);
+      }
+    if (i1 <= i0) i0 = i1 = 0;
+    out.push_back(KvGroup{j, g, i0 | (i1 << 16), (int64_t)(i1 - i0)});
+  }
+  return out;
+}
+
+// The shares of at most `cap` cost (steps + kPieceCost a piece): their number,
+// and the pieces if `out` is given.
+int kv_cut(const nsp_worklist *wl, const std::vector<KvGroup> &groups, int64_t cap, KvSplit *out) {
+  int shares = 0;
+  int64_t room = 0;
+  for (const KvGroup &gr : groups) {
+    const int L = wl->cu_seqlens[gr.item + 1] - wl->cu_seqlens[gr.item];
+    const int nk = (L + nsp::kBwdBN - 1) / nsp::kBwdBN, nqt = (L + nsp::kBwdBM - 1) / nsp::kBwdBM;
+    for (int n = 0; n < nk; ++n) {
+      const int64_t steps = gr.w * (nqt - (int64_t)n * nsp::kBwdBN / nsp::kBwdBM);
+      int64_t at = 0;
+      int parts = 0;
+      do {
+        const int64_t rest = steps - at;
+        if (room < kPieceCost + std::min(rest, kMinPiece)) {
+          ++shares;
+          room = cap;
+          if (out) out->share.push_back((int)out->pieces.size());
+        }
+        int64_t take = std::min(rest, room - kPieceCost);
+        if (take < rest && rest - take < kMinPiece) take = std::max(std::min(rest, kMinPiece), rest - kMinPiece);
+        if (out) out->pieces.push_back(nsp::KvPiece{gr.item, n, gr.heads, gr.g, (int)at, (int)take, -1, 0});
+        at += take;
+        room -= take + kPieceCost;
+        ++parts;
+      } while (at < steps);
+      if (out && parts > 1) {
+        out->reduce.push_back(nsp::KvReduce{gr.item, n, gr.g, out->slots, parts, {0, 0, 0}});
+        for (int k = 0; k < parts; ++k) out->pieces[out->pieces.size() - parts + k].slot = out->slots++;
+      }
+    }
+  }
+  if (out) out->share.push_back((int)out->pieces.size());
+  return shares;
+}
+
+size_t noalloc_part_room(int64_t lse_elems);
+
+// The split of a list's dK/dV pass; no pieces if it is not worth one.
+KvSplit kv_split(const nsp_worklist *wl) {
+  KvSplit sp;
+  std::vector<KvGroup> groups;
+  std::vector<int64_t> cost;
+  int64_t total = 0, lse_elems = 0;
+  for (int j = 0; j < wl->n_items; ++j) {
+    const int L = wl->cu_seqlens[j + 1] - wl->cu_seqlens[j];
+    lse_elems += (int64_t)L * (wl->q_heads[2 * j + 1] - wl->q_heads[2 * j]);
+    if (L == 0) continue;
+    const int nk = (L + nsp::kBwdBN - 1) / nsp::kBwdBN, nqt = (L + nsp::kBwdBM - 1) / nsp::kBwdBM;
+    for (const KvGroup &gr : kv_groups(wl, j)) {
+      groups.push_back(gr);
+      if (cost.size() + nk > kMaxSplitTiles) return sp;
+      for (int n = 0; n < nk; ++n) {
+        cost.push_back(gr.w * (nqt - (int64_t)n * nsp::kBwdBN / nsp::kBwdBM) + kPieceCost);
+        total += cost.back();
+      }
+    }
+  }
+  if (cost.empty()) return sp;
+  // the whole tiles, longest first, on the compute units as they go idle
+  std::sort(cost.begin(), cost.end(), std::greater<int64_t>());
+  std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> idle;
+  for (int c = 0; c < kAssumedCUs; ++c) idle.push(0);
+  int64_t whole = 0;
+  for (int64_t c : cost) {
+    const int64_t t = idle.top() + c;
+    idle.pop();
+    idle.push(t);
+    whole = std::max(whole, t);
+  }
+  // the least share that needs no more shares than compute units
+  int64_t lo = std::max(kPieceCost + kMinPiece, total / kAssumedCUs), hi = whole;
+  if (whole - lo < kSplitGain) return sp;
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) / 2;
+    if (kv_cut(wl, groups, mid, nullptr) <= kAssumedCUs) hi = mid;
+    else lo = mid + 1;
+  }
+  if (whole - lo < kSplitGain + lo / 16) return sp;
+  kv_cut(wl, groups, lo, &sp);
+  // (the allocation-free backward, whose results are the same, has to hold it)
+  const size_t slot_bytes = (size_t)nsp::kv_slot_floats(wl->head_dim) * sizeof(float);
+  if (sp.slots > nsp::kKvSlots || sp.slots * slot_bytes > noalloc_part_room(lse_elems)) return KvSplit();
+  return sp;
+}
+
+// The pieces of the call's items, workgroup by workgroup: consecutive shares
+// on one XCD (workgroup b starts on XCD b % 8), whose key tiles read the same
+// Q / dO rows.
+void add_split(HostAttnSched &s, const nsp_worklist *wl) {
+  const KvSplit sp = kv_split(wl);
+  if (sp.pieces.empty()) return;
+  std::vector<int> shares;                    // with pieces of the call's items
+  for (size_t i = 0; i + 1 < sp.share.size(); ++i)
+    for (int k = sp.share[i]; k < sp.share[i + 1]; ++k)
+      if (selected(wl, sp.pieces[k].item)) {
+        shares.push_back((int)i);
+        break;
+      }
+  const int n = (int)shares.size();
+  for (int b = 0; b < (n + kNumXcd - 1) / kNumXcd * kNumXcd; ++b) {
+    const int x = b % kNumXcd, lo = (int)((int64_t)n * x / kNumXcd), hi = (int)((int64_t)n * (x + 1) / kNumXcd);
+    const int first = (int)s.kv_pieces.size(), i = lo + b / kNumXcd;
+    if (i < hi)
+      for (int k = sp.share[shares[i]]; k < sp.share[shares[i] + 1]; ++k)
+        if (selected(wl, sp.pieces[k].item)) s.kv_pieces.push_back(sp.pieces[k]);
+    s.kv_wgs.push_back(int2{first, (int)s.kv_pieces.size()});
+  }
+  for (const nsp::KvReduce &r : sp.reduce)
+    if (selected(wl, r.item)) s.kv_reduce.push_back(r);
+}
+
 HostAttnSched build_attn_schedule(const nsp_worklist *wl) {
   HostAttnSched s;
   const int D = wl->head_dim;
@@ -494,6 +665,7 @@ HostAttnSched build_attn_schedule(const nsp_worklist *wl) {
   }
   s.q_rows = qo / D;
   lpt_sort(s.fwd_units, fcost);
+  add_split(s, wl);
   kv_balance(item_gangs, wl);
   for (const KvGang *g : kv_queue_order(item_gangs, s.kv_qoff))
     s.kv_units.insert(s.kv_units.end(), g->units.begin(), g->units.end());
@@ -627,10 +799,11 @@ nsp_status upload(const void *host, size_t bytes, void **dev) {
 }
 
 // The device image of an attention schedule: ItemDesc[n_items] | forward/dQ
-// units | dK/dV units | preprocess spans, each part 256-byte aligned.
+// units | dK/dV units | preprocess spans | split dK/dV, each part 256-byte
+// aligned.
 struct AttnBlob {
   std::vector<char> bytes;
-  size_t o_fwd = 0, o_kv = 0, o_kvq = 0, o_pre = 0;
+  size_t o_fwd = 0, o_kv = 0, o_kvq = 0, o_pre = 0, o_piece = 0, o_wg = 0, o_red = 0;
 };
 
 AttnBlob attn_blob(const HostAttnSched &hs) {
@@ -644,7 +817,10 @@ AttnBlob attn_blob(const HostAttnSched &hs) {
   b.o_kv = n_items + n_fwd;
   b.o_kvq = n_items + n_fwd + n_kv;
   b.o_pre = n_items + n_fwd + n_kv + n_kvq;
-  b.bytes.assign(b.o_pre + n_pre, 0);
+  b.o_piece = b.o_pre + n_pre;
+  b.o_wg = b.o_piece + align256(hs.kv_pieces.size() * sizeof(nsp::KvPiece));
+  b.o_red = b.o_wg + align256(hs.kv_wgs.size() * sizeof(int2));
+  b.bytes.assign(b.o_red + align256(hs.kv_reduce.size() * sizeof(nsp::KvReduce)), 0);
   auto put = [&](size_t off, const void *src, size_t n) {
     if (n) memcpy(b.bytes.data() + off, src, n);
   };
@@ -653,6 +829,9 @@ AttnBlob attn_blob(const HostAttnSched &hs) {
   put(b.o_kv, hs.kv_units.data(), hs.kv_units.size() * sizeof(int4));
   put(b.o_kvq, hs.kv_qoff.data(), hs.kv_qoff.size() * sizeof(int));
   put(b.o_pre, hs.pre_blocks.data(), hs.pre_blocks.size() * sizeof(nsp::PreBlock));
+  put(b.o_piece, hs.kv_pieces.data(), hs.kv_pieces.size() * sizeof(nsp::KvPiece));
+  put(b.o_wg, hs.kv_wgs.data(), hs.kv_wgs.size() * sizeof(int2));
+  put(b.o_red, hs.kv_reduce.data(), hs.kv_reduce.size() * sizeof(nsp::KvReduce));
   return b;
 }
 
@@ -664,6 +843,11 @@ nsp::Schedule attn_schedule_at(const HostAttnSched &hs, const AttnBlob &b, char 
   s.kv_units = reinterpret_cast<int4 *>(dev + b.o_kv);
   s.kv_qoff = reinterpret_cast<int *>(dev + b.o_kvq);
   s.pre_blocks = reinterpret_cast<nsp::PreBlock *>(dev + b.o_pre);
+  s.kv_pieces = reinterpret_cast<nsp::KvPiece *>(dev + b.o_piece);
+  s.kv_wgs = reinterpret_cast<int2 *>(dev + b.o_wg);
+  s.kv_reduce = reinterpret_cast<nsp::KvReduce *>(dev + b.o_red);
+  s.n_kv_wgs = (int)hs.kv_wgs.size();
+  s.n_kv_reduce = (int)hs.kv_reduce.size();
   s.n_items = (int)hs.items.size();
   s.n_fwd_units = (int)hs.fwd_units.size();
   s.n_kv_units = (int)hs.kv_units.size();
@@ -734,7 +918,9 @@ nsp_status hip_status(hipError_t err, const char *what) {
 }
 
 // Workspace layout: -Delta [lse_elems] | lse*log2(e) [lse_elems] (float32,
-// each 256-byte aligned) | 256 bytes of unit-queue heads.
+// each 256-byte aligned) | 256 bytes of unit-queue heads | the partial sums of
+// a split dK/dV pass (kv_part_bytes; the allocation-free backward holds what is
+// left of its scratch instead).
 size_t bwd_workspace_bytes(const WlInfo &w) {
   return 2 * align256((size_t)w.lse_elems * sizeof(float)) + 256;
 }
@@ -810,6 +996,11 @@ nsp_status validate_bwd(const nsp_worklist *wl, float softmax_scale, int32_t cau
 }
 
 // The largest sum_j L_j hq_j whose backward workspace fits the scratch.
+size_t noalloc_part_room(int64_t lse_elems) {
+  const size_t base = 2 * align256((size_t)lse_elems * sizeof(float)) + 256;
+  const size_t room = nsp::kScratchBytes - nsp::kScratchSchedBytes;
+  return base < room ? room - base : 0;
+}
 constexpr size_t noalloc_max_lse_elems() {
   return ((nsp::kScratchBytes - nsp::kScratchSchedBytes - 256) / 2 / 256 * 256) / sizeof(float);
 }
@@ -862,7 +1053,7 @@ nsp_status noalloc_upload(int dev, const std::string &key, const HostSched &h, c
 nsp_status launch_backward(int D, const nsp::Schedule &s, float softmax_scale, const void *q, const void *k,
                            const void *v, const void *o, nsp_dtype o_dtype, const void *dout, const float *lse,
                            void *dq, void *dk, void *dv, nsp_dtype grad_dtype, float *delta, float *lse2,
-                           int *queue, hipStream_t stream) {
+                           int *queue, float *part, hipStream_t stream) {
   nsp::AttnArgs a{};
   a.q = q;
   a.k = k;
@@ -888,8 +1079,17 @@ nsp_status launch_backward(int D, const nsp::Schedule &s, float softmax_scale, c
                      "backward preprocess launch"));
   a.units = s.kv_units;
   a.qoff = s.kv_qoff;
+  const bool split = s.n_kv_wgs > 0;
+  if (split) {
+    a.pieces = s.kv_pieces;
+    a.wgs = s.kv_wgs;
+    a.reduce = s.kv_reduce;
+    a.n_reduce = s.n_kv_reduce;
+    a.part = part;
+  }
   NSP_TRY(hip_status(timed_launch(K_DKDV, stream,
-                                  [&] { return nsp::launch_bwd_dkdv(D, g32, a, s.n_kv_units, stream); }),
+                                  [&] { return nsp::launch_bwd_dkdv(D, g32, a, split ? s.n_kv_wgs : s.n_kv_units,
+                                                                    stream); }),
                      "backward dK/dV launch"));
   a.units = s.fwd_units;
   return hip_status(timed_launch(K_DQ, stream, [&] { return nsp::launch_bwd_dq(D, g32, a, s.n_fwd_units, stream); }),
@@ -938,7 +1138,7 @@ nsp_status nsp_varlen_attn_fwd(const nsp_worklist *wl, float softmax_scale, int3
 size_t nsp_varlen_attn_bwd_workspace(const nsp_worklist *wl) {
   WlInfo w;
   if (validate_worklist(wl, &w) != NSP_OK) return 0;
-  return bwd_workspace_bytes(w);
+  return bwd_workspace_bytes(w) + nsp::kv_part_bytes(wl->head_dim);
 }
 
 nsp_status nsp_varlen_attn_bwd(const nsp_worklist *wl, float softmax_scale, int32_t causal, const void *q,
@@ -948,7 +1148,7 @@ nsp_status nsp_varlen_attn_bwd(const nsp_worklist *wl, float softmax_scale, int3
   g_last_error.clear();
   WlInfo w;
   NSP_TRY(validate_bwd(wl, softmax_scale, causal, q, k, v, o, o_dtype, dout, lse, dq, dk, dv, grad_dtype, &w));
-  const size_t need = bwd_workspace_bytes(w);
+  const size_t base = bwd_workspace_bytes(w), need = base + nsp::kv_part_bytes(wl->head_dim);
   if (w.q_elems > 0 && (!workspace || ws_bytes < need))
     return fail(NSP_EWORKSPACE, "workspace of %zu bytes given, %zu needed", workspace ? ws_bytes : 0, need);
   if (w.q_elems > 0 && misaligned(workspace, 256)) return fail(NSP_EINVAL, "workspace is not 256-byte aligned");
@@ -960,7 +1160,8 @@ nsp_status nsp_varlen_attn_bwd(const nsp_worklist *wl, float softmax_scale, int3
   char *ws = static_cast<char *>(workspace);
   return launch_backward(wl->head_dim, s, softmax_scale, q, k, v, o, o_dtype, dout, lse, dq, dk, dv, grad_dtype,
                          reinterpret_cast<float *>(ws), reinterpret_cast<float *>(ws + lse_bytes),
-                         reinterpret_cast<int *>(ws + 2 * lse_bytes), stream);
+                         reinterpret_cast<int *>(ws + 2 * lse_bytes),
+                         reinterpret_cast<float *>(ws + base), stream);
 }
 
 nsp_status nsp_varlen_attn_bwd_noalloc(const nsp_worklist *wl, float softmax_scale, int32_t causal, const void *q,
@@ -993,7 +1194,7 @@ nsp_status nsp_varlen_attn_bwd_noalloc(const nsp_worklist *wl, float softmax_sca
   const size_t lse_bytes = align256((size_t)w.lse_elems * sizeof(float));
   return launch_backward(wl->head_dim, s, softmax_scale, q, k, v, o, o_dtype, dout, lse, dq, dk, dv, grad_dtype,
                          reinterpret_cast<float *>(ws + 256), reinterpret_cast<float *>(ws + 256 + lse_bytes),
-                         reinterpret_cast<int *>(ws), stream);
+                         reinterpret_cast<int *>(ws), reinterpret_cast<float *>(ws + ws_need), stream);
 }
 
 static nsp_status relayout(const nsp_worklist *wl, nsp_kind kind, nsp_dtype dtype, bool pack, nsp_replica rep,

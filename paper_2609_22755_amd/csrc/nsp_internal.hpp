@@ -56,6 +56,28 @@ constexpr int kKvTileMask = kKvDescending - 1;
 // Key-tile pairs per dK/dV gang (the workgroups one XCD runs at once).
 constexpr int kKvGang = 32;
 
+// Split dK/dV units (lists whose units would leave compute units idle, see
+// kv_split in the schedule builder).  A piece is a run of a key tile's steps
+// (ascending query tiles from the diagonal, the query heads of the group
+// inner): all of them (slot < 0: the workgroup stores the gradients), or some,
+// whose float32 sums go to a slot of the partial buffer.
+struct KvPiece {
+  int32_t item, tile, heads, g;   // as in a dK/dV unit, no direction flag
+  int32_t first, count;           // steps
+  int32_t slot, pad;
+};
+// A key tile in several pieces: its partial sums are slots slot .. slot+count-1.
+struct KvReduce {
+  int32_t item, tile, g, slot, count, pad[3];
+};
+// Floats of one slot: dK then dV of a 128-key tile.
+constexpr int64_t kv_slot_floats(int D) { return 2 * (int64_t)kBwdBN * D; }
+// Slots of the partial buffer: the cuts between 256 shares make at most 2 * 255
+// pieces of cut tiles.  The buffer has this size for every list, so that a
+// workspace of a larger list serves a smaller one.
+constexpr int kKvSlots = 512;
+constexpr size_t kv_part_bytes(int D) { return kKvSlots * (size_t)kv_slot_floats(D) * sizeof(float); }
+
 // Work unit: int4 {item, tile, a, b}.
 //   forward / dQ : a = local query head, b = local KV head
 //   dK / dV      : a = first local query head | (end local query head << 16),
@@ -65,6 +87,10 @@ struct Schedule {
   int4 *fwd_units = nullptr;   // device, LPT order (forward and dQ)
   int4 *kv_units = nullptr;    // device, dK/dV units, per-XCD queues one after another
   int *kv_qoff = nullptr;      // device, 9 ints: queue x is kv_units[kv_qoff[x] .. kv_qoff[x+1])
+  KvPiece *kv_pieces = nullptr;   // device, split dK/dV: the pieces, workgroup by workgroup
+  int2 *kv_wgs = nullptr;         // device, workgroup b runs pieces kv_wgs[b].x .. kv_wgs[b].y - 1
+  KvReduce *kv_reduce = nullptr;  // device, the key tiles in several pieces
+  int n_kv_wgs = 0, n_kv_reduce = 0;
   PreBlock *pre_blocks = nullptr; // device, the preprocess workgroups of the items the call computes
   int n_items = 0;
   int n_fwd_units = 0;
@@ -88,6 +114,11 @@ struct AttnArgs {
   const ItemDesc *items;
   const PreBlock *pre_blocks;
   const int4 *units;
+  const KvPiece *pieces;  // split dK/dV
+  const int2 *wgs;
+  const KvReduce *reduce;
+  int n_reduce;
+  float *part;            // split dK/dV: partial sums, kv_slot_floats a slot
   const int *qoff;        // dK/dV: start of each XCD's queue in `units`, and the end
   int n_items;
   float scale;            // softmax scale
@@ -122,6 +153,8 @@ hipError_t compute_units(int *cus);
 hipError_t launch_attn_fwd(int head_dim, bool o_f32, const AttnArgs &a, int n_units, hipStream_t s);
 hipError_t launch_bwd_preprocess(int head_dim, bool o_f32, const AttnArgs &a, int n_blocks, hipStream_t s);
 hipError_t launch_bwd_dq(int head_dim, bool g_f32, const AttnArgs &a, int n_units, hipStream_t s);
+// With a.wgs the split pass (n_units workgroups over a.pieces, then the sums of
+// the a.n_reduce tiles of a.reduce), else the units of a.units.
 hipError_t launch_bwd_dkdv(int head_dim, bool g_f32, const AttnArgs &a, int n_units, hipStream_t s);
 hipError_t launch_relayout(const void *src, void *dst, const CopyTask *tasks, int n_tasks,
                            int sum_mode, hipStream_t s);

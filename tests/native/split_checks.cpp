@@ -1,0 +1,155 @@
+// The split of the dK/dV pass (kv_split, add_split in nsp_abi.cpp) on seeded
+// random work lists, against the rules it has to keep: every step of every key
+// tile in exactly one piece, in order; a tile in several pieces has one slot
+// for each, consecutive and its own, and one entry in the sum pass; no more
+// shares than compute units and none much longer than the mean; a masked call
+// runs exactly the unmasked call's pieces of its items; the workspace that the
+// query asks for and the allocation-free scratch hold the slots.  Built with
+// g++ from the library's host sources; prints "split checks ok".
+#include "nsp_abi.cpp"
+
+#include <cstdlib>
+#include <map>
+#include <random>
+#include <set>
+
+#define CHECK(c)                                                                 \
+  do {                                                                           \
+    if (!(c)) {                                                                  \
+      std::fprintf(stderr, "%s:%d: check failed: %s\n", __FILE__, __LINE__, #c); \
+      std::exit(1);                                                              \
+    }                                                                            \
+  } while (0)
+
+namespace {
+
+std::mt19937_64 rng(411);
+int uni(int lo, int hi) { return std::uniform_int_distribution<int>(lo, hi)(rng); }
+
+using Key = std::tuple<int, int, int>;   // item, tile, KV head
+
+void check_list(const nsp_worklist &w, const std::vector<uint8_t> &mask, int *n_split) {
+  WlInfo info;
+  CHECK(validate_worklist(&w, &info) == NSP_OK);
+  const KvSplit sp = kv_split(&w);
+  const size_t slot_bytes = nsp::kv_slot_floats(w.head_dim) * sizeof(float);
+  CHECK(nsp_varlen_attn_bwd_workspace(&w) == bwd_workspace_bytes(info) + nsp::kKvSlots * slot_bytes);
+  HostAttnSched full;
+  add_split(full, &w);
+  if (sp.pieces.empty()) {
+    CHECK(full.kv_wgs.empty() && sp.slots == 0);
+    return;
+  }
+  ++*n_split;
+  CHECK(bwd_workspace_bytes(info) + sp.slots * slot_bytes <= nsp::kScratchBytes - nsp::kScratchSchedBytes);
+  CHECK(sp.slots <= nsp::kKvSlots);
+  // pieces of each tile, in launch-list order of the whole call
+  std::map<Key, std::vector<nsp::KvPiece>> tiles;
+  int64_t total = 0, longest = 0;
+  for (size_t i = 0; i + 1 < sp.share.size(); ++i) {
+    int64_t c = 0;
+    for (int k = sp.share[i]; k < sp.share[i + 1]; ++k) {
+      tiles[Key(sp.pieces[k].item, sp.pieces[k].tile, sp.pieces[k].g)].push_back(sp.pieces[k]);
+      c += sp.pieces[k].count + kPieceCost;
+    }
+    CHECK(c > 0);
+    total += c;
+    longest = std::max(longest, c);
+  }
+  CHECK((int)sp.share.size() - 1 <= kAssumedCUs);
+  CHECK(longest <= 2 * (total / kAssumedCUs + kPieceCost + kMinPiece));
+  std::map<Key, nsp::KvReduce> sums;
+  for (const nsp::KvReduce &r : sp.reduce) CHECK(sums.emplace(Key(r.item, r.tile, r.g), r).second);
+  std::set<int> slots;
+  size_t n_tiles = 0;
+  for (int j = 0; j < w.n_items; ++j) {
+    const int L = w.cu_seqlens[j + 1] - w.cu_seqlens[j];
+    const int nk = (L + 127) / 128, nq = (L + 63) / 64;
+    for (int g = 0; g < w.kv_heads[2 * j + 1] - w.kv_heads[2 * j]; ++g) {
+      int h0 = -1, h1 = -1;
+      for (int i = w.q_heads[2 * j]; i < w.q_heads[2 * j + 1]; ++i)
+        if ((int64_t)i * w.hkv_total / w.hq_total == w.kv_heads[2 * j] + g) {
+          if (h0 < 0) h0 = i - w.q_heads[2 * j];
+          h1 = i - w.q_heads[2 * j] + 1;
+        }
+      for (int n = 0; n < nk; ++n, ++n_tiles) {
+        auto it = tiles.find(Key(j, n, g));
+        CHECK(it != tiles.end());
+        int64_t at = 0;
+        const int steps = h0 < 0 ? 0 : (h1 - h0) * (nq - 2 * n);
+        auto r = sums.find(Key(j, n, g));
+        CHECK((r != sums.end()) == (it->second.size() > 1));
+        for (size_t k = 0; k < it->second.size(); ++k) {
+          const nsp::KvPiece &p = it->second[k];
+          CHECK(p.first == at && (p.count > 0 || steps == 0));
+          CHECK(p.heads == (h0 < 0 ? 0 : (h0 | (h1 << 16))));
+          at += p.count;
+          if (r == sums.end()) CHECK(p.slot == -1);
+          else CHECK(p.slot == r->second.slot + (int)k && p.slot < sp.slots && slots.insert(p.slot).second);
+        }
+        CHECK(at == steps);
+        if (r != sums.end()) CHECK(r->second.count == (int)it->second.size());
+      }
+    }
+  }
+  CHECK(n_tiles == tiles.size() && (int)slots.size() == sp.slots);
+  // the device lists of the whole and of a masked call
+  for (int pass = 0; pass < 2; ++pass) {
+    nsp_worklist m = w;
+    m.item_mask = pass ? mask.data() : nullptr;
+    HostAttnSched s;
+    add_split(s, &m);
+    CHECK(nsp_varlen_attn_bwd_workspace(&m) == nsp_varlen_attn_bwd_workspace(&w));
+    size_t want = 0, sums_want = 0;
+    for (const nsp::KvPiece &p : sp.pieces) want += selected(&m, p.item);
+    for (const nsp::KvReduce &r : sp.reduce) sums_want += selected(&m, r.item);
+    CHECK(s.kv_pieces.size() == want && s.kv_reduce.size() == sums_want);
+    int at = 0;
+    for (const int2 &wg : s.kv_wgs) {
+      CHECK(wg.x == at && wg.y >= at);
+      at = wg.y;
+    }
+    CHECK(at == (int)want && s.kv_wgs.size() % 8 == 0);
+    for (const nsp::KvPiece &p : s.kv_pieces) {
+      CHECK(selected(&m, p.item));
+      bool same = false;
+      for (const nsp::KvPiece &o : tiles[Key(p.item, p.tile, p.g)]) same |= memcmp(&o, &p, sizeof p) == 0;
+      CHECK(same);
+    }
+  }
+}
+
+}  // namespace
+
+int main() {
+  int n_split = 0;
+  for (int rep = 0; rep < 400; ++rep) {
+    static const int heads[][2] = {{32, 4}, {8, 2}, {16, 16}, {4, 1}, {12, 6}};
+    const int *h = heads[uni(0, 4)];
+    const int n = uni(1, 6), top = 1 << uni(6, 14);
+    std::vector<int32_t> cu(1, 0), qh, kvh;
+    std::vector<uint8_t> mask;
+    for (int j = 0; j < n; ++j) {
+      cu.push_back(cu.back() + (uni(0, 6) ? uni(1, top) : 0));
+      const int group = h[0] / h[1];
+      const int q0 = uni(0, h[0] - 1), q1 = uni(q0 + 1, h[0]);
+      qh.push_back(q0);
+      qh.push_back(q1);
+      kvh.push_back(uni(0, q0 / group));               // KV heads without query heads among them
+      kvh.push_back(uni((q1 - 1) / group + 1, h[1]));
+      mask.push_back(uni(0, 1));
+    }
+    nsp_worklist w{};
+    w.n_items = n;
+    w.cu_seqlens = cu.data();
+    w.q_heads = qh.data();
+    w.kv_heads = kvh.data();
+    w.hq_total = h[0];
+    w.hkv_total = h[1];
+    w.head_dim = uni(0, 1) ? 128 : 64;
+    check_list(w, mask, &n_split);
+  }
+  CHECK(n_split > 100 && n_split < 400);
+  std::printf("split checks ok (%d of 400 lists split)\n", n_split);
+  return 0;
+}
