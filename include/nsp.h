@@ -268,17 +268,15 @@ nsp_status nsp_recompute_plan(const nsp_worklist *wl, int64_t budget_bytes, nsp_
  *           tile by tile, every query head of a tile in turn, up from its
  *           diagonal, or down from the item end when desc = 1.
  *   Forward/dQ units are generated item by item (m, then i) and sorted
- *   longest work first (stable).  Slot b of that list belongs to XCD b % 8:
- *   a one-shot grid's workgroup b starts there (the hardware deals
- *   workgroups round-robin over the 8 XCDs), and the persistent passes take
- *   slot b from the queue of XCD b % 8, their own XCD's queue first, the
- *   others' once it is empty.  When the longest scheduled item's K and V
+ *   longest work first (stable).  When the longest scheduled item's K and V
  *   slices of one head (4 L_j head_dim bytes) exceed one XCD's L2 (4 MiB),
- *   every full chunk of 8 x 32 units gives XCD x one run of 32 consecutive
- *   units of the sorted order -- run x in even chunks, run 7 - x in odd
- *   ones -- so that units streaming the same K/V tiles share an XCD's L2;
- *   the last, incomplete chunk keeps the sorted order.  Otherwise the
- *   sorted order is launched as it is.
+ *   every full chunk of 8 x 32 units gives slots b % 8 == x of the chunk one
+ *   run of 32 consecutive units of the sorted order -- run x in even chunks,
+ *   run 7 - x in odd ones; the last, incomplete chunk keeps the sorted order.
+ *   The passes run these units on per-XCD queues, in gangs of at most 16 units
+ *   of one item and KV head (at most a quarter of the item's query tiles, or
+ *   two), which stream the same K/V tiles at the same time; gangs go to the
+ *   queues like the dK/dV ones below.
  *   dK/dV units are grouped into gangs per item: for n < nk/2 (nk key tiles)
  *   the pairs (n, nk-1-n) over the item's KV heads in order (g, then n), 32
  *   pairs a gang; a gang lists the 32 units n with desc = 1, then the
@@ -300,7 +298,7 @@ nsp_status nsp_recompute_plan(const nsp_worklist *wl, int64_t budget_bytes, nsp_
  *   gangs, and the queues are laid out one after another (see
  *   nsp_attn_kv_queues).  The persistent dK/dV pass takes its own XCD's
  *   queue first, the others' once it is empty; a one-shot grid (no more
- *   units than compute units) runs slot b in workgroup b.
+ *   units than compute units) runs entry b / 8 of queue b % 8 in workgroup b.
  *   Items with L_j = 0 or outside wl->item_mask contribute no units.
  *   units     out, capacity x 4 int32 in the order above (may be NULL if
  *             capacity = 0: a size query)

@@ -325,20 +325,14 @@ __device__ __forceinline__ void dq_unit(const AttnArgs &a, int slot, bf16 *smem)
   }
 }
 
-// dQ pass.  With queue heads (more units than compute units), one
-// persistent workgroup per compute unit takes units from the per-XCD queues,
-// as the dK/dV pass does; without (heads == nullptr), workgroup b runs launch
-// slot b.
+// dQ pass over the per-XCD queues (a.qoff), as the dK/dV pass: with queue heads
+// one persistent workgroup per compute unit, without one workgroup per unit.
 template <int D, bool G_F32>
-__global__ void __launch_bounds__(64 * kFwdWaves, 1) bwd_dq_kernel(AttnArgs a, int *heads, int n_units) {
+__global__ void __launch_bounds__(64 * kFwdWaves, 1) bwd_dq_kernel(AttnArgs a, int *heads) {
   __shared__ __attribute__((aligned(16))) bf16 smem[8 * DqCfg<D>::TILE];
   __shared__ int s_slot;
-  const int own = (int)(__builtin_amdgcn_s_getreg(kHwRegXccId) % kXcdQueues);
-  for (int iter = 0;; ++iter) {
-    const int slot = heads ? next_queue_slot(heads, n_units, own, &s_slot) : (iter == 0 ? (int)blockIdx.x : -1);
-    if (slot < 0) break;
-    dq_unit<D, G_F32>(a, slot, smem);
-  }
+  UnitQueue q(heads, a.qoff, &s_slot);
+  for (int slot = q.first(); slot >= 0; slot = q.next()) dq_unit<D, G_F32>(a, slot, smem);
 }
 
 // ----------------------------------------------------------------- dK/dV --
@@ -879,6 +873,9 @@ __device__ __forceinline__ void dkdv_unit(const AttnArgs &a, int item, int tile,
 #undef NSP_KV_STEP
   }
 
+  // nothing may still be loading into the stages when the next unit fills them
+  // (the stores below stay in flight)
+  wait_all_loads();
   kv_drain<D>(st);
   if (PIECE && part) {
     // accumulator order: lane by lane, 16 bytes each, so that every store and
@@ -913,12 +910,11 @@ __device__ __forceinline__ void dkdv_unit(const AttnArgs &a, int item, int tile,
   }
 }
 
-// dK/dV pass.  With queue heads (more units than compute units), one
-// persistent workgroup per compute unit takes units from the per-XCD queues,
-// stored one after another (a.qoff; next_range_slot); without
-// (heads == nullptr), workgroup b runs launch slot b.
+// dK/dV pass over the per-XCD queues (a.qoff): with queue heads (more units
+// than compute units) one persistent workgroup per compute unit, without one
+// workgroup per unit.
 template <int D, bool G_F32>
-__global__ void __launch_bounds__(256, 1) bwd_dkdv_kernel(AttnArgs a, int *heads, int n_units) {
+__global__ void __launch_bounds__(256, 1) bwd_dkdv_kernel(AttnArgs a, int *heads) {
   using C = KvCfg<D>;
   // four pipeline stages (distinct objects, so that the compiler can tell the
   // stage being filled from the ones being read)
@@ -927,15 +923,11 @@ __global__ void __launch_bounds__(256, 1) bwd_dkdv_kernel(AttnArgs a, int *heads
   __shared__ __attribute__((aligned(16))) bf16 stg2[C::STAGE];
   __shared__ __attribute__((aligned(16))) bf16 stg3[C::STAGE];
   __shared__ int s_slot;
-  const int own = (int)(__builtin_amdgcn_s_getreg(kHwRegXccId) % kXcdQueues);
-  for (int iter = 0;; ++iter) {
-    const int slot = heads ? next_range_slot(heads, a.qoff, own, &s_slot) : (iter == 0 ? (int)blockIdx.x : -1);
-    if (slot < 0) break;
+  UnitQueue q(heads, a.qoff, &s_slot);
+  for (int slot = q.first(); slot >= 0; slot = q.next()) {
     const int4 u = a.units[slot];
     dkdv_unit<D, G_F32, false>(a, u.x, u.y & kKvTileMask, (u.y & kKvDescending) != 0, u.z, u.w, 0, 0, nullptr, stg0,
                                stg1, stg2, stg3);
-    // nothing may still be loading into the stages when the next unit fills them
-    __builtin_amdgcn_s_waitcnt(0);
   }
 }
 
@@ -957,9 +949,8 @@ __global__ void __launch_bounds__(256, 1) bwd_dkdv_split_kernel(AttnArgs a) {
     const KvPiece p = a.pieces[i];
     dkdv_unit<D, G_F32, true>(a, p.item, p.tile, false, p.heads, p.g, p.first, p.count,
                               p.slot < 0 ? nullptr : a.part + p.slot * kv_slot_floats(D), stg0, stg1, stg2, stg3);
-    // nothing may still be loading into the stages, and no wave still reading
-    // them, when the next piece fills them
-    __builtin_amdgcn_s_waitcnt(0);
+    // no wave may still be reading the stages when the next piece fills them
+    wait_lds();
     stage_barrier();
   }
 }
@@ -1015,14 +1006,14 @@ hipError_t launch_bwd_preprocess(int head_dim, bool o_f32, const AttnArgs &a, in
 
 // Grid and queue heads of a pass over n_units units: with more units than
 // compute units, one persistent workgroup per compute unit (the kernels'
-// resources allow no more) and the heads; otherwise one workgroup per unit
-// and no heads.
-static hipError_t pass_grid(int n_units, int *heads_if_persistent, dim3 *grid, int **heads) {
+// resources allow no more) and the heads, unless the list asks for one
+// workgroup per unit; otherwise one workgroup per unit and no heads.
+static hipError_t pass_grid(const AttnArgs &a, int n_units, int *heads_if_persistent, dim3 *grid, int **heads) {
   int cus = 0;
   hipError_t e = compute_units(&cus);
   if (e != hipSuccess) return e;
-  const bool persistent = n_units > cus;
-  *grid = dim3(persistent ? cus : n_units);
+  const bool persistent = n_units > cus && !a.one_shot;
+  *grid = dim3(persistent ? cus : kXcdQueues * a.q_longest);
   *heads = persistent ? heads_if_persistent : nullptr;
   return hipSuccess;
 }
@@ -1031,14 +1022,14 @@ hipError_t launch_bwd_dq(int head_dim, bool g_f32, const AttnArgs &a, int n_unit
   if (n_units == 0) return hipSuccess;
   dim3 grid, block(64 * kFwdWaves);
   int *heads = nullptr;
-  hipError_t e = pass_grid(n_units, a.queue + kDqQueue0, &grid, &heads);
+  hipError_t e = pass_grid(a, n_units, a.queue + kDqQueue0, &grid, &heads);
   if (e != hipSuccess) return e;
   if (head_dim == 128) {
-    if (g_f32) bwd_dq_kernel<128, true><<<grid, block, 0, s>>>(a, heads, n_units);
-    else bwd_dq_kernel<128, false><<<grid, block, 0, s>>>(a, heads, n_units);
+    if (g_f32) bwd_dq_kernel<128, true><<<grid, block, 0, s>>>(a, heads);
+    else bwd_dq_kernel<128, false><<<grid, block, 0, s>>>(a, heads);
   } else {
-    if (g_f32) bwd_dq_kernel<64, true><<<grid, block, 0, s>>>(a, heads, n_units);
-    else bwd_dq_kernel<64, false><<<grid, block, 0, s>>>(a, heads, n_units);
+    if (g_f32) bwd_dq_kernel<64, true><<<grid, block, 0, s>>>(a, heads);
+    else bwd_dq_kernel<64, false><<<grid, block, 0, s>>>(a, heads);
   }
   return hipGetLastError();
 }
@@ -1058,14 +1049,14 @@ hipError_t launch_bwd_dkdv(int head_dim, bool g_f32, const AttnArgs &a, int n_un
   }
   dim3 grid, block(256);
   int *heads = nullptr;
-  hipError_t e = pass_grid(n_units, a.queue + kKvQueue0, &grid, &heads);
+  hipError_t e = pass_grid(a, n_units, a.queue + kKvQueue0, &grid, &heads);
   if (e != hipSuccess) return e;
   if (head_dim == 128) {
-    if (g_f32) bwd_dkdv_kernel<128, true><<<grid, block, 0, s>>>(a, heads, n_units);
-    else bwd_dkdv_kernel<128, false><<<grid, block, 0, s>>>(a, heads, n_units);
+    if (g_f32) bwd_dkdv_kernel<128, true><<<grid, block, 0, s>>>(a, heads);
+    else bwd_dkdv_kernel<128, false><<<grid, block, 0, s>>>(a, heads);
   } else {
-    if (g_f32) bwd_dkdv_kernel<64, true><<<grid, block, 0, s>>>(a, heads, n_units);
-    else bwd_dkdv_kernel<64, false><<<grid, block, 0, s>>>(a, heads, n_units);
+    if (g_f32) bwd_dkdv_kernel<64, true><<<grid, block, 0, s>>>(a, heads);
+    else bwd_dkdv_kernel<64, false><<<grid, block, 0, s>>>(a, heads);
   }
   return hipGetLastError();
 }

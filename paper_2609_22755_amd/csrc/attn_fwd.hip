@@ -375,23 +375,19 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs &a, int slot, bf16 *smem
   }
 }
 
-// The forward pass.  With queue heads (a.queue: kXcdQueues heads and a
-// count of workgroups done, zero at launch), one persistent workgroup per
-// compute unit takes units from the per-XCD queues, and the last workgroup
-// to finish sets them back to zero for the next launch on the same stream.
-// Without (a.queue == nullptr), workgroup b runs launch slot b.
+// The forward pass over the per-XCD queues (a.qoff).  With queue heads (a.queue:
+// kXcdQueues heads and a count of workgroups done, zero at launch), one
+// persistent workgroup per compute unit, and the last workgroup to finish sets
+// them back to zero for the next launch on the same stream.  Without
+// (a.queue == nullptr), one workgroup per unit.
 template <int D, bool O_F32>
-__global__ void __launch_bounds__(64 * kFwdWaves, 1) attn_fwd_kernel(AttnArgs a, int n_units) {
+__global__ void __launch_bounds__(64 * kFwdWaves, 1) attn_fwd_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(16))) bf16 smem[8 * FwdCfg<D>::TILE];
   __shared__ int s_slot;
-  const int own = (int)(__builtin_amdgcn_s_getreg(kHwRegXccId) % kXcdQueues);
-  for (int iter = 0;; ++iter) {
-    const int slot = a.queue ? next_queue_slot(a.queue, n_units, own, &s_slot) : (iter == 0 ? (int)blockIdx.x : -1);
-    if (slot < 0) break;
-    fwd_unit<D, O_F32>(a, slot, smem);
-  }
+  UnitQueue q(a.queue, a.qoff, &s_slot);
+  for (int slot = q.first(); slot >= 0; slot = q.next()) fwd_unit<D, O_F32>(a, slot, smem);
   // every fetch of this workgroup has returned before its count is added
-  // (thread 0 made both, the fetch's result decided to stop), so the last
+  // (one wave makes both, the fetch's result decided to stop), so the last
   // workgroup counted knows that no fetch of this launch is still to come
   if (a.queue && threadIdx.x == 0 && atomicAdd(a.queue + kXcdQueues, 1) == (int)gridDim.x - 1) {
     for (int x = 0; x < kXcdQueues; ++x) atomicExch(a.queue + x, 0);
@@ -472,19 +468,20 @@ hipError_t launch_attn_fwd(int head_dim, bool o_f32, const AttnArgs &a_in, int n
   hipError_t e = compute_units(&cus);
   if (e != hipSuccess) return e;
   // with more units than compute units, one persistent workgroup per compute
-  // unit (its resources allow no more) on the stream's counter block;
-  // otherwise, or without a block, one workgroup per unit
-  if (n_units > cus) {
+  // unit (its resources allow no more) on the stream's counter block, unless
+  // the list asks for one workgroup per unit; otherwise, or without a block, one
+  // workgroup per unit
+  if (n_units > cus && !a.one_shot) {
     e = fwd_queue_block(s, &a.queue);
     if (e != hipSuccess) return e;
   }
-  dim3 grid(a.queue ? cus : n_units), block(64 * kFwdWaves);
+  dim3 grid(a.queue ? cus : kXcdQueues * a.q_longest), block(64 * kFwdWaves);
   if (head_dim == 128) {
-    if (o_f32) attn_fwd_kernel<128, true><<<grid, block, 0, s>>>(a, n_units);
-    else attn_fwd_kernel<128, false><<<grid, block, 0, s>>>(a, n_units);
+    if (o_f32) attn_fwd_kernel<128, true><<<grid, block, 0, s>>>(a);
+    else attn_fwd_kernel<128, false><<<grid, block, 0, s>>>(a);
   } else {
-    if (o_f32) attn_fwd_kernel<64, true><<<grid, block, 0, s>>>(a, n_units);
-    else attn_fwd_kernel<64, false><<<grid, block, 0, s>>>(a, n_units);
+    if (o_f32) attn_fwd_kernel<64, true><<<grid, block, 0, s>>>(a);
+    else attn_fwd_kernel<64, false><<<grid, block, 0, s>>>(a);
   }
   return hipGetLastError();
 }

@@ -244,59 +244,85 @@ __device__ __forceinline__ float pin(float x) {
 // The wave index as a scalar (wave-uniform) value.
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
-// Per-XCD unit queues of the persistent passes.  The unit list is in launch
-// order and slot b belongs to XCD b % 8, so queue x holds slots x, x + 8,
-// x + 16, ... and its head (an int in device memory, zero before the pass)
-// counts the slots taken.  A workgroup drains the queue of its own XCD first
-// -- keeping the XCD runs of the order, and their L2 reuse, on one XCD --
-// then takes what is left in the others: XCDs run at different speeds, and a
-// fixed slot-to-XCD map would leave the fast ones idle at the end.  Every
-// head only grows, so each workgroup stops after at most n_units + 8
-// fetches.  One lane fetches; the slot reaches the workgroup through LDS
-// between two barriers (the second also keeps the next unit's tile loads
-// from overwriting LDS that a wave still reads).  Returns -1 when every
-// queue is empty.
+// Wait for this wave's LDS (and scalar) operations only.
+__device__ __forceinline__ void wait_lds() { wait_loads_le<63>(); }
+
+// Per-XCD unit queues of a pass: queue x holds the units off[x] .. off[x+1]-1
+// of the unit list.  Workgroup b starts with entry b / 8 of queue b % 8 (it
+// starts on XCD b % 8).  Without heads that is all; with them (ints in device
+// memory, zero before the pass; the head of queue x counts the entries taken
+// after the first ones) a workgroup goes on until every queue is empty.  It
+// drains the queue of its own XCD first -- keeping the gangs of the order, and
+// their L2 reuse, on one XCD -- then takes what is left in the others: XCDs run
+// at different speeds, and a fixed unit-to-XCD map would leave the fast ones
+// idle at the end.
+//
+// One wave fetches.  The atomics go to memory past the XCDs' L2, about 1 us
+// each, so the eight heads are read together to see which queue has units
+// left: adding to eight empty queues in turn took 15 to 20 us at the end of a
+// pass (12 items of 512 tokens, forward: 69 us, one workgroup a unit 51 us).
+// Asking for the next unit while one runs was no faster: a unit taken that
+// early is not there for the compute unit that goes idle first (32 items of
+// 2048 tokens, forward: 1343 us against 1248).  Heads only grow, and a queue
+// found empty is not asked again, so every workgroup stops after at most
+// n_units + 8 fetches.
 constexpr int kXcdQueues = 8;
 // s_getreg operand for HW_REG_XCC_ID (register 20, bits 0..15): the XCD a
 // wave runs on
 constexpr int kHwRegXccId = 20 | (0 << 6) | ((16 - 1) << 11);
 
-__device__ __forceinline__ int next_queue_slot(int *heads, int n_units, int own, int *s_slot) {
-  if (threadIdx.x == 0) {
-    int slot = -1;
-    for (int t = 0; t < kXcdQueues && slot < 0; ++t) {
-      const int x = (own + t) % kXcdQueues;
-      const int k = atomicAdd(heads + x, 1);
-      if (x + kXcdQueues * k < n_units) slot = x + kXcdQueues * k;
-    }
-    *s_slot = slot;
-  }
-  __syncthreads();
-  const int slot = *s_slot;
-  __syncthreads();
-  return slot;
-}
+struct UnitQueue {
+  int *heads;
+  const int *off;
+  int *s_slot;         // in LDS
+  unsigned empty;      // queues found empty
 
-// The same over per-XCD queues stored one after another: queue x holds the
-// slots off[x] .. off[x+1]-1 (off: kXcdQueues + 1 ints).
-__device__ __forceinline__ int next_range_slot(int *heads, const int *off, int own, int *s_slot) {
-  if (threadIdx.x == 0) {
-    int slot = -1;
-    for (int t = 0; t < kXcdQueues && slot < 0; ++t) {
-      const int x = (own + t) % kXcdQueues;
-      const int b = off[x], e = off[x + 1];
-      if (b < e) {
-        const int k = atomicAdd(heads + x, 1);
-        if (b + k < e) slot = b + k;
+  __device__ __forceinline__ UnitQueue(int *heads_, const int *off_, int *s_slot_)
+      : heads(heads_), off(off_), s_slot(s_slot_), empty(0) {}
+  __device__ __forceinline__ int count(int x) const { return off[x + 1] - off[x]; }
+  // entries of queue x that the workgroups start with
+  __device__ __forceinline__ int started(int x) const { return ((int)gridDim.x - x + kXcdQueues - 1) / kXcdQueues; }
+
+  // The next unit of the own queue, or of the first one after it that is not
+  // empty (-1: none).  By a whole wave: lane x looks at queue x.
+  __device__ __forceinline__ int fetch() {
+    const int lane = threadIdx.x & 63, own = (int)(__builtin_amdgcn_s_getreg(kHwRegXccId) % kXcdQueues);
+    int y = own;
+    for (;;) {
+      if (!(empty >> y & 1)) {
+        int k = 0;
+        if (lane == 0) k = atomicAdd(heads + y, 1);
+        k = started(y) + __builtin_amdgcn_readfirstlane(k);
+        if (k < count(y)) return off[y] + k;
+        empty |= 1u << y;
       }
+      const int x = lane & 7;
+      const int h = __hip_atomic_load(heads + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const unsigned left = (unsigned)__ballot(started(x) + h < count(x)) & 0xffu & ~empty;
+      if (left == 0) return -1;
+      y = (own + __builtin_ctz((left | left << kXcdQueues) >> own)) % kXcdQueues;
     }
-    *s_slot = slot;
   }
-  __syncthreads();
-  const int slot = *s_slot;
-  __syncthreads();
-  return slot;
-}
+  // The workgroup's first unit (-1: none).
+  __device__ __forceinline__ int first() {
+    const int x = (int)blockIdx.x % kXcdQueues, i = (int)blockIdx.x / kXcdQueues;
+    if (i < count(x)) return off[x] + i;
+    return next();
+  }
+  // Its next unit (-1: none).  Also the barrier between a unit's last LDS
+  // accesses and the next unit's first; stores to memory stay in flight across
+  // it.
+  __device__ __forceinline__ int next() {
+    if (!heads) return -1;
+    if (wave_id() == 0) {
+      const int s = fetch();
+      if (threadIdx.x == 0) *s_slot = s;
+    }
+    wait_lds();
+    stage_barrier();
+    return __builtin_amdgcn_readfirstlane(*s_slot);
+  }
+};
 
 // Wait for this wave's outstanding global (and LDS) operations.
 __device__ __forceinline__ void wait_all_loads() { __builtin_amdgcn_s_waitcnt(0); }

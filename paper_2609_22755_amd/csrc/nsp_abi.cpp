@@ -148,6 +148,9 @@ nsp_status validate_relayout(const nsp_worklist *wl, nsp_kind kind, nsp_dtype dt
 struct HostAttnSched {
   std::vector<ItemDesc> items;
   std::vector<int4> fwd_units, kv_units;
+  std::vector<int4> q_units;    // fwd_units in gangs, on per-XCD queues: what the passes run
+  std::vector<int> q_off;       // kXcdQueues + 1 entries, as kv_qoff
+  bool one_shot = false;        // forward / dQ: one workgroup a unit
   std::vector<int> kv_qoff;     // kXcdQueues + 1 entries: the dK/dV queue of XCD x is kv_units[kv_qoff[x] ..)
   std::vector<nsp::PreBlock> pre_blocks;
   std::vector<nsp::KvPiece> kv_pieces;   // split dK/dV (empty: not split)
@@ -168,9 +171,10 @@ void lpt_sort(std::vector<int4> &units, std::vector<int64_t> &cost) {
   units.swap(out);
 }
 
-// Workgroups are dispatched round-robin over the 8 XCDs of an MI355X
-// (workgroup b starts on XCD b % 8, each XCD with its own L2).  Units that
-// are adjacent in LPT order stream the same K/V (forward, dQ) or Q/dO (dK/dV)
+// The order that nsp_attn_schedule reports for the forward / dQ units (the
+// passes run them in gangs, add_fwd_gangs).  Workgroups are dispatched
+// round-robin over the 8 XCDs of an MI355X (workgroup b starts on XCD b % 8,
+// each XCD with its own L2).  Units that are adjacent in LPT order stream the same K/V (forward, dQ) or Q/dO (dK/dV)
 // tiles at about the same time, so they should share an XCD: in chunk
 // c = b/(8G), launch slot b runs the (b/8)%G-th of the G consecutive units
 // given to XCD b%8.  XCDs take their G-runs in alternating order from chunk
@@ -300,6 +304,52 @@ void add_kv_gangs(std::vector<KvGang> &gangs, const nsp_worklist *wl, int j, int
       gang.dur = std::max(gang.dur, mids[p].w * tiles(mids[p].n));
     }
     gangs.push_back(std::move(gang));
+  }
+}
+
+// Forward / dQ gangs.  The units of the query heads of one KV head stream the
+// same K / V tiles, all from the item's first on.  A gang is a run of such
+// units of consecutive query tiles, longest first, that goes to one XCD, so that
+// the units the XCD runs at once read each tile at the same time and it comes
+// from memory once (a list in plain longest-first order, dealt out over the
+// XCDs, reads it up to 8 times).  Up to kFwdGang units and a quarter of the
+// item's query tiles: longer gangs leave long units to the end of a queue.
+// Measured forward, longest-first order / gangs of 32, 16 and 8 units without
+// the second limit: 32 items of 2048 tokens 1199 / 1117, 1124, 1210 us; 200 of
+// 300 552 / 525, 525, 545; one 16384-token node of 4 heads 405 / 407, 356, 338;
+// 4 items of 4096 with one query head a KV head 265 / 276, 275, 265 (with it
+// 260); the long-tail share 102.5 / 102.4, 102.5, 102.6 ms.
+constexpr int kFwdGang = 16;
+constexpr int64_t kUnitCost = 4;   // 64-key steps that starting and ending a unit costs
+
+// Passes of at most this many 64-key steps a compute unit run one workgroup a
+// unit, longer ones persistent workgroups: a persistent workgroup asks memory
+// for each unit and three more times at the end (5 to 15 us a pass), but evens
+// out XCDs that run a few percent apart.  Forward, persistent / one workgroup a
+// unit: 100 items of 300 tokens, D = 64 (28 steps) 64 / 48 us; one of 4096 (68
+// steps) 137 / 127; 6 of 2048 (108 steps) 214 / 217; 20 of 1500, one query head
+// a KV head (103 steps) 239 / 263; 32 of 2048 (576 steps) 1117 / 1244.
+constexpr int64_t kOneShotSteps = 80;
+
+void add_fwd_gangs(std::vector<KvGang> &gangs, const nsp_worklist *wl, int j, int L) {
+  const int ql = wl->q_heads[2 * j], hq = wl->q_heads[2 * j + 1] - ql;
+  const int kl = wl->kv_heads[2 * j], hkv = wl->kv_heads[2 * j + 1] - kl;
+  for (int g = 0; g < hkv; ++g) {
+    std::vector<int> heads;
+    for (int i = 0; i < hq; ++i)
+      if ((int)(((int64_t)(ql + i) * wl->hkv_total) / wl->hq_total) - kl == g) heads.push_back(i);
+    const int nq = (L + nsp::kFwdBM - 1) / nsp::kFwdBM;
+    const int most = std::min(kFwdGang, std::max(2, nq / 4) * (int)heads.size());
+    for (int m = nq - 1, n = 0; m >= 0; --m)
+      for (int i : heads) {
+        if (n++ % most == 0) gangs.emplace_back();
+        KvGang &gang = gangs.back();
+        const int64_t steps = (std::min<int64_t>(L, (int64_t)nsp::kFwdBM * (m + 1)) + nsp::kFwdBN - 1) / nsp::kFwdBN;
+        gang.units.push_back(int4{j, m, i, g});
+        gang.steps.push_back(steps);
+        gang.cost += steps + kUnitCost;
+        gang.dur = std::max(gang.dur, steps);
+      }
   }
 }
 
@@ -630,7 +680,7 @@ HostAttnSched build_attn_schedule(const nsp_worklist *wl) {
       small_blocks += (int64_t)(wl->q_heads[2 * j + 1] - wl->q_heads[2 * j]) *
                       ((wl->cu_seqlens[j + 1] - wl->cu_seqlens[j] + nsp::kPreSmallRows - 1) / nsp::kPreSmallRows);
   const int pre_rows = small_blocks > nsp::kPreFewBlocks ? nsp::kPreBlockRows : nsp::kPreSmallRows;
-  ItemGangs item_gangs;
+  ItemGangs item_gangs, fwd_gangs;
   for (int j = 0; j < wl->n_items; ++j) {
     const int L = wl->cu_seqlens[j + 1] - wl->cu_seqlens[j];
     const int ql = wl->q_heads[2 * j], hq = wl->q_heads[2 * j + 1] - ql;
@@ -656,6 +706,8 @@ HostAttnSched build_attn_schedule(const nsp_worklist *wl) {
           s.fwd_units.push_back(int4{j, m, i, g});
           fcost.push_back(std::min<int64_t>(L, (int64_t)nsp::kFwdBM * (m + 1)));
         }
+      fwd_gangs.emplace_back(j, std::vector<KvGang>());
+      add_fwd_gangs(fwd_gangs.back().second, wl, j, L);
       item_gangs.emplace_back(j, std::vector<KvGang>());
       add_kv_gangs(item_gangs.back().second, wl, j, L, 0);
     }
@@ -665,6 +717,12 @@ HostAttnSched build_attn_schedule(const nsp_worklist *wl) {
   }
   s.q_rows = qo / D;
   lpt_sort(s.fwd_units, fcost);
+  int64_t steps = 0;
+  for (const KvGang *g : kv_queue_order(fwd_gangs, s.q_off)) {
+    s.q_units.insert(s.q_units.end(), g->units.begin(), g->units.end());
+    for (int64_t n : g->steps) steps += n;
+  }
+  s.one_shot = steps <= kOneShotSteps * kAssumedCUs;
   add_split(s, wl);
   kv_balance(item_gangs, wl);
   for (const KvGang *g : kv_queue_order(item_gangs, s.kv_qoff))
@@ -803,13 +861,13 @@ nsp_status upload(const void *host, size_t bytes, void **dev) {
 // aligned.
 struct AttnBlob {
   std::vector<char> bytes;
-  size_t o_fwd = 0, o_kv = 0, o_kvq = 0, o_pre = 0, o_piece = 0, o_wg = 0, o_red = 0;
+  size_t o_fwd = 0, o_kv = 0, o_kvq = 0, o_pre = 0, o_piece = 0, o_wg = 0, o_red = 0, o_fwdq = 0;
 };
 
 AttnBlob attn_blob(const HostAttnSched &hs) {
   AttnBlob b;
   const size_t n_items = align256(hs.items.size() * sizeof(ItemDesc));
-  const size_t n_fwd = align256(hs.fwd_units.size() * sizeof(int4));
+  const size_t n_fwd = align256(hs.q_units.size() * sizeof(int4));
   const size_t n_kv = align256(hs.kv_units.size() * sizeof(int4));
   const size_t n_kvq = align256(hs.kv_qoff.size() * sizeof(int));
   const size_t n_pre = align256(hs.pre_blocks.size() * sizeof(nsp::PreBlock));
@@ -820,12 +878,14 @@ AttnBlob attn_blob(const HostAttnSched &hs) {
   b.o_piece = b.o_pre + n_pre;
   b.o_wg = b.o_piece + align256(hs.kv_pieces.size() * sizeof(nsp::KvPiece));
   b.o_red = b.o_wg + align256(hs.kv_wgs.size() * sizeof(int2));
-  b.bytes.assign(b.o_red + align256(hs.kv_reduce.size() * sizeof(nsp::KvReduce)), 0);
+  b.o_fwdq = b.o_red + align256(hs.kv_reduce.size() * sizeof(nsp::KvReduce));
+  b.bytes.assign(b.o_fwdq + align256(hs.q_off.size() * sizeof(int)), 0);
   auto put = [&](size_t off, const void *src, size_t n) {
     if (n) memcpy(b.bytes.data() + off, src, n);
   };
   put(0, hs.items.data(), hs.items.size() * sizeof(ItemDesc));
-  put(b.o_fwd, hs.fwd_units.data(), hs.fwd_units.size() * sizeof(int4));
+  put(b.o_fwd, hs.q_units.data(), hs.q_units.size() * sizeof(int4));
+  put(b.o_fwdq, hs.q_off.data(), hs.q_off.size() * sizeof(int));
   put(b.o_kv, hs.kv_units.data(), hs.kv_units.size() * sizeof(int4));
   put(b.o_kvq, hs.kv_qoff.data(), hs.kv_qoff.size() * sizeof(int));
   put(b.o_pre, hs.pre_blocks.data(), hs.pre_blocks.size() * sizeof(nsp::PreBlock));
@@ -849,7 +909,16 @@ nsp::Schedule attn_schedule_at(const HostAttnSched &hs, const AttnBlob &b, char 
   s.n_kv_wgs = (int)hs.kv_wgs.size();
   s.n_kv_reduce = (int)hs.kv_reduce.size();
   s.n_items = (int)hs.items.size();
-  s.n_fwd_units = (int)hs.fwd_units.size();
+  s.n_fwd_units = (int)hs.q_units.size();
+  s.fwd_qoff = reinterpret_cast<int *>(dev + b.o_fwdq);
+  auto longest = [](const std::vector<int> &off) {
+    int n = 0;
+    for (size_t x = 0; x + 1 < off.size(); ++x) n = std::max(n, off[x + 1] - off[x]);
+    return n;
+  };
+  s.fwd_longest = longest(hs.q_off);
+  s.fwd_one_shot = hs.one_shot;
+  s.kv_longest = longest(hs.kv_qoff);
   s.n_kv_units = (int)hs.kv_units.size();
   s.n_pre_blocks = (int)hs.pre_blocks.size();
   s.q_rows = hs.q_rows;
@@ -1079,6 +1148,7 @@ nsp_status launch_backward(int D, const nsp::Schedule &s, float softmax_scale, c
                      "backward preprocess launch"));
   a.units = s.kv_units;
   a.qoff = s.kv_qoff;
+  a.q_longest = s.kv_longest;
   const bool split = s.n_kv_wgs > 0;
   if (split) {
     a.pieces = s.kv_pieces;
@@ -1092,6 +1162,9 @@ nsp_status launch_backward(int D, const nsp::Schedule &s, float softmax_scale, c
                                                                     stream); }),
                      "backward dK/dV launch"));
   a.units = s.fwd_units;
+  a.qoff = s.fwd_qoff;
+  a.q_longest = s.fwd_longest;
+  a.one_shot = s.fwd_one_shot;
   return hip_status(timed_launch(K_DQ, stream, [&] { return nsp::launch_bwd_dq(D, g32, a, s.n_fwd_units, stream); }),
                     "backward dQ launch");
 }
@@ -1126,6 +1199,9 @@ nsp_status nsp_varlen_attn_fwd(const nsp_worklist *wl, float softmax_scale, int3
   a.lse = lse;
   a.items = s.items;
   a.units = s.fwd_units;
+  a.qoff = s.fwd_qoff;
+  a.q_longest = s.fwd_longest;
+  a.one_shot = s.fwd_one_shot;
   a.n_items = s.n_items;
   a.scale = softmax_scale;
   a.scale_log2 = softmax_scale * 1.4426950408889634f;

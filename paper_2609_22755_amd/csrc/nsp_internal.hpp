@@ -84,7 +84,10 @@ constexpr size_t kv_part_bytes(int D) { return kKvSlots * (size_t)kv_slot_floats
 //                  b = local KV head
 struct Schedule {
   ItemDesc *items = nullptr;   // device
-  int4 *fwd_units = nullptr;   // device, LPT order (forward and dQ)
+  int4 *fwd_units = nullptr;   // device, forward and dQ units, per-XCD queues one after another
+  int *fwd_qoff = nullptr;     // device, 9 ints: queue x is fwd_units[fwd_qoff[x] .. fwd_qoff[x+1])
+  int fwd_longest = 0, kv_longest = 0;   // entries of the longest forward / dQ and dK/dV queues
+  bool fwd_one_shot = false;   // forward / dQ: one workgroup a unit, also with more units than compute units
   int4 *kv_units = nullptr;    // device, dK/dV units, per-XCD queues one after another
   int *kv_qoff = nullptr;      // device, 9 ints: queue x is kv_units[kv_qoff[x] .. kv_qoff[x+1])
   KvPiece *kv_pieces = nullptr;   // device, split dK/dV: the pieces, workgroup by workgroup
@@ -119,7 +122,9 @@ struct AttnArgs {
   const KvReduce *reduce;
   int n_reduce;
   float *part;            // split dK/dV: partial sums, kv_slot_floats a slot
-  const int *qoff;        // dK/dV: start of each XCD's queue in `units`, and the end
+  const int *qoff;        // start of each XCD's queue in `units`, and the end
+  int q_longest;          // entries of the longest of them
+  bool one_shot;          // one workgroup a unit, also with more units than compute units
   int n_items;
   float scale;            // softmax scale
   float scale_log2;       // softmax scale * log2(e)

@@ -4,7 +4,9 @@
 // for each, consecutive and its own, and one entry in the sum pass; no more
 // shares than compute units and none much longer than the mean; a masked call
 // runs exactly the unmasked call's pieces of its items; the workspace that the
-// query asks for and the allocation-free scratch hold the slots.  Built with
+// query asks for and the allocation-free scratch hold the slots.  And the gangs of
+// the forward / dQ units: a permutation of the unit list on queues of about
+// equal work.  Built with
 // g++ from the library's host sources; prints "split checks ok".
 #include "nsp_abi.cpp"
 
@@ -119,6 +121,29 @@ void check_list(const nsp_worklist &w, const std::vector<uint8_t> &mask, int *n_
   }
 }
 
+void check_gangs(const nsp_worklist &w) {
+  const HostAttnSched s = build_attn_schedule(&w);
+  auto key = [](const int4 &u) { return std::make_tuple(u.x, u.y, u.z, u.w); };
+  std::multiset<std::tuple<int, int, int, int>> a, b;
+  for (const int4 &u : s.fwd_units) a.insert(key(u));
+  for (const int4 &u : s.q_units) b.insert(key(u));
+  CHECK(a == b && s.q_off.size() == 9 && s.q_off[0] == 0 && s.q_off[8] == (int)s.q_units.size());
+  int64_t most = 0, total = 0, gang = 0;
+  for (int x = 0; x < 8; ++x) {
+    CHECK(s.q_off[x] <= s.q_off[x + 1]);
+    int64_t work = 0;
+    for (int k = s.q_off[x]; k < s.q_off[x + 1]; ++k) {
+      const int L = w.cu_seqlens[s.q_units[k].x + 1] - w.cu_seqlens[s.q_units[k].x];
+      const int64_t c = (std::min(L, 256 * (s.q_units[k].y + 1)) + 63) / 64 + kUnitCost;
+      work += c;
+      gang = std::max(gang, c * kFwdGang);
+    }
+    most = std::max(most, work);
+    total += work;
+  }
+  CHECK(most <= total / 8 + gang);
+}
+
 }  // namespace
 
 int main() {
@@ -148,6 +173,9 @@ int main() {
     w.hkv_total = h[1];
     w.head_dim = uni(0, 1) ? 128 : 64;
     check_list(w, mask, &n_split);
+    check_gangs(w);
+    w.item_mask = mask.data();
+    check_gangs(w);
   }
   CHECK(n_split > 100 && n_split < 400);
   std::printf("split checks ok (%d of 400 lists split)\n", n_split);
