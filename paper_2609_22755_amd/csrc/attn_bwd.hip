@@ -104,18 +104,20 @@ __global__ void __launch_bounds__(256) bwd_preprocess_kernel(AttnArgs a) {
 
 // -------------------------------------------------------------------- dQ --
 
-template <int D>
+// Waves as in the forward: RB blocks of 32 query rows, KG key groups.
+template <int D, int RB, int KG>
 struct DqCfg {
-  static constexpr int BM = kFwdBM;
-  static constexpr int BN = kFwdBN;
-  static constexpr int NW = kFwdWaves;
+  static constexpr int BM = 32 * RB;
+  static constexpr int NW = RB * KG;
+  static constexpr int BN = RB == 8 ? kFwdBN : 32;
   static constexpr int TILE = BN * D;
   static constexpr int KS = D / 16;
   static constexpr int MB = D / 32;
-  // the tiles are loaded by the first NL waves (one per SIMD), as in the
-  // forward
+  // the tiles of a group are loaded by its first NL waves, as in the forward
   static constexpr int NL = 4;
   static constexpr int LPW = 2 * TileLoader<D, BN, NL>::PER_WAVE;   // loads per loading wave and tile
+  static constexpr int PER_CU = NW == 4 ? 2 : 1;                    // workgroups a compute unit holds
+  static_assert((RB == 8 && KG == 1) || RB == 4, "256-row units, or 128-row ones of one or two key groups");
 };
 
 template <int D>
@@ -137,12 +139,12 @@ struct DqAddr {
   unsigned kr[D / 16];      // K row operand of a 32-key half, k block k (K ring)
   unsigned vr[D / 16];      // the same in the V ring
   unsigned kt[D / 32][2];   // K^T transpose reads, head_dim block mb, rows 0..7 / 8..15
-  __device__ __forceinline__ DqAddr(int lane, unsigned v_ring) {
+  __device__ __forceinline__ DqAddr(int lane, unsigned k_ring, unsigned v_ring) {
     const int l32 = lane & 31, h = lane >> 5, g = lane >> 4, j = lane & 15;
 #pragma unroll
     for (int k = 0; k < D / 16; ++k) {
-      kr[k] = 2u * (unsigned)tile_off<D>(l32, 16 * k + 8 * h);
-      vr[k] = v_ring + kr[k];
+      kr[k] = k_ring + 2u * (unsigned)tile_off<D>(l32, 16 * k + 8 * h);
+      vr[k] = v_ring - k_ring + kr[k];
       asm volatile("" : "+v"(kr[k]));
       asm volatile("" : "+v"(vr[k]));
     }
@@ -150,7 +152,7 @@ struct DqAddr {
     for (int mb = 0; mb < D / 32; ++mb)
 #pragma unroll
       for (int hi = 0; hi < 2; ++hi) {
-        kt[mb][hi] = 2u * (unsigned)tile_off<D>(4 * h + (j >> 2) + 8 * hi, 32 * mb + 16 * (g & 1) + 4 * (j & 3));
+        kt[mb][hi] = k_ring + 2u * (unsigned)tile_off<D>(4 * h + (j >> 2) + 8 * hi, 32 * mb + 16 * (g & 1) + 4 * (j & 3));
         asm volatile("" : "+v"(kt[mb][hi]));
       }
   }
@@ -163,8 +165,7 @@ struct DqAddr {
 // md = g%MB, g = f%NH - 2*KS.
 template <int D>
 __device__ __forceinline__ bf16x8 dq_operand(int f, const bf16 *smem, const DqAddr<D> &ad, unsigned so) {
-  using C = DqCfg<D>;
-  constexpr int NS = 2 * C::KS, NH = NS + 2 * C::MB;
+  constexpr int MB = D / 32, NS = 2 * (D / 16), NH = NS + 2 * MB;
   const int kb = f / NH, g = f % NH;
   const char *base = (const char *)smem;
   if (g < NS) {
@@ -172,26 +173,25 @@ __device__ __forceinline__ bf16x8 dq_operand(int f, const bf16 *smem, const DqAd
     return *(const bf16x8 *)(base + ((g & 1) ? ad.vr[g >> 1] : ad.kr[g >> 1]) + o);
   }
   const int gq = g - NS;
-  const unsigned o = so + 2u * D * (unsigned)(32 * kb + 16 * (gq / C::MB));
-  return cat4(lds_read_tr4((const bf16 *)(base + ad.kt[gq % C::MB][0] + o)),
-              lds_read_tr4((const bf16 *)(base + ad.kt[gq % C::MB][1] + o)));
+  const unsigned o = so + 2u * D * (unsigned)(32 * kb + 16 * (gq / MB));
+  return cat4(lds_read_tr4((const bf16 *)(base + ad.kt[gq % MB][0] + o)),
+              lds_read_tr4((const bf16 *)(base + ad.kt[gq % MB][1] + o)));
 }
 
-// One 64-key tile, in two 32-key halves:
+// One tile of BN keys, in 32-key halves:
 // S^T = K Q^T, dP^T = V dO^T, dS^T = P^T (dP^T - Delta), dQ^T += K^T dS^T
 // (K^T read from the row-major K tile with transpose reads).  The products
 // run in a fixed order, one per scheduling chunk, each chunk issuing the LDS
 // operand PF products ahead; the softmax of a half sits between its S/dP and
 // dQ products (the other wave on the SIMD keeps the matrix core busy then).
-template <int D>
+template <int D, int BN>
 __device__ __forceinline__ void dq_tile(DqState<D> &st, const bf16 *smem, const DqAddr<D> &ad, unsigned so, int n0,
                                         int wq0, int qrow, int lane, float c) {
-  using C = DqCfg<D>;
-  constexpr int KS = C::KS, MB = C::MB;
-  constexpr int NS = 2 * KS, NH = NS + 2 * MB, NP = 2 * NH;
+  constexpr int KS = D / 16, MB = D / 32;
+  constexpr int NS = 2 * KS, NH = NS + 2 * MB, NP = BN / 32 * NH;
   constexpr int PF = 3;
   const int h = lane >> 5;
-  const bool diag = n0 + kFwdBN - 1 > wq0;   // tile straddles this wave's diagonal
+  const bool diag = n0 + BN - 1 > wq0;   // tile straddles this wave's diagonal
   bf16x8 op[NP];
   f32x16 s, p;
   bf16x8 db[2];
@@ -226,59 +226,73 @@ __device__ __forceinline__ void dq_tile(DqState<D> &st, const bf16 *smem, const 
   }
 }
 
-// One dQ unit (launch slot `slot` of the unit list).  smem: K and V tiles,
-// a four-stage ring: K of stage s at smem + s*TILE, V at smem + (4+s)*TILE,
-// filled by untracked loads (as in the forward).
-template <int D, bool G_F32>
+// One dQ unit: entry `slot` of the unit list, rows BM*tile .. of its item.
+// smem: K and V tiles, for each key group a four-stage ring: K of stage s at
+// the group's base + s*TILE, V at base + (4+s)*TILE, filled by untracked loads
+// (as in the forward).
+template <int D, bool G_F32, int RB, int KG>
 __device__ __forceinline__ void dq_unit(const AttnArgs &a, int slot, bf16 *smem) {
-  using C = DqCfg<D>;
+  using C = DqCfg<D, RB, KG>;
   const int4 u = a.units[slot];
   const ItemDesc it = a.items[u.x];
   const int L = it.L;
   const int m0 = u.y * C::BM;
   const int wave = wave_id(), lane = threadIdx.x & 63;
-  const int l32 = lane & 31, h = lane >> 5;
+  const int rb = wave % RB, g = KG == 1 ? 0 : wave / RB;
+  const int l32 = lane & 31;
   const int64_t qs = (int64_t)it.hq * D;
   const int64_t ks = (int64_t)it.hkv * D;
   const int64_t qhead = it.q_off + (int64_t)u.z * D;
-  const bool loader = wave < C::NL;
-  const TileLoader<D, C::BN, C::NL> ldK((const bf16 *)a.k + it.kv_off + (int64_t)u.w * D, ks, wave % C::NL, lane);
-  const TileLoader<D, C::BN, C::NL> ldV((const bf16 *)a.v + it.kv_off + (int64_t)u.w * D, ks, wave % C::NL, lane);
+  const bool loader = rb < C::NL;
+  const TileLoader<D, C::BN, C::NL> ldK((const bf16 *)a.k + it.kv_off + (int64_t)u.w * D, ks, rb % C::NL, lane);
+  const TileLoader<D, C::BN, C::NL> ldV((const bf16 *)a.v + it.kv_off + (int64_t)u.w * D, ks, rb % C::NL, lane);
 
-  const int wq0 = m0 + wave * 32;
+  const int wq0 = m0 + rb * 32;
   const int qrow = wq0 + l32;
   const int n_end = min(L, m0 + C::BM);
-  const int n_tiles = (n_end + C::BN - 1) / C::BN;
-  const int wave_tiles = wq0 < L ? min(n_tiles, (wq0 + 31) / C::BN + 1) : 0;
+  const int n_tiles = (n_end + KG * C::BN - 1) / (KG * C::BN);
+  // tiles (of the whole key range) with keys at or before this wave's rows
+  const int wave_tiles = wq0 < L ? (min(wq0 + 32, L) + C::BN - 1) / C::BN : 0;
 
+  bf16 *const ring = smem + g * 8 * C::TILE;
+  auto load_kv = [&](int stage, int t) {
+    ldK.load_untracked(ring + stage * C::TILE, (KG * t + g) * C::BN, L);
+    ldV.load_untracked(ring + (4 + stage) * C::TILE, (KG * t + g) * C::BN, L);
+  };
+  // tiles 0 and 1 in flight (past the item end a tile load fetches nothing),
+  // and the rows of Q, then of dO, through the other two stages of K and V
+  if (loader) {
+    load_kv(0, 0);
+    load_kv(1, 1);
+  }
+  constexpr int WPS = C::BN / 32;            // waves a stage
+  bf16 *const reg = ring + (rb < 2 * WPS ? 2 * C::TILE : 6 * C::TILE - 2 * WPS * 32 * D) + rb * 32 * D;
+  start_rows<D>((const bf16 *)a.q + qhead, qs, wq0, L, reg, lane);
   DqState<D> st;
   {
-    const int64_t r = qhead + (int64_t)min(qrow, L - 1) * qs + 8 * h;
-#pragma unroll
-    for (int k = 0; k < C::KS; ++k) {
-      st.qf[k] = *(const bf16x8 *)((const bf16 *)a.q + r + 16 * k);
-      st.gf[k] = *(const bf16x8 *)((const bf16 *)a.dout + r + 16 * k);
-    }
     const int64_t srow = it.lse_off + (int64_t)u.z * L + min(qrow, L - 1);
     st.lse2 = a.lse2[srow];
     const float nd = a.delta[srow];          // -Delta
 #pragma unroll
     for (int e = 0; e < 16; ++e) st.ndlt[e] = nd;
   }
-  // The query-side registers land before the tile loads are issued: the
-  // compiler does not count those loads, so a wait of its own for these
-  // registers inside the loop would drain the ring.
   wait_all_loads();
-  // tiles 0..2 in flight (past the item end a tile load fetches nothing)
-  if (loader)
-    for (int j = 0; j < 3; ++j) {
-      ldK.load_untracked(smem + j * C::TILE, j * C::BN, L);
-      ldV.load_untracked(smem + (4 + j) * C::TILE, j * C::BN, L);
-    }
+  read_rows<D>(reg, lane, st.qf);
+  wait_lds();
+  start_rows<D>((const bf16 *)a.dout + qhead, qs, wq0, L, reg, lane);
+  // Everything lands before the next tile loads are issued: the compiler does
+  // not count those loads, so a wait of its own inside the loop would drain the
+  // ring.
+  wait_all_loads();
+  read_rows<D>(reg, lane, st.gf);
+  wait_lds();
+  stage_barrier();
+  if (loader) load_kv(2, 2);
 #pragma unroll
   for (int mb = 0; mb < C::MB; ++mb) st.acc[mb] = f32x16{};
   const float c = a.scale_log2;
-  const DqAddr<D> ad(lane, 2u * 4u * C::TILE);
+  const unsigned rbase = 2u * (unsigned)(g * 8 * C::TILE);
+  const DqAddr<D> ad(lane, rbase, rbase + 2u * 4u * C::TILE);
   constexpr unsigned TB = 2u * C::TILE;       // bytes per tile
 
   // step t: as in the forward -- wait for this wave's loads of tile t,
@@ -289,12 +303,9 @@ __device__ __forceinline__ void dq_unit(const AttnArgs &a, int slot, bf16 *smem)
     {                                                                               \
       wait_loads_le<2 * C::LPW>();                                                  \
       stage_barrier();                                                              \
-      if (loader) {                                                                 \
-        ldK.load_untracked(smem + (FILL) * C::TILE, (t + 3) * C::BN, L);            \
-        ldV.load_untracked(smem + (4 + (FILL)) * C::TILE, (t + 3) * C::BN, L);      \
-      }                                                                             \
-      if (t < wave_tiles)                                                           \
-        dq_tile<D>(st, smem, ad, (CUR) * TB, t * C::BN, wq0, qrow, lane, c);        \
+      if (loader) load_kv(FILL, t + 3);                                             \
+      if (KG * t + g < wave_tiles)                                                  \
+        dq_tile<D, C::BN>(st, smem, ad, (CUR) * TB, (KG * t + g) * C::BN, wq0, qrow, lane, c);  \
       if (++t >= n_tiles) break;                                                    \
     }
     NSP_DQ_STEP(0, 3)
@@ -303,36 +314,44 @@ __device__ __forceinline__ void dq_unit(const AttnArgs &a, int slot, bf16 *smem)
     NSP_DQ_STEP(3, 2)
 #undef NSP_DQ_STEP
   }
-  // no buffer->LDS load may still be in flight when the workgroup ends
+  // no buffer->LDS load may still be in flight, and no wave still reading the
+  // rings, when the rows to store pass through them
   wait_all_loads();
-
-  if (qrow < L) {
-    const int64_t obase = qhead + (int64_t)qrow * qs;
+  stage_barrier();
+  constexpr int MB0 = C::MB / KG;            // head_dim blocks that this wave stores
+  if constexpr (KG == 2) {
+    // the sums of the two groups, each wave the blocks that it stores
+    float *x = (float *)smem + wave * (64 * 16 * MB0) + lane;
+    const float *y = (const float *)smem + (wave ^ RB) * (64 * 16 * MB0) + lane;
 #pragma unroll
-    for (int mb = 0; mb < C::MB; ++mb)
+    for (int mb = 0; mb < MB0; ++mb)
 #pragma unroll
-      for (int gq = 0; gq < 4; ++gq) {
-        const int d0 = 32 * mb + 8 * gq + 4 * h;
-        f32x4 v4 = {st.acc[mb][4 * gq] * a.scale, st.acc[mb][4 * gq + 1] * a.scale,
-                    st.acc[mb][4 * gq + 2] * a.scale, st.acc[mb][4 * gq + 3] * a.scale};
-        if constexpr (G_F32) {
-          *(f32x4 *)((float *)a.dq + obase + d0) = v4;
-        } else {
-          bf16x4 b4 = {(bf16)v4[0], (bf16)v4[1], (bf16)v4[2], (bf16)v4[3]};
-          *(bf16x4 *)((bf16 *)a.dq + obase + d0) = b4;
-        }
-      }
+      for (int e = 0; e < 16; ++e) x[64 * (16 * mb + e)] = g == 0 ? st.acc[MB0 + mb][e] : st.acc[mb][e];
+    wait_lds();
+    stage_barrier();
+#pragma unroll
+    for (int mb = 0; mb < MB0; ++mb)
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        st.acc[mb][e] = (g == 0 ? st.acc[mb][e] : st.acc[MB0 + mb][e]) + y[64 * (16 * mb + e)];
+    wait_lds();
+    stage_barrier();
+  }
+  if (wq0 < L) {
+    const int esz = G_F32 ? 4 : 2;
+    char *out = (char *)a.dq + (qhead + (int64_t)wq0 * qs + 32 * MB0 * g) * esz;
+    store_rows<MB0, G_F32>(st.acc, a.scale, smem + wave * 32 * 32 * MB0 * (esz / 2), out, qs * esz, L - wq0, lane);
   }
 }
 
 // dQ pass over the per-XCD queues (a.qoff), as the dK/dV pass: with queue heads
-// one persistent workgroup per compute unit, without one workgroup per unit.
-template <int D, bool G_F32>
-__global__ void __launch_bounds__(64 * kFwdWaves, 1) bwd_dq_kernel(AttnArgs a, int *heads) {
-  __shared__ __attribute__((aligned(16))) bf16 smem[8 * DqCfg<D>::TILE];
+// persistent workgroups, without one workgroup per unit.
+template <int D, bool G_F32, int RB, int KG>
+__global__ void __launch_bounds__(64 * RB * KG, (RB * KG == 4 ? 2 : 1)) bwd_dq_kernel(AttnArgs a, int *heads) {
+  __shared__ __attribute__((aligned(16))) bf16 smem[KG * 8 * DqCfg<D, RB, KG>::TILE];
   __shared__ int s_slot;
   UnitQueue q(heads, a.qoff, &s_slot);
-  for (int slot = q.first(); slot >= 0; slot = q.next()) dq_unit<D, G_F32>(a, slot, smem);
+  for (int slot = q.first(); slot >= 0; slot = q.next()) dq_unit<D, G_F32, RB, KG>(a, slot, smem);
 }
 
 // ----------------------------------------------------------------- dK/dV --
@@ -1004,34 +1023,44 @@ hipError_t launch_bwd_preprocess(int head_dim, bool o_f32, const AttnArgs &a, in
   return hipGetLastError();
 }
 
-// Grid and queue heads of a pass over n_units units: with more units than
-// compute units, one persistent workgroup per compute unit (the kernels'
-// resources allow no more) and the heads, unless the list asks for one
-// workgroup per unit; otherwise one workgroup per unit and no heads.
-static hipError_t pass_grid(const AttnArgs &a, int n_units, int *heads_if_persistent, dim3 *grid, int **heads) {
+// Grid and queue heads of a pass over n_units units, `per_cu` workgroups a
+// compute unit: with more units than the chip holds workgroups, persistent
+// workgroups and the heads, unless the list asks for one workgroup per unit;
+// otherwise one workgroup per unit and no heads.
+static hipError_t pass_grid(const AttnArgs &a, int n_units, int per_cu, int *heads_if_persistent, dim3 *grid,
+                            int **heads) {
   int cus = 0;
   hipError_t e = compute_units(&cus);
   if (e != hipSuccess) return e;
-  const bool persistent = n_units > cus && !a.one_shot;
-  *grid = dim3(persistent ? cus : kXcdQueues * a.q_longest);
+  const bool persistent = n_units > per_cu * cus && !a.one_shot;
+  *grid = dim3(persistent ? per_cu * cus : kXcdQueues * a.q_longest);
   *heads = persistent ? heads_if_persistent : nullptr;
   return hipSuccess;
 }
 
+template <int D, bool G_F32, int RB, int KG>
+static hipError_t launch_dq(const AttnArgs &a, int n_units, hipStream_t s) {
+  dim3 grid;
+  int *heads = nullptr;
+  hipError_t e = pass_grid(a, n_units, DqCfg<D, RB, KG>::PER_CU, a.queue + kDqQueue0, &grid, &heads);
+  if (e != hipSuccess) return e;
+  bwd_dq_kernel<D, G_F32, RB, KG><<<grid, dim3(64 * RB * KG), 0, s>>>(a, heads);
+  return hipGetLastError();
+}
+
+template <int D, bool G_F32>
+static hipError_t launch_dq_kind(const AttnArgs &a, int n_units, hipStream_t s) {
+  switch (a.q_kind) {
+    case kQHalf: return launch_dq<D, G_F32, 4, 1>(a, n_units, s);
+    case kQKeys: return launch_dq<D, G_F32, 4, 2>(a, n_units, s);
+    default: return launch_dq<D, G_F32, kFwdWaves, 1>(a, n_units, s);
+  }
+}
+
 hipError_t launch_bwd_dq(int head_dim, bool g_f32, const AttnArgs &a, int n_units, hipStream_t s) {
   if (n_units == 0) return hipSuccess;
-  dim3 grid, block(64 * kFwdWaves);
-  int *heads = nullptr;
-  hipError_t e = pass_grid(a, n_units, a.queue + kDqQueue0, &grid, &heads);
-  if (e != hipSuccess) return e;
-  if (head_dim == 128) {
-    if (g_f32) bwd_dq_kernel<128, true><<<grid, block, 0, s>>>(a, heads);
-    else bwd_dq_kernel<128, false><<<grid, block, 0, s>>>(a, heads);
-  } else {
-    if (g_f32) bwd_dq_kernel<64, true><<<grid, block, 0, s>>>(a, heads);
-    else bwd_dq_kernel<64, false><<<grid, block, 0, s>>>(a, heads);
-  }
-  return hipGetLastError();
+  if (head_dim == 128) return g_f32 ? launch_dq_kind<128, true>(a, n_units, s) : launch_dq_kind<128, false>(a, n_units, s);
+  return g_f32 ? launch_dq_kind<64, true>(a, n_units, s) : launch_dq_kind<64, false>(a, n_units, s);
 }
 
 template <int D, bool G_F32>
@@ -1049,7 +1078,7 @@ hipError_t launch_bwd_dkdv(int head_dim, bool g_f32, const AttnArgs &a, int n_un
   }
   dim3 grid, block(256);
   int *heads = nullptr;
-  hipError_t e = pass_grid(a, n_units, a.queue + kKvQueue0, &grid, &heads);
+  hipError_t e = pass_grid(a, n_units, 1, a.queue + kKvQueue0, &grid, &heads);
   if (e != hipSuccess) return e;
   if (head_dim == 128) {
     if (g_f32) bwd_dkdv_kernel<128, true><<<grid, block, 0, s>>>(a, heads);

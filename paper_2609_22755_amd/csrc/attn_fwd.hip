@@ -35,21 +35,27 @@
 namespace nsp {
 namespace {
 
-template <int D>
+// A workgroup of RB x KG waves: RB blocks of 32 query rows, and KG groups of
+// waves that share the keys (KG > 1: group g takes the 32-key blocks g, g + KG,
+// ... through rings of its own, and the groups' results are combined at the
+// end).
+template <int D, int RB, int KG>
 struct FwdCfg {
-  static constexpr int BM = kFwdBM;
-  static constexpr int BN = kFwdBN;
-  static constexpr int NW = kFwdWaves;
+  static constexpr int BM = 32 * RB;
+  static constexpr int NW = RB * KG;
+  static constexpr int BN = RB == 8 ? kFwdBN : 32;
   static constexpr int TILE = BN * D;        // elements of one K or V tile (unpadded rows)
   static constexpr int KS = D / 16;          // MFMA k-steps over head_dim
   static constexpr int MB = D / 32;          // 32-wide head_dim blocks
-  // the tiles are loaded by the first NL waves (one per SIMD): while a
-  // loading wave waits for the memory pipeline to accept its loads, the other
-  // wave on its SIMD keeps the matrix core busy
+  // the tiles of a group are loaded by its first NL waves (with eight: one per
+  // SIMD; while a loading wave waits for the memory pipeline to accept its
+  // loads, the other wave on its SIMD keeps the matrix core busy)
   static constexpr int NL = 4;
   // buffer->LDS loads per loading wave and tile (K and V)
   static constexpr int LPW = 2 * TileLoader<D, BN, NL>::PER_WAVE;
-  static_assert(BM == 32 * NW, "one 32-row block per wave");
+  // workgroups a compute unit holds
+  static constexpr int PER_CU = NW == 4 ? 2 : 1;
+  static_assert((RB == 8 && KG == 1) || RB == 4, "256-row units, or 128-row ones of one or two key groups");
 };
 
 // Rows whose running maximum grows by more than 2^kRescaleLog2 rescale the
@@ -80,7 +86,7 @@ template <int D>
 struct FwdAddr {
   unsigned k[D / 16];       // K row operand, k block k (rows l%32, keys of a half)
   unsigned v[D / 32][2];    // V^T transpose reads, head_dim block mb, rows 0..7 / 8..15 of a 16-key block
-  __device__ __forceinline__ FwdAddr(int lane, unsigned k_ring) {
+  __device__ __forceinline__ FwdAddr(int lane, unsigned v_ring, unsigned k_ring) {
     const int l32 = lane & 31, h = lane >> 5, g = lane >> 4, j = lane & 15;
 #pragma unroll
     for (int kb = 0; kb < D / 16; ++kb) {
@@ -91,7 +97,7 @@ struct FwdAddr {
     for (int mb = 0; mb < D / 32; ++mb)
 #pragma unroll
       for (int hi = 0; hi < 2; ++hi) {
-        v[mb][hi] = 2u * (unsigned)tile_off<D>(4 * h + (j >> 2) + 8 * hi, 32 * mb + 16 * (g & 1) + 4 * (j & 3));
+        v[mb][hi] = v_ring + 2u * (unsigned)tile_off<D>(4 * h + (j >> 2) + 8 * hi, 32 * mb + 16 * (g & 1) + 4 * (j & 3));
         asm volatile("" : "+v"(v[mb][hi]));
       }
   }
@@ -232,12 +238,13 @@ __device__ __forceinline__ float fwd_block_max(const f32x16 &s, float c) {
   return wave_max_halves(mx) * c;
 }
 
-// Half-step u (keys 32u .. 32u+31) of a wave that processes `halves` halves;
-// waves already done skip it.  The last one, u = halves-1, is the wave's
-// diagonal block: it masks its scores and updates the reference maximum from
-// the masked ones first (the half-step before it computes these scores but
-// leaves the maximum alone, so that keys past a row never raise it).
-template <int D>
+// Half-step u (keys 32u .. 32u+31) of a wave with rows over `halves` halves,
+// of which it takes every KG-th; waves already done skip it.  The last one,
+// u = halves-1, is the rows' diagonal block: it masks its scores and updates
+// the reference maximum from the masked ones first (the half-step before it
+// computes these scores but leaves the maximum alone, so that keys past a row
+// never raise it).
+template <int D, int KG>
 __device__ __forceinline__ void fwd_half_step(FwdState<D> &st, f32x16 &sc, f32x16 &sn, const bf16 *smem,
                                               const FwdAddr<D> &ad, unsigned kn_off, unsigned v_off,
                                               unsigned kn_next, int u, int halves, int qrow, int h, float c) {
@@ -247,58 +254,75 @@ __device__ __forceinline__ void fwd_half_step(FwdState<D> &st, f32x16 &sc, f32x1
       fwd_update_max<D>(st, fwd_block_max(sc, c));
     }
     const float mx = fwd_half<D>(st, sc, sn, smem, ad, kn_off, v_off, kn_next, c);
-    if (u + 2 < halves) fwd_update_max<D>(st, mx);
+    if (u + KG + 1 < halves) fwd_update_max<D>(st, mx);
   }
 }
 
-// One forward unit (launch slot `slot` of the unit list).  smem: K and V
-// tiles, two four-stage rings: V tile t in stage t%4 at smem + (t%4)*TILE, K
-// tile t at smem + (4 + t%4)*TILE.  Each ring spans at most 64 KiB, so every
-// read is one of the per-lane addresses of FwdAddr plus an instruction
-// offset.  Step t reads K of tiles t and t+1 and V of tile t.  The rings are
+// One forward unit: entry `slot` of the unit list, rows BM*tile .. of its item.
+// smem: K and V tiles, for each key group two four-stage rings: V tile t in
+// stage t%4 at the group's base + (t%4)*TILE, K tile t at base +
+// (4 + t%4)*TILE.  Each ring spans at most 64 KiB, so every read is one of the
+// per-lane addresses of FwdAddr plus an instruction offset.  The rings are
 // filled by loads the compiler does not track; the waits and barriers of the
 // steps order them against the reads.
-template <int D, bool O_F32>
+template <int D, bool O_F32, int RB, int KG>
 __device__ __forceinline__ void fwd_unit(const AttnArgs &a, int slot, bf16 *smem) {
-  using C = FwdCfg<D>;
+  using C = FwdCfg<D, RB, KG>;
   const int4 u = a.units[slot];
   const ItemDesc it = a.items[u.x];
   const int L = it.L;
   const int m0 = u.y * C::BM;
   const int wave = wave_id(), lane = threadIdx.x & 63;
+  const int rb = wave % RB, g = KG == 1 ? 0 : wave / RB;
   const int l32 = lane & 31, h = lane >> 5;
   const int64_t qs = (int64_t)it.hq * D;
   const int64_t ks = (int64_t)it.hkv * D;
   const bf16 *Qh = (const bf16 *)a.q + it.q_off + (int64_t)u.z * D;
-  const bool loader = wave < C::NL;
-  const TileLoader<D, C::BN, C::NL> ldK((const bf16 *)a.k + it.kv_off + (int64_t)u.w * D, ks, wave % C::NL, lane);
-  const TileLoader<D, C::BN, C::NL> ldV((const bf16 *)a.v + it.kv_off + (int64_t)u.w * D, ks, wave % C::NL, lane);
+  const bool loader = rb < C::NL;
+  const TileLoader<D, C::BN, C::NL> ldK((const bf16 *)a.k + it.kv_off + (int64_t)u.w * D, ks, rb % C::NL, lane);
+  const TileLoader<D, C::BN, C::NL> ldV((const bf16 *)a.v + it.kv_off + (int64_t)u.w * D, ks, rb % C::NL, lane);
 
-  const int wq0 = m0 + wave * 32;          // first query row of this wave
+  const int wq0 = m0 + rb * 32;            // first query row of this wave
   const int qrow = wq0 + l32;              // this lane's query row
   const int n_end = min(L, m0 + C::BM);
-  const int n_tiles = (n_end + C::BN - 1) / C::BN;
-  // 32-key halves with keys <= this wave's rows: the last one is the wave's
+  // steps of the workgroup (of its first key group, which has no fewer)
+  const int n_tiles = (n_end + KG * C::BN - 1) / (KG * C::BN);
+  // 32-key halves with keys <= this wave's rows: the last one is the rows'
   // diagonal block (none for a wave wholly past the item end)
   const int halves = wq0 < L ? wq0 / 32 + 1 : 0;
 
-  FwdState<D> st;
-  {
-    const bf16 *qp = Qh + (int64_t)min(qrow, L - 1) * qs + 8 * h;
-#pragma unroll
-    for (int k = 0; k < C::KS; ++k) st.qf[k] = *(const bf16x8 *)(qp + 16 * k);
+  bf16 *const ring = smem + g * 8 * C::TILE;
+  auto load_k = [&](int stage, int t) {
+    ldK.load_untracked(ring + (4 + (stage & 3)) * C::TILE, (KG * t + g) * C::BN, L);
+  };
+  auto load_v = [&](int stage, int t) { ldV.load_untracked(ring + (stage & 3) * C::TILE, (KG * t + g) * C::BN, L); };
+  // K tiles 0..2 and V tile 0 in flight (past the item end a tile load fetches
+  // nothing), and the query rows, through the stages that are still free
+  // (V 1..3 and K 3)
+  if (loader) {
+    load_k(0, 0);
+    load_v(0, 0);
+    load_k(1, 1);
+    load_k(2, 2);
   }
-  // The query-side registers land before the tile loads are issued: the
-  // compiler does not count those loads, so a wait of its own for these
-  // registers inside the loop would drain the ring.
+  constexpr int WPS = C::BN / 32;            // waves a stage
+  bf16 *const qreg = ring + (rb < 3 * WPS ? C::TILE : 7 * C::TILE - 3 * WPS * 32 * D) + rb * 32 * D;
+  start_rows<D>(Qh, qs, wq0, L, qreg, lane);
+  // Everything lands before the next tile loads are issued: the compiler does
+  // not count those loads, so a wait of its own inside the loop would drain the
+  // ring.
   wait_all_loads();
-  // tiles 0..2 in flight (past the item end a tile load fetches nothing)
-  if (loader)
-    for (int j = 0; j < 3; ++j) {
-      ldK.load_untracked(smem + (4 + j) * C::TILE, j * C::BN, L);
-      ldV.load_untracked(smem + j * C::TILE, j * C::BN, L);
-    }
-  const FwdAddr<D> ad(lane, 2u * 4u * C::TILE);
+  FwdState<D> st;
+  read_rows<D>(qreg, lane, st.qf);
+  wait_lds();
+  stage_barrier();
+  if (loader) {
+    load_v(1, 1);
+    if constexpr (C::BN == 32) load_k(3, 3);
+    load_v(2, 2);
+  }
+  const unsigned rbase = 2u * (unsigned)(g * 8 * C::TILE);
+  const FwdAddr<D> ad(lane, rbase, rbase + 2u * 4u * C::TILE);
   constexpr unsigned TB = 2u * C::TILE;       // bytes per tile
   constexpr unsigned HB = 2u * 32u * D;       // bytes per 32 rows
 #pragma unroll
@@ -307,71 +331,116 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs &a, int slot, bf16 *smem
   st.l_part = 0.f;
   const float c = a.scale_log2;
 
-  // scores of keys 0..31 (every wave with rows in the item has keys there)
+  // scores of the group's first 32 keys (g = 0: every wave with rows in the
+  // item has keys there)
   f32x16 sa, sb;
-  wait_loads_le<2 * C::LPW>();
-  stage_barrier();
-  if (halves > 0) {
+  if (halves > g) {
     sa = f32x16{};
 #pragma unroll
     for (int k = 0; k < C::KS; ++k) sa = mfma32x32x16(lds_b128_at(smem, ad.k[k]), st.qf[k], sa);
-    // (keys 0..31 are the diagonal block of wave 0: its first half-step
-    // takes their maximum after masking)
-    if (halves > 1) fwd_update_max<D>(st, fwd_block_max(sa, c));
-    // the first operands of the first half-step (K tile 0, rows 32..63)
+    // (a wave whose first keys are its diagonal block takes their maximum
+    // after masking, in its first half-step)
+    if (halves > g + 1) fwd_update_max<D>(st, fwd_block_max(sa, c));
+    // the first operands of the first half-step (the next 32 keys)
 #pragma unroll
     for (int f = 0; f < kFwdPf; ++f) st.op0[f] = fwd_operand<D>(f, smem, ad, HB, 0);
   }
 
-  // step t: wait for this wave's loads of tile t+1 (those of tile t+2 may
-  // stay in flight), barrier (every wave's part has landed and every wave is
-  // done with step t-1), refill stage (t-1)%4 with tile t+3, then two
-  // half-steps: keys 64t.. (next scores from K tile t, rows 32..63) and keys
-  // 64t+32.. (next scores from K tile t+1, rows 0..31).
   int t = 0;
   for (;;) {
+    if constexpr (C::BN == 64) {
+      // step t: wait for this wave's loads of tile t+1 (those of tile t+2 may
+      // stay in flight), barrier (every wave's part has landed and every wave
+      // is done with step t-1), refill stage (t-1)%4 with tile t+3, then two
+      // half-steps: keys 64t.. (next scores from K tile t, rows 32..63) and
+      // keys 64t+32.. (next scores from K tile t+1, rows 0..31).
 #define NSP_FWD_STEP(CUR)                                                                   \
-    {                                                                                      \
-      wait_loads_le<C::LPW>();                                                             \
-      stage_barrier();                                                                     \
-      if (loader) {                                                                        \
-        ldK.load_untracked(smem + (4 + (((CUR) + 3) & 3)) * C::TILE, (t + 3) * C::BN, L);  \
-        ldV.load_untracked(smem + (((CUR) + 3) & 3) * C::TILE, (t + 3) * C::BN, L);        \
-      }                                                                                    \
-      fwd_half_step<D>(st, sa, sb, smem, ad, (CUR) * TB + HB, (CUR) * TB, (((CUR) + 1) & 3) * TB, 2 * t,   \
-                       halves, qrow, h, c);                                                \
-      fwd_half_step<D>(st, sb, sa, smem, ad, (((CUR) + 1) & 3) * TB, (CUR) * TB + HB,                    \
-                       (((CUR) + 1) & 3) * TB + HB, 2 * t + 1, halves, qrow, h, c);                 \
-      if (++t >= n_tiles) break;                                                           \
-    }
-    NSP_FWD_STEP(0)
-    NSP_FWD_STEP(1)
-    NSP_FWD_STEP(2)
-    NSP_FWD_STEP(3)
-#undef NSP_FWD_STEP
-  }
-  // no buffer->LDS load may still be in flight when the workgroup ends
-  wait_all_loads();
-
-  const float l_run = wave_sum_halves(st.l_part);
-  if (qrow < L) {
-    const float inv = 1.f / l_run;
-    const int64_t obase = it.q_off + (int64_t)qrow * qs + (int64_t)u.z * D;
-#pragma unroll
-    for (int mb = 0; mb < C::MB; ++mb)
-#pragma unroll
-      for (int gq = 0; gq < 4; ++gq) {
-        const int d0 = 32 * mb + 8 * gq + 4 * h;
-        f32x4 v4 = {st.acc[mb][4 * gq] * inv, st.acc[mb][4 * gq + 1] * inv, st.acc[mb][4 * gq + 2] * inv,
-                    st.acc[mb][4 * gq + 3] * inv};
-        if constexpr (O_F32) {
-          *(f32x4 *)((float *)a.o_out + obase + d0) = v4;
-        } else {
-          bf16x4 b4 = {(bf16)v4[0], (bf16)v4[1], (bf16)v4[2], (bf16)v4[3]};
-          *(bf16x4 *)((bf16 *)a.o_out + obase + d0) = b4;
-        }
+      {                                                                                    \
+        wait_loads_le<C::LPW>();                                                           \
+        stage_barrier();                                                                   \
+        if (loader) {                                                                      \
+          load_k((CUR) + 3, t + 3);                                                        \
+          load_v((CUR) + 3, t + 3);                                                        \
+        }                                                                                  \
+        fwd_half_step<D, KG>(st, sa, sb, smem, ad, (CUR) * TB + HB, (CUR) * TB, (((CUR) + 1) & 3) * TB, 2 * t,  \
+                             halves, qrow, h, c);                                          \
+        fwd_half_step<D, KG>(st, sb, sa, smem, ad, (((CUR) + 1) & 3) * TB, (CUR) * TB + HB,                \
+                             (((CUR) + 1) & 3) * TB + HB, 2 * t + 1, halves, qrow, h, c);             \
+        if (++t >= n_tiles) break;                                                         \
       }
-    if (h == 0) a.lse[it.lse_off + (int64_t)u.z * L + qrow] = (st.m_run + __log2f(l_run)) * kLn2;
+      NSP_FWD_STEP(0)
+      NSP_FWD_STEP(1)
+      NSP_FWD_STEP(2)
+      NSP_FWD_STEP(3)
+#undef NSP_FWD_STEP
+    } else {
+      // step t, 32 keys of each group: the half-step of the group's tile t
+      // reads V tile t, K tile t+1 (next scores) and, for the read-ahead, K
+      // tile t+2, so K runs two tiles ahead of V.  K tile t was last read in
+      // step t-1, its stage takes K tile t+4; V tile t+3 goes to the stage of
+      // V tile t-1.  Loads are issued K before V: those of V t+1, K t+3 and
+      // V t+2 may stay in flight at the barrier.
+#define NSP_FWD_STEP(CUR, SC, SN)                                                           \
+      {                                                                                    \
+        wait_loads_le<3 * C::LPW / 2>();                                                   \
+        stage_barrier();                                                                   \
+        load_k((CUR), t + 4);                                                              \
+        load_v((CUR) + 3, t + 3);                                                          \
+        fwd_half_step<D, KG>(st, SC, SN, smem, ad, (((CUR) + 1) & 3) * TB, (CUR) * TB, (((CUR) + 2) & 3) * TB,  \
+                             KG * t + g, halves, qrow, h, c);                              \
+        if (++t >= n_tiles) break;                                                         \
+      }
+      NSP_FWD_STEP(0, sa, sb)
+      NSP_FWD_STEP(1, sb, sa)
+      NSP_FWD_STEP(2, sa, sb)
+      NSP_FWD_STEP(3, sb, sa)
+#undef NSP_FWD_STEP
+    }
+  }
+  // no buffer->LDS load may still be in flight, and no wave still reading the
+  // rings, when the rows to store pass through them
+  wait_all_loads();
+  stage_barrier();
+
+  float l_run = wave_sum_halves(st.l_part);
+  constexpr int MB0 = C::MB / KG;          // head_dim blocks that this wave stores
+  if constexpr (KG == 2) {
+    // The two groups' sums of a row block: each wave hands the other the
+    // blocks that it does not store, with its maximum and row sum, and scales
+    // both to the common maximum.  A group without keys for the rows has
+    // maximum -inf and zeros.
+    constexpr int W = 64 * (16 * MB0 + 2);   // floats of one wave
+    float *x = (float *)smem + wave * W + lane;
+    const float *y = (const float *)smem + (wave ^ RB) * W + lane;
+#pragma unroll
+    for (int mb = 0; mb < MB0; ++mb)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) x[64 * (16 * mb + e)] = g == 0 ? st.acc[MB0 + mb][e] : st.acc[mb][e];
+    x[64 * 16 * MB0] = st.m_run;
+    x[64 * (16 * MB0 + 1)] = l_run;
+    wait_lds();
+    stage_barrier();
+    const float mo = y[64 * 16 * MB0], lo = y[64 * (16 * MB0 + 1)];
+    const float m = fmaxf(st.m_run, mo);
+    const float ao = fast_exp2(st.m_run - m), ay = fast_exp2(mo - m);
+    // (in the order of the groups, the same in both)
+    l_run = g == 0 ? __fadd_rn(l_run * ao, lo * ay) : __fadd_rn(lo * ay, l_run * ao);
+    st.m_run = m;
+#pragma unroll
+    for (int mb = 0; mb < MB0; ++mb)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const float own = g == 0 ? st.acc[mb][e] : st.acc[MB0 + mb][e];
+        st.acc[mb][e] = __fadd_rn(own * ao, y[64 * (16 * mb + e)] * ay);
+      }
+    wait_lds();
+    stage_barrier();
+  }
+  if (wq0 < L) {
+    const int esz = O_F32 ? 4 : 2;
+    char *out = (char *)a.o_out + (it.q_off + (int64_t)wq0 * qs + (int64_t)u.z * D + 32 * MB0 * g) * esz;
+    store_rows<MB0, O_F32>(st.acc, 1.f / l_run, smem + wave * 32 * 32 * MB0 * (esz / 2), out, qs * esz, L - wq0, lane);
+    if (h == 0 && g == 0 && qrow < L) a.lse[it.lse_off + (int64_t)u.z * L + qrow] = (st.m_run + __log2f(l_run)) * kLn2;
   }
 }
 
@@ -380,12 +449,12 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs &a, int slot, bf16 *smem
 // persistent workgroup per compute unit, and the last workgroup to finish sets
 // them back to zero for the next launch on the same stream.  Without
 // (a.queue == nullptr), one workgroup per unit.
-template <int D, bool O_F32>
-__global__ void __launch_bounds__(64 * kFwdWaves, 1) attn_fwd_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) bf16 smem[8 * FwdCfg<D>::TILE];
+template <int D, bool O_F32, int RB, int KG>
+__global__ void __launch_bounds__(64 * RB * KG, RB * KG == 4 ? 2 : 1) attn_fwd_kernel(AttnArgs a) {
+  __shared__ __attribute__((aligned(16))) bf16 smem[KG * 8 * FwdCfg<D, RB, KG>::TILE];
   __shared__ int s_slot;
   UnitQueue q(a.queue, a.qoff, &s_slot);
-  for (int slot = q.first(); slot >= 0; slot = q.next()) fwd_unit<D, O_F32>(a, slot, smem);
+  for (int slot = q.first(); slot >= 0; slot = q.next()) fwd_unit<D, O_F32, RB, KG>(a, slot, smem);
   // every fetch of this workgroup has returned before its count is added
   // (one wave makes both, the fetch's result decided to stop), so the last
   // workgroup counted knows that no fetch of this launch is still to come
@@ -460,30 +529,40 @@ hipError_t fwd_queue_block(hipStream_t s, int **out) {
 
 }  // namespace
 
-hipError_t launch_attn_fwd(int head_dim, bool o_f32, const AttnArgs &a_in, int n_units, hipStream_t s) {
-  if (n_units == 0) return hipSuccess;
+template <int D, bool O_F32, int RB, int KG>
+static hipError_t launch_fwd(const AttnArgs &a_in, int n_units, int cus, hipStream_t s) {
   AttnArgs a = a_in;
   a.queue = nullptr;
+  // with more units than the compute units hold workgroups, persistent
+  // workgroups on the stream's counter block, unless the list asks for one
+  // workgroup per unit; otherwise, or without a block, one workgroup per unit
+  const int resident = cus * FwdCfg<D, RB, KG>::PER_CU;
+  if (n_units > resident && !a.one_shot) {
+    hipError_t e = fwd_queue_block(s, &a.queue);
+    if (e != hipSuccess) return e;
+  }
+  attn_fwd_kernel<D, O_F32, RB, KG>
+      <<<dim3(a.queue ? resident : kXcdQueues * a.q_longest), dim3(64 * RB * KG), 0, s>>>(a);
+  return hipGetLastError();
+}
+
+template <int D, bool O_F32>
+static hipError_t launch_fwd_kind(const AttnArgs &a, int n_units, int cus, hipStream_t s) {
+  switch (a.q_kind) {
+    case kQHalf: return launch_fwd<D, O_F32, 4, 1>(a, n_units, cus, s);
+    case kQKeys: return launch_fwd<D, O_F32, 4, 2>(a, n_units, cus, s);
+    default: return launch_fwd<D, O_F32, kFwdWaves, 1>(a, n_units, cus, s);
+  }
+}
+
+hipError_t launch_attn_fwd(int head_dim, bool o_f32, const AttnArgs &a, int n_units, hipStream_t s) {
+  if (n_units == 0) return hipSuccess;
   int cus = 0;
   hipError_t e = compute_units(&cus);
   if (e != hipSuccess) return e;
-  // with more units than compute units, one persistent workgroup per compute
-  // unit (its resources allow no more) on the stream's counter block, unless
-  // the list asks for one workgroup per unit; otherwise, or without a block, one
-  // workgroup per unit
-  if (n_units > cus && !a.one_shot) {
-    e = fwd_queue_block(s, &a.queue);
-    if (e != hipSuccess) return e;
-  }
-  dim3 grid(a.queue ? cus : kXcdQueues * a.q_longest), block(64 * kFwdWaves);
-  if (head_dim == 128) {
-    if (o_f32) attn_fwd_kernel<128, true><<<grid, block, 0, s>>>(a);
-    else attn_fwd_kernel<128, false><<<grid, block, 0, s>>>(a);
-  } else {
-    if (o_f32) attn_fwd_kernel<64, true><<<grid, block, 0, s>>>(a);
-    else attn_fwd_kernel<64, false><<<grid, block, 0, s>>>(a);
-  }
-  return hipGetLastError();
+  if (head_dim == 128)
+    return o_f32 ? launch_fwd_kind<128, true>(a, n_units, cus, s) : launch_fwd_kind<128, false>(a, n_units, cus, s);
+  return o_f32 ? launch_fwd_kind<64, true>(a, n_units, cus, s) : launch_fwd_kind<64, false>(a, n_units, cus, s);
 }
 
 }  // namespace nsp

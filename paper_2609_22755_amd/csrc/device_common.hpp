@@ -215,6 +215,72 @@ struct TileLoader {
   }
 };
 
+// Row block of a wave: 32 rows of D bf16 between memory and the registers that
+// the matrix products want (one row a lane, D/16 operands of 8 elements).
+// Straight from memory such an access touches 32 rows an instruction, 16 bytes
+// of each, and the address unit takes a cycle or more for every row: the query
+// rows of a forward unit took 2.2 us and its stores 3.2 us of the 16 us that a
+// unit of 300 tokens takes.  So rows go through LDS (in memory order, 16 bytes a
+// lane, whole rows a few lanes wide), in a region of 32 * D elements that is the
+// wave's own.
+//
+// Start the loads of rows r0 .. r0+31 (zeros at and past L; src, r0 and L
+// uniform); after a wait for them, read_rows gives the operands.  (The lane is
+// hidden from the compiler in all three, which would otherwise keep their
+// per-lane addresses in registers from unit to unit.)
+__device__ __forceinline__ int hidden(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+template <int D>
+__device__ __forceinline__ void start_rows(const bf16 *src, int64_t stride, int r0, int L, bf16 *region, int lane) {
+  const TileLoader<D, 32, 1> ld(src, stride, 0, hidden(lane));
+  const uint64_t at = (uint64_t)(src + (int64_t)r0 * stride);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)at), hi = __builtin_amdgcn_readfirstlane((uint32_t)(at >> 32));
+  const int row_bytes = (int)stride * 2;
+  const int bytes = __builtin_amdgcn_readfirstlane(max(0, min(L - r0, 32) * row_bytes - (row_bytes - 2 * D)));
+  const __amdgpu_buffer_rsrc_t rs =
+      __builtin_amdgcn_make_buffer_rsrc((void *)((uint64_t)hi << 32 | lo), 0, bytes, 0x00020000);
+#pragma unroll
+  for (int k = 0; k < TileLoader<D, 32, 1>::PER_WAVE; ++k) load_lds_untracked<16>(rs, ld.voff[k], ld.dst(region, k));
+}
+template <int D>
+__device__ __forceinline__ void read_rows(const bf16 *region, int lane_, bf16x8 *op) {
+  const int lane = hidden(lane_);
+#pragma unroll
+  for (int k = 0; k < D / 16; ++k) op[k] = lds_row8<D>(region, lane & 31, 16 * k + 8 * (lane >> 5));
+}
+
+// Store the transposed accumulators acc[0 .. NB-1] (row = column of the output,
+// column = output row, C layout), times mul, as 32 rows of 32 * NB elements
+// from `out` on; only the first `rows` of them.  `region`: 32 * 32 * NB
+// elements of LDS of the wave's own, 16-byte chunks swizzled by row.
+template <int NB, bool F32>
+__device__ __forceinline__ void store_rows(const f32x16 *acc, float mul, void *region, char *out, int64_t row_bytes,
+                                           int rows, int lane_) {
+  const int lane = hidden(lane_);
+  constexpr int CH = NB * (F32 ? 8 : 4);       // 16-byte chunks a row
+  const int l32 = lane & 31, h = lane >> 5;
+  char *lds = (char *)region;
+#pragma unroll
+  for (int mb = 0; mb < NB; ++mb)
+#pragma unroll
+    for (int gq = 0; gq < 4; ++gq) {
+      const f32x4 v = {acc[mb][4 * gq] * mul, acc[mb][4 * gq + 1] * mul, acc[mb][4 * gq + 2] * mul,
+                       acc[mb][4 * gq + 3] * mul};
+      const int c = F32 ? 8 * mb + 2 * gq + h : 4 * mb + gq;
+      char *p = lds + 16 * (l32 * CH + (c ^ (l32 & (CH - 1))));
+      if constexpr (F32) *(f32x4 *)p = v;
+      else *(bf16x4 *)(p + 8 * h) = bf16x4{(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]};
+    }
+#pragma unroll
+  for (int j = 0; j < CH / 2; ++j) {
+    const int row = (64 * j + lane) / CH, c = (64 * j + lane) % CH;
+    const f32x4 v = *(const f32x4 *)(lds + 16 * (row * CH + (c ^ (row & (CH - 1)))));
+    if (row < rows) *(f32x4 *)(out + row * row_bytes + 16 * c) = v;
+  }
+}
+
 // s_waitcnt: at most n buffer->LDS loads of this wave still in flight, no LDS
 // operation in flight.  (gfx9 encoding: vmcnt[3:0] and [15:14], expcnt[6:4],
 // lgkmcnt[11:8].)

@@ -145,12 +145,18 @@ nsp_status validate_relayout(const nsp_worklist *wl, nsp_kind kind, nsp_dtype dt
 
 // ----------------------------------------------------- schedule building --
 
+// The units of a forward or dQ pass: gangs on per-XCD queues.
+struct QUnits {
+  int kind = nsp::kQWhole;      // QKind
+  std::vector<int4> units;
+  std::vector<int> off;         // kXcdQueues + 1 entries, as kv_qoff
+  bool one_shot = false;        // one workgroup a unit
+};
+
 struct HostAttnSched {
   std::vector<ItemDesc> items;
   std::vector<int4> fwd_units, kv_units;
-  std::vector<int4> q_units;    // fwd_units in gangs, on per-XCD queues: what the passes run
-  std::vector<int> q_off;       // kXcdQueues + 1 entries, as kv_qoff
-  bool one_shot = false;        // forward / dQ: one workgroup a unit
+  QUnits fwd, dq;               // what the forward and dQ passes run
   std::vector<int> kv_qoff;     // kXcdQueues + 1 entries: the dK/dV queue of XCD x is kv_units[kv_qoff[x] ..)
   std::vector<nsp::PreBlock> pre_blocks;
   std::vector<nsp::KvPiece> kv_pieces;   // split dK/dV (empty: not split)
@@ -331,20 +337,20 @@ constexpr int64_t kUnitCost = 4;   // 64-key steps that starting and ending a un
 // a KV head (103 steps) 239 / 263; 32 of 2048 (576 steps) 1117 / 1244.
 constexpr int64_t kOneShotSteps = 80;
 
-void add_fwd_gangs(std::vector<KvGang> &gangs, const nsp_worklist *wl, int j, int L) {
+void add_fwd_gangs(std::vector<KvGang> &gangs, const nsp_worklist *wl, int j, int L, int rows) {
   const int ql = wl->q_heads[2 * j], hq = wl->q_heads[2 * j + 1] - ql;
   const int kl = wl->kv_heads[2 * j], hkv = wl->kv_heads[2 * j + 1] - kl;
   for (int g = 0; g < hkv; ++g) {
     std::vector<int> heads;
     for (int i = 0; i < hq; ++i)
       if ((int)(((int64_t)(ql + i) * wl->hkv_total) / wl->hq_total) - kl == g) heads.push_back(i);
-    const int nq = (L + nsp::kFwdBM - 1) / nsp::kFwdBM;
-    const int most = std::min(kFwdGang, std::max(2, nq / 4) * (int)heads.size());
+    const int nq = (L + rows - 1) / rows, per = nsp::kFwdBM / rows;
+    const int most = std::min(kFwdGang * per, std::max(2 * per, nq / 4) * (int)heads.size());
     for (int m = nq - 1, n = 0; m >= 0; --m)
       for (int i : heads) {
         if (n++ % most == 0) gangs.emplace_back();
         KvGang &gang = gangs.back();
-        const int64_t steps = (std::min<int64_t>(L, (int64_t)nsp::kFwdBM * (m + 1)) + nsp::kFwdBN - 1) / nsp::kFwdBN;
+        const int64_t steps = (std::min<int64_t>(L, (int64_t)rows * (m + 1)) + nsp::kFwdBN - 1) / nsp::kFwdBN;
         gang.units.push_back(int4{j, m, i, g});
         gang.steps.push_back(steps);
         gang.cost += steps + kUnitCost;
@@ -669,7 +675,63 @@ void add_split(HostAttnSched &s, const nsp_worklist *wl) {
     if (selected(wl, r.item)) s.kv_reduce.push_back(r);
 }
 
-HostAttnSched build_attn_schedule(const nsp_worklist *wl) {
+// The kind of the forward / dQ units (QKind).
+//  * 128-row units, two workgroups a compute unit: while one waits for its first
+//    tiles or stores its rows (about 5 us a unit), the other one computes.  K/V
+//    are read twice as often.  For short units, at most kShortUnit 64-key steps on
+//    the mean: forward, 256-row / 128-row units, 100 items of 100 tokens (2
+//    steps) 90 / 54 us, 200 of 300 (4.5) 534 / 437, 100 of 600 (7.3) 552 / 522, 8
+//    of 1000 (10) 88.9 / 89.5, 50 of 1200 (11.8) 756 / 790; whole backward with
+//    dQ in such units 200 of 300 1411 / 1212, 50 of 1200 2417 / 2365, 32 of 2048
+//    (18) 3585 / 3556, one of 4096 (34) 435 / 449.
+//  * 128 rows and two key groups, one workgroup a compute unit: a list of at most
+//    one 256-row unit a compute unit lasts as long as its longest unit, which
+//    this cuts to about a quarter.  One 4096-token node of 4 heads 82 / 60 us,
+//    16384 tokens 348 / 270 (128-row units of one group: 67, 302).  The groups'
+//    sums are rounded in another order, so this is decided from every item of
+//    the list, whatever the call's mask; the other two kinds give the same bits.
+constexpr double kShortUnitFwd = 8, kShortUnitDq = 20;
+
+int q_unit_kind(const nsp_worklist *wl, double short_unit) {
+  int64_t units[2] = {0, 0}, steps[2] = {0, 0};   // of every item, of the call's
+  for (int j = 0; j < wl->n_items; ++j) {
+    const int64_t L = wl->cu_seqlens[j + 1] - wl->cu_seqlens[j], hq = wl->q_heads[2 * j + 1] - wl->q_heads[2 * j];
+    for (int64_t m = 0; m * nsp::kFwdBM < L; ++m) {
+      const int64_t n = (std::min<int64_t>(L, nsp::kFwdBM * (m + 1)) + nsp::kFwdBN - 1) / nsp::kFwdBN;
+      for (int c = 0; c < (selected(wl, j) ? 2 : 1); ++c) {
+        units[c] += hq;
+        steps[c] += hq * n;
+      }
+    }
+  }
+  if (units[0] <= kAssumedCUs && steps[0] > kShortUnitFwd * units[0]) return nsp::kQKeys;
+  return units[1] <= kAssumedCUs || steps[1] <= short_unit * units[1] ? nsp::kQHalf : nsp::kQWhole;
+}
+
+QUnits q_units(const nsp_worklist *wl, int kind) {
+  QUnits q;
+  q.kind = kind;
+  ItemGangs gangs;
+  for (int j = 0; j < wl->n_items; ++j) {
+    const int L = wl->cu_seqlens[j + 1] - wl->cu_seqlens[j];
+    if (L == 0 || !selected(wl, j)) continue;
+    gangs.emplace_back(j, std::vector<KvGang>());
+    add_fwd_gangs(gangs.back().second, wl, j, L, kind == nsp::kQWhole ? nsp::kFwdBM : nsp::kFwdBM / 2);
+  }
+  int64_t steps = 0;
+  for (const KvGang *g : kv_queue_order(gangs, q.off)) {
+    q.units.insert(q.units.end(), g->units.begin(), g->units.end());
+    for (int64_t n : g->steps) steps += n;
+  }
+  if (kind != nsp::kQWhole) steps /= 2;          // of 256-row units: two 128-row ones are one
+  q.one_shot = steps <= kOneShotSteps * kAssumedCUs;
+  return q;
+}
+
+// `compact`: 256-row units and large preprocess blocks whatever the list, for a
+// schedule that has to fit a limited space (the results are the same bits: lists
+// that split their dK/dV or take key groups are too small to need it).
+HostAttnSched build_attn_schedule(const nsp_worklist *wl, bool compact = false) {
   HostAttnSched s;
   const int D = wl->head_dim;
   int64_t qo = 0, ko = 0, lo = 0;
@@ -679,8 +741,8 @@ HostAttnSched build_attn_schedule(const nsp_worklist *wl) {
     if (selected(wl, j))
       small_blocks += (int64_t)(wl->q_heads[2 * j + 1] - wl->q_heads[2 * j]) *
                       ((wl->cu_seqlens[j + 1] - wl->cu_seqlens[j] + nsp::kPreSmallRows - 1) / nsp::kPreSmallRows);
-  const int pre_rows = small_blocks > nsp::kPreFewBlocks ? nsp::kPreBlockRows : nsp::kPreSmallRows;
-  ItemGangs item_gangs, fwd_gangs;
+  const int pre_rows = compact || small_blocks > nsp::kPreFewBlocks ? nsp::kPreBlockRows : nsp::kPreSmallRows;
+  ItemGangs item_gangs;
   for (int j = 0; j < wl->n_items; ++j) {
     const int L = wl->cu_seqlens[j + 1] - wl->cu_seqlens[j];
     const int ql = wl->q_heads[2 * j], hq = wl->q_heads[2 * j + 1] - ql;
@@ -706,8 +768,6 @@ HostAttnSched build_attn_schedule(const nsp_worklist *wl) {
           s.fwd_units.push_back(int4{j, m, i, g});
           fcost.push_back(std::min<int64_t>(L, (int64_t)nsp::kFwdBM * (m + 1)));
         }
-      fwd_gangs.emplace_back(j, std::vector<KvGang>());
-      add_fwd_gangs(fwd_gangs.back().second, wl, j, L);
       item_gangs.emplace_back(j, std::vector<KvGang>());
       add_kv_gangs(item_gangs.back().second, wl, j, L, 0);
     }
@@ -717,12 +777,9 @@ HostAttnSched build_attn_schedule(const nsp_worklist *wl) {
   }
   s.q_rows = qo / D;
   lpt_sort(s.fwd_units, fcost);
-  int64_t steps = 0;
-  for (const KvGang *g : kv_queue_order(fwd_gangs, s.q_off)) {
-    s.q_units.insert(s.q_units.end(), g->units.begin(), g->units.end());
-    for (int64_t n : g->steps) steps += n;
-  }
-  s.one_shot = steps <= kOneShotSteps * kAssumedCUs;
+  s.fwd = q_units(wl, compact ? nsp::kQWhole : q_unit_kind(wl, kShortUnitFwd));
+  const int dq_kind = compact ? nsp::kQWhole : q_unit_kind(wl, kShortUnitDq);
+  s.dq = dq_kind == s.fwd.kind ? s.fwd : q_units(wl, dq_kind);
   add_split(s, wl);
   kv_balance(item_gangs, wl);
   for (const KvGang *g : kv_queue_order(item_gangs, s.kv_qoff))
@@ -857,17 +914,17 @@ nsp_status upload(const void *host, size_t bytes, void **dev) {
 }
 
 // The device image of an attention schedule: ItemDesc[n_items] | forward/dQ
-// units | dK/dV units | preprocess spans | split dK/dV, each part 256-byte
-// aligned.
+// units | dK/dV units | preprocess spans | split dK/dV | queue offsets, each
+// part 256-byte aligned.
 struct AttnBlob {
   std::vector<char> bytes;
-  size_t o_fwd = 0, o_kv = 0, o_kvq = 0, o_pre = 0, o_piece = 0, o_wg = 0, o_red = 0, o_fwdq = 0;
+  size_t o_fwd = 0, o_kv = 0, o_kvq = 0, o_pre = 0, o_piece = 0, o_wg = 0, o_red = 0, o_fwdq = 0, o_dq = 0, o_dqq = 0;
 };
 
 AttnBlob attn_blob(const HostAttnSched &hs) {
   AttnBlob b;
   const size_t n_items = align256(hs.items.size() * sizeof(ItemDesc));
-  const size_t n_fwd = align256(hs.q_units.size() * sizeof(int4));
+  const size_t n_fwd = align256(hs.fwd.units.size() * sizeof(int4));
   const size_t n_kv = align256(hs.kv_units.size() * sizeof(int4));
   const size_t n_kvq = align256(hs.kv_qoff.size() * sizeof(int));
   const size_t n_pre = align256(hs.pre_blocks.size() * sizeof(nsp::PreBlock));
@@ -879,13 +936,25 @@ AttnBlob attn_blob(const HostAttnSched &hs) {
   b.o_wg = b.o_piece + align256(hs.kv_pieces.size() * sizeof(nsp::KvPiece));
   b.o_red = b.o_wg + align256(hs.kv_wgs.size() * sizeof(int2));
   b.o_fwdq = b.o_red + align256(hs.kv_reduce.size() * sizeof(nsp::KvReduce));
-  b.bytes.assign(b.o_fwdq + align256(hs.q_off.size() * sizeof(int)), 0);
+  size_t end = b.o_fwdq + align256(hs.fwd.off.size() * sizeof(int));
+  b.o_dq = b.o_fwd;                  // the same units, unless of another kind
+  b.o_dqq = b.o_fwdq;
+  if (hs.dq.kind != hs.fwd.kind) {
+    b.o_dq = end;
+    b.o_dqq = b.o_dq + align256(hs.dq.units.size() * sizeof(int4));
+    end = b.o_dqq + align256(hs.dq.off.size() * sizeof(int));
+  }
+  b.bytes.assign(end, 0);
   auto put = [&](size_t off, const void *src, size_t n) {
     if (n) memcpy(b.bytes.data() + off, src, n);
   };
   put(0, hs.items.data(), hs.items.size() * sizeof(ItemDesc));
-  put(b.o_fwd, hs.q_units.data(), hs.q_units.size() * sizeof(int4));
-  put(b.o_fwdq, hs.q_off.data(), hs.q_off.size() * sizeof(int));
+  put(b.o_fwd, hs.fwd.units.data(), hs.fwd.units.size() * sizeof(int4));
+  put(b.o_fwdq, hs.fwd.off.data(), hs.fwd.off.size() * sizeof(int));
+  if (b.o_dq != b.o_fwd) {
+    put(b.o_dq, hs.dq.units.data(), hs.dq.units.size() * sizeof(int4));
+    put(b.o_dqq, hs.dq.off.data(), hs.dq.off.size() * sizeof(int));
+  }
   put(b.o_kv, hs.kv_units.data(), hs.kv_units.size() * sizeof(int4));
   put(b.o_kvq, hs.kv_qoff.data(), hs.kv_qoff.size() * sizeof(int));
   put(b.o_pre, hs.pre_blocks.data(), hs.pre_blocks.size() * sizeof(nsp::PreBlock));
@@ -899,7 +968,6 @@ AttnBlob attn_blob(const HostAttnSched &hs) {
 nsp::Schedule attn_schedule_at(const HostAttnSched &hs, const AttnBlob &b, char *dev) {
   nsp::Schedule s;
   s.items = reinterpret_cast<ItemDesc *>(dev);
-  s.fwd_units = reinterpret_cast<int4 *>(dev + b.o_fwd);
   s.kv_units = reinterpret_cast<int4 *>(dev + b.o_kv);
   s.kv_qoff = reinterpret_cast<int *>(dev + b.o_kvq);
   s.pre_blocks = reinterpret_cast<nsp::PreBlock *>(dev + b.o_pre);
@@ -909,15 +977,17 @@ nsp::Schedule attn_schedule_at(const HostAttnSched &hs, const AttnBlob &b, char 
   s.n_kv_wgs = (int)hs.kv_wgs.size();
   s.n_kv_reduce = (int)hs.kv_reduce.size();
   s.n_items = (int)hs.items.size();
-  s.n_fwd_units = (int)hs.q_units.size();
-  s.fwd_qoff = reinterpret_cast<int *>(dev + b.o_fwdq);
   auto longest = [](const std::vector<int> &off) {
     int n = 0;
     for (size_t x = 0; x + 1 < off.size(); ++x) n = std::max(n, off[x + 1] - off[x]);
     return n;
   };
-  s.fwd_longest = longest(hs.q_off);
-  s.fwd_one_shot = hs.one_shot;
+  auto pass = [&](const QUnits &q, size_t o_units, size_t o_off) {
+    return nsp::QPass{reinterpret_cast<int4 *>(dev + o_units), reinterpret_cast<int *>(dev + o_off),
+                      (int)q.units.size(), longest(q.off), q.kind, q.one_shot};
+  };
+  s.fwd = pass(hs.fwd, b.o_fwd, b.o_fwdq);
+  s.dq = pass(hs.dq, b.o_dq, b.o_dqq);
   s.kv_longest = longest(hs.kv_qoff);
   s.n_kv_units = (int)hs.kv_units.size();
   s.n_pre_blocks = (int)hs.pre_blocks.size();
@@ -1094,6 +1164,10 @@ nsp_status get_host_schedule(const std::string &key, const nsp_worklist *wl, Hos
     auto h = std::make_shared<HostSched>();
     h->hs = build_attn_schedule(wl);
     h->blob = attn_blob(h->hs);
+    if (h->blob.bytes.size() > nsp::kScratchSchedBytes) {
+      h->hs = build_attn_schedule(wl, true);
+      h->blob = attn_blob(h->hs);
+    }
     *made = std::move(h);
     return (int)NSP_OK;
   });
@@ -1115,6 +1189,14 @@ nsp_status noalloc_upload(int dev, const std::string &key, const HostSched &h, c
                      "copying the schedule into the device scratch"));
   g_noalloc_key[dev] = key;
   return NSP_OK;
+}
+
+void set_pass(nsp::AttnArgs *a, const nsp::QPass &q) {
+  a->units = q.units;
+  a->qoff = q.off;
+  a->q_longest = q.longest;
+  a->q_kind = q.kind;
+  a->one_shot = q.one_shot;
 }
 
 // The three backward kernels on `stream`: preprocess (-Delta, lse2, and the
@@ -1161,11 +1243,8 @@ nsp_status launch_backward(int D, const nsp::Schedule &s, float softmax_scale, c
                                   [&] { return nsp::launch_bwd_dkdv(D, g32, a, split ? s.n_kv_wgs : s.n_kv_units,
                                                                     stream); }),
                      "backward dK/dV launch"));
-  a.units = s.fwd_units;
-  a.qoff = s.fwd_qoff;
-  a.q_longest = s.fwd_longest;
-  a.one_shot = s.fwd_one_shot;
-  return hip_status(timed_launch(K_DQ, stream, [&] { return nsp::launch_bwd_dq(D, g32, a, s.n_fwd_units, stream); }),
+  set_pass(&a, s.dq);
+  return hip_status(timed_launch(K_DQ, stream, [&] { return nsp::launch_bwd_dq(D, g32, a, s.dq.n_units, stream); }),
                     "backward dQ launch");
 }
 
@@ -1198,16 +1277,13 @@ nsp_status nsp_varlen_attn_fwd(const nsp_worklist *wl, float softmax_scale, int3
   a.o_out = o;
   a.lse = lse;
   a.items = s.items;
-  a.units = s.fwd_units;
-  a.qoff = s.fwd_qoff;
-  a.q_longest = s.fwd_longest;
-  a.one_shot = s.fwd_one_shot;
+  set_pass(&a, s.fwd);
   a.n_items = s.n_items;
   a.scale = softmax_scale;
   a.scale_log2 = softmax_scale * 1.4426950408889634f;
   return hip_status(timed_launch(K_FWD, stream,
                                  [&] { return nsp::launch_attn_fwd(wl->head_dim, o_dtype == NSP_F32, a,
-                                                                   s.n_fwd_units, stream); }),
+                                                                   s.fwd.n_units, stream); }),
                     "attention forward launch");
 }
 

@@ -47,6 +47,10 @@ constexpr int kFwdBM = 32 * kFwdWaves;   // query rows per forward / dQ workgrou
 constexpr int kFwdBN = 64;    // keys per inner iteration
 constexpr int kBwdBN = 128;   // keys per dK/dV workgroup (4 waves x 32)
 constexpr int kBwdBM = 64;    // query rows per dK/dV pipeline step (two 32-row sub-steps)
+// Forward and dQ units of a call: 256 query rows by eight waves, 128 rows by four (two
+// workgroups a compute unit), or 128 rows by eight in two groups that share the
+// keys.
+enum QKind { kQWhole = 0, kQHalf = 1, kQKeys = 2 };
 // Consecutive LPT units placed on one XCD (about the workgroups an XCD runs at once).
 constexpr int kXcdGroupFwd = 32;
 // dK/dV unit tile field: 128-key tile index, and the flag of a unit that
@@ -82,12 +86,20 @@ constexpr size_t kv_part_bytes(int D) { return kKvSlots * (size_t)kv_slot_floats
 //   forward / dQ : a = local query head, b = local KV head
 //   dK / dV      : a = first local query head | (end local query head << 16),
 //                  b = local KV head
+// The forward and dQ units of a schedule (device): per-XCD queues one after
+// another, queue x is units[off[x] .. off[x+1]).
+struct QPass {
+  int4 *units = nullptr;
+  int *off = nullptr;
+  int n_units = 0;
+  int longest = 0;         // entries of the longest queue
+  int kind = kQWhole;      // QKind
+  bool one_shot = false;   // one workgroup a unit, also with more units than fit at once
+};
+
 struct Schedule {
   ItemDesc *items = nullptr;   // device
-  int4 *fwd_units = nullptr;   // device, forward and dQ units, per-XCD queues one after another
-  int *fwd_qoff = nullptr;     // device, 9 ints: queue x is fwd_units[fwd_qoff[x] .. fwd_qoff[x+1])
-  int fwd_longest = 0, kv_longest = 0;   // entries of the longest forward / dQ and dK/dV queues
-  bool fwd_one_shot = false;   // forward / dQ: one workgroup a unit, also with more units than compute units
+  QPass fwd, dq;
   int4 *kv_units = nullptr;    // device, dK/dV units, per-XCD queues one after another
   int *kv_qoff = nullptr;      // device, 9 ints: queue x is kv_units[kv_qoff[x] .. kv_qoff[x+1])
   KvPiece *kv_pieces = nullptr;   // device, split dK/dV: the pieces, workgroup by workgroup
@@ -96,8 +108,7 @@ struct Schedule {
   int n_kv_wgs = 0, n_kv_reduce = 0;
   PreBlock *pre_blocks = nullptr; // device, the preprocess workgroups of the items the call computes
   int n_items = 0;
-  int n_fwd_units = 0;
-  int n_kv_units = 0;
+  int n_kv_units = 0, kv_longest = 0;
   int n_pre_blocks = 0;
   int64_t q_rows = 0;          // sum_j L_j * hq_j
   int64_t q_elems = 0, kv_elems = 0, lse_elems = 0;
@@ -124,6 +135,7 @@ struct AttnArgs {
   float *part;            // split dK/dV: partial sums, kv_slot_floats a slot
   const int *qoff;        // start of each XCD's queue in `units`, and the end
   int q_longest;          // entries of the longest of them
+  int q_kind;             // QKind of the units
   bool one_shot;          // one workgroup a unit, also with more units than compute units
   int n_items;
   float scale;            // softmax scale

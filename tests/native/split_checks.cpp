@@ -5,8 +5,8 @@
 // shares than compute units and none much longer than the mean; a masked call
 // runs exactly the unmasked call's pieces of its items; the workspace that the
 // query asks for and the allocation-free scratch hold the slots.  And the gangs of
-// the forward / dQ units: a permutation of the unit list on queues of about
-// equal work.  Built with
+// the forward / dQ units: the unit list, or its halves, on queues of about equal
+// work, of a kind that changes results only with the whole list.  Built with
 // g++ from the library's host sources; prints "split checks ok".
 #include "nsp_abi.cpp"
 
@@ -121,33 +121,71 @@ void check_list(const nsp_worklist &w, const std::vector<uint8_t> &mask, int *n_
   }
 }
 
-void check_gangs(const nsp_worklist &w) {
+void check_gangs(const nsp_worklist &w, int *kinds) {
   const HostAttnSched s = build_attn_schedule(&w);
   auto key = [](const int4 &u) { return std::make_tuple(u.x, u.y, u.z, u.w); };
-  std::multiset<std::tuple<int, int, int, int>> a, b;
-  for (const int4 &u : s.fwd_units) a.insert(key(u));
-  for (const int4 &u : s.q_units) b.insert(key(u));
-  CHECK(a == b && s.q_off.size() == 9 && s.q_off[0] == 0 && s.q_off[8] == (int)s.q_units.size());
-  int64_t most = 0, total = 0, gang = 0;
-  for (int x = 0; x < 8; ++x) {
-    CHECK(s.q_off[x] <= s.q_off[x + 1]);
-    int64_t work = 0;
-    for (int k = s.q_off[x]; k < s.q_off[x + 1]; ++k) {
-      const int L = w.cu_seqlens[s.q_units[k].x + 1] - w.cu_seqlens[s.q_units[k].x];
-      const int64_t c = (std::min(L, 256 * (s.q_units[k].y + 1)) + 63) / 64 + kUnitCost;
-      work += c;
-      gang = std::max(gang, c * kFwdGang);
+  for (const QUnits *q : {&s.fwd, &s.dq}) {
+    kinds[q->kind] += 1;
+    const int rows = q->kind == nsp::kQWhole ? 256 : 128;
+    std::multiset<std::tuple<int, int, int, int>> want, got;
+    for (const int4 &u : s.fwd_units)
+      for (int p = 0; p < 256 / rows; ++p) {
+        const int tile = u.y * (256 / rows) + p, L = w.cu_seqlens[u.x + 1] - w.cu_seqlens[u.x];
+        if (tile * rows < L) want.insert(std::make_tuple(u.x, tile, u.z, u.w));
+      }
+    for (const int4 &u : q->units) got.insert(key(u));
+    CHECK(want == got && q->off.size() == 9 && q->off[0] == 0 && q->off[8] == (int)q->units.size());
+    int64_t most = 0, total = 0, longest = 0;
+    for (int x = 0; x < 8; ++x) {
+      CHECK(q->off[x] <= q->off[x + 1]);
+      int64_t work = 0;
+      for (int k = q->off[x]; k < q->off[x + 1]; ++k) {
+        const int L = w.cu_seqlens[q->units[k].x + 1] - w.cu_seqlens[q->units[k].x];
+        const int64_t c = (std::min(L, rows * (q->units[k].y + 1)) + 63) / 64 + kUnitCost;
+        work += c;
+        longest = std::max(longest, c);
+      }
+      most = std::max(most, work);
+      total += work;
     }
-    most = std::max(most, work);
-    total += work;
+    CHECK(most <= total / 8 + longest * kFwdGang * (256 / rows));
   }
-  CHECK(most <= total / 8 + gang);
+  // two key groups: decided alike for every mask
+  nsp_worklist all = w;
+  all.item_mask = nullptr;
+  CHECK((build_attn_schedule(&all).fwd.kind == nsp::kQKeys) == (s.fwd.kind == nsp::kQKeys));
+  CHECK((s.dq.kind == nsp::kQKeys) == (s.fwd.kind == nsp::kQKeys));
+}
+
+// A list near the allocation-free scratch's limits: its schedule fits as it did
+// with 256-row units and 512-token preprocess blocks.
+void check_compact() {
+  std::vector<int32_t> cu(1, 0), qh, kvh;
+  for (int j = 0; j < 44700; ++j) {
+    cu.push_back(cu.back() + 129);
+    for (int k = 0; k < 2; ++k) {
+      qh.push_back(2 * k);
+      kvh.push_back(2 * k);
+    }
+  }
+  nsp_worklist w{};
+  w.n_items = 44700;
+  w.cu_seqlens = cu.data();
+  w.q_heads = qh.data();
+  w.kv_heads = kvh.data();
+  w.hq_total = w.hkv_total = 2;
+  w.head_dim = 64;
+  HostSchedPtr h;
+  CHECK(get_host_schedule(worklist_key("attn", 0, &w, 0), &w, &h) == NSP_OK);
+  CHECK(attn_blob(build_attn_schedule(&w)).bytes.size() > nsp::kScratchSchedBytes);
+  CHECK(h->blob.bytes.size() <= nsp::kScratchSchedBytes);
 }
 
 }  // namespace
 
 int main() {
-  int n_split = 0;
+  check_compact();
+  int n_split = 0, kinds[3] = {0, 0, 0};
   for (int rep = 0; rep < 400; ++rep) {
     static const int heads[][2] = {{32, 4}, {8, 2}, {16, 16}, {4, 1}, {12, 6}};
     const int *h = heads[uni(0, 4)];
@@ -173,11 +211,11 @@ int main() {
     w.hkv_total = h[1];
     w.head_dim = uni(0, 1) ? 128 : 64;
     check_list(w, mask, &n_split);
-    check_gangs(w);
+    check_gangs(w, kinds);
     w.item_mask = mask.data();
-    check_gangs(w);
+    check_gangs(w, kinds);
   }
-  CHECK(n_split > 100 && n_split < 400);
+  CHECK(n_split > 100 && n_split < 400 && kinds[0] > 50 && kinds[1] > 50 && kinds[2] > 50);
   std::printf("split checks ok (%d of 400 lists split)\n", n_split);
   return 0;
 }

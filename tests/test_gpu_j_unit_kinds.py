@@ -1,0 +1,80 @@
+"""The kinds of forward / dQ units: 256 query rows by eight waves, 128 rows by
+four (short units), 128 rows in two key groups (lists that leave compute units
+idle), at the sizes where one can go wrong: edges of 32, 128 and 256 rows and
+of 32 and 64 keys, rows whose second key group is empty, both head widths and
+output types, against the float64 oracle; and the same items beside long ones,
+in a list that takes 256-row units: 128-row units give the same bits, two key
+groups scale their P by another reference maximum before the bf16 rounding (half
+an ulp, 2^-9, on each side: O within 2^-8 in the 2-norm; the row sums, and so
+LSE, are float32 sums of the unrounded P)."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_2609_22755_amd import nsp
+from paper_2609_22755_amd.workloads import draw_attention_inputs, small_worklist
+
+from gpu_util import (FWD_MAX_ABS, FWD_REL_L2, GRAD_REL_L2, LSE_MAX_ABS, max_abs, oracle_full, rel_l2, report,
+                      require_gpu, run_attention, to_np)
+
+pytestmark = pytest.mark.gpu
+
+CASES = {
+    # name: (lengths, sp, hq, hkv, head_dim, the list takes two key groups)
+    "short_edges": ([1, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 160, 255, 256, 257, 300], None, 8, 2, 128, False),
+    "short_edges_d64": ([1, 32, 33, 64, 65, 128, 129, 255, 256, 257], None, 8, 2, 64, False),
+    "keys_one": ([1153], None, 4, 1, 128, True),
+    "keys_edges": ([1024, 1057, 33, 1], None, 4, 2, 128, True),
+    "keys_d64": ([1280, 130, 64], None, 4, 2, 64, True),
+}
+
+
+def padded(wl, lengths):
+    """The list with more items behind its own."""
+    k = len(lengths)
+    return dataclasses.replace(
+        wl, lengths=np.concatenate([wl.lengths, np.array(lengths, np.int32)]),
+        sp=np.concatenate([wl.sp, np.ones(k, np.int32)]),
+        q_heads=np.concatenate([wl.q_heads, np.tile([[0, wl.hq_total]], (k, 1))]),
+        kv_heads=np.concatenate([wl.kv_heads, np.tile([[0, wl.hkv_total]], (k, 1))]))
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_unit_kinds(name):
+    import torch
+    require_gpu()
+    lengths, sp, hq, hkv, D, keys = CASES[name]
+    wl = small_worklist(lengths, hq, hkv, D, sp=sp)
+    inp = draw_attention_inputs(wl, 500 + len(name))
+    scale = 1.0 / np.sqrt(D)
+    ref = oracle_full(wl, *inp, scale)
+    f32 = run_attention(wl, *inp, scale, o_dtype=torch.float32, g_dtype=torch.float32)
+    b16 = run_attention(wl, *inp, scale)
+    errs = dict(o=rel_l2(to_np(f32["o"]), ref["o"]), o_max=max_abs(to_np(f32["o"]), ref["o"]),
+                lse=max_abs(to_np(f32["lse"]), ref["lse"]), dq=rel_l2(to_np(b16["dq"]), ref["dq"]),
+                dq32=rel_l2(to_np(f32["dq"]), ref["dq"]))
+    report(f"kinds {name}", **errs)
+    assert errs["o"] <= FWD_REL_L2 and errs["o_max"] <= FWD_MAX_ABS and errs["lse"] <= LSE_MAX_ABS
+    assert errs["dq"] <= GRAD_REL_L2 and errs["dq32"] <= GRAD_REL_L2
+    assert torch.equal(b16["o"].view(torch.int16), f32["o"].to(torch.bfloat16).view(torch.int16))
+    big = padded(wl, [8192] * 4)
+    q, k, v, do = (nsp.to_device_bf16(x) for x in inp)
+
+    def wide(t, n):
+        return torch.cat([t, torch.zeros(n - t.numel(), dtype=t.dtype, device="cuda")])
+
+    x = [wide(q, big.q_elems()), wide(k, big.kv_elems()), wide(v, big.kv_elems())]
+    o = torch.full((big.q_elems(),), float("nan"), dtype=torch.float32, device="cuda")
+    lse = torch.full((big.lse_elems(),), float("nan"), dtype=torch.float32, device="cuda")
+    nsp.nsp_varlen_attn_fwd(big, *x, o, lse, scale)
+    torch.cuda.synchronize()
+    o, lse = o[:q.numel()], lse[:f32["lse"].numel()]
+    if keys:
+        err = rel_l2(to_np(o), to_np(f32["o"]))
+        report(f"kinds {name}: two key groups against one", o=err)
+        assert not torch.equal(o, f32["o"]), "the list does not take two key groups"
+        assert err <= 2.0 ** -8 and max_abs(to_np(lse), to_np(f32["lse"])) <= 1e-5
+    else:
+        assert torch.equal(o.view(torch.int32), f32["o"].view(torch.int32))
+        assert torch.equal(lse.view(torch.int32), f32["lse"].view(torch.int32))
