@@ -786,7 +786,7 @@ __device__ __forceinline__ void dkdv_unit(const AttnArgs &a, int item, int tile,
   const int n0 = tile * C::BN;
   const int i_lo = heads & 0xffff, i_hi = heads >> 16;
   const int wave = wave_id(), lane = threadIdx.x & 63;
-  const int l32 = lane & 31, h = lane >> 5;
+  const int l32 = lane & 31;
   const int64_t qs = (int64_t)it.hq * D;
   const int64_t ks = (int64_t)it.hkv * D;
   const int64_t kvhead = it.kv_off + (int64_t)g * D;
@@ -799,21 +799,6 @@ __device__ __forceinline__ void dkdv_unit(const AttnArgs &a, int item, int tile,
   const int n_iter = PIECE ? count : nh * (mt_end - mt0);
 
   KvState<D> st;
-  {
-    const int64_t r = kvhead + (int64_t)min(key, L - 1) * ks + 8 * h;
-#pragma unroll
-    for (int k = 0; k < C::KS; ++k) {
-      st.kf[k] = *(const bf16x8 *)((const bf16 *)a.k + r + 16 * k);
-      st.vf[k] = *(const bf16x8 *)((const bf16 *)a.v + r + 16 * k);
-    }
-    // K and V move to AGPRs here, once (they are the B operands of every S and
-    // dP product, which reads them from there)
-#pragma unroll
-    for (int k = 0; k < C::KS; ++k) {
-      asm volatile("" : "+a"(st.kf[k]));
-      asm volatile("" : "+a"(st.vf[k]));
-    }
-  }
 #pragma unroll
   for (int md = 0; md < C::MB; ++md) { st.dk[md] = f32x16{}; st.dv[md] = f32x16{}; }
   const float c = a.scale_log2;
@@ -841,14 +826,28 @@ __device__ __forceinline__ void dkdv_unit(const AttnArgs &a, int item, int tile,
   cu.dm = dm;
   cu.tq = (int64_t)dm * qs - (int64_t)(nh - 1) * D;
   cu.tl = dm - (nh - 1) * L;
-  // prologue: steps 0..2 in flight
+  // prologue: steps 0 and 1 in flight, and the K and V rows, through the other
+  // two stages
   kv_issue<D>(cu, stg0, L, row_bytes, 0 < n_iter);
   kv_issue<D>(cu, stg1, L, row_bytes, 1 < n_iter);
+  bf16 *const kreg = stg3 + wave * 32 * D, *const vreg = stg2 + wave * 32 * D;
+  start_rows<D>((const bf16 *)a.k + kvhead, ks, kbase, L, kreg, lane);
+  start_rows<D>((const bf16 *)a.v + kvhead, ks, kbase, L, vreg, lane);
+  wait_all_loads();
+  read_rows<D>(kreg, lane, st.kf);
+  read_rows<D>(vreg, lane, st.vf);
+  // K and V move to AGPRs here, once (they are the B operands of every S and
+  // dP product, which reads them from there)
+#pragma unroll
+  for (int k = 0; k < C::KS; ++k) {
+    asm volatile("" : "+a"(st.kf[k]));
+    asm volatile("" : "+a"(st.vf[k]));
+  }
+  wait_lds();
+  stage_barrier();
   kv_issue<D>(cu, stg2, L, row_bytes, 2 < n_iter);
   // the fill of the first step (step 3)
   KvFill<D> fill = kv_fill<D>(cu, stg3, L, row_bytes, 3 < n_iter);
-  __builtin_amdgcn_s_waitcnt(0);               // tiles 0..2, K and V landed
-  stage_barrier();
   {
     // moved into VGPRs (compiler-made copies, which wait for the matrix
     // core), like the S and dP the steps hand over: the loop-carried values
@@ -892,9 +891,10 @@ __device__ __forceinline__ void dkdv_unit(const AttnArgs &a, int item, int tile,
 #undef NSP_KV_STEP
   }
 
-  // nothing may still be loading into the stages when the next unit fills them
-  // (the stores below stay in flight)
+  // no load into the stages may still be in flight, and no wave still reading
+  // them, when the rows to store pass through them
   wait_all_loads();
+  stage_barrier();
   kv_drain<D>(st);
   if (PIECE && part) {
     // accumulator order: lane by lane, 16 bytes each, so that every store and
@@ -908,24 +908,12 @@ __device__ __forceinline__ void dkdv_unit(const AttnArgs &a, int item, int tile,
         *(f32x4 *)(p + C::BN * D) =
             f32x4{st.dv[md][4 * gq], st.dv[md][4 * gq + 1], st.dv[md][4 * gq + 2], st.dv[md][4 * gq + 3]};
       }
-  } else if (key < L) {
-    const int64_t obase = kvhead + (int64_t)key * ks;
-#pragma unroll
-    for (int md = 0; md < C::MB; ++md)
-#pragma unroll
-      for (int gq = 0; gq < 4; ++gq) {
-        const int d0 = 32 * md + 8 * gq + 4 * h;
-        f32x4 k4 = {st.dk[md][4 * gq] * a.scale, st.dk[md][4 * gq + 1] * a.scale,
-                    st.dk[md][4 * gq + 2] * a.scale, st.dk[md][4 * gq + 3] * a.scale};
-        f32x4 v4 = {st.dv[md][4 * gq], st.dv[md][4 * gq + 1], st.dv[md][4 * gq + 2], st.dv[md][4 * gq + 3]};
-        if constexpr (G_F32) {
-          *(f32x4 *)((float *)a.dk + obase + d0) = k4;
-          *(f32x4 *)((float *)a.dv + obase + d0) = v4;
-        } else {
-          *(bf16x4 *)((bf16 *)a.dk + obase + d0) = bf16x4{(bf16)k4[0], (bf16)k4[1], (bf16)k4[2], (bf16)k4[3]};
-          *(bf16x4 *)((bf16 *)a.dv + obase + d0) = bf16x4{(bf16)v4[0], (bf16)v4[1], (bf16)v4[2], (bf16)v4[3]};
-        }
-      }
+  } else if (kbase < L) {
+    const int esz = G_F32 ? 4 : 2;
+    const int64_t at = (kvhead + (int64_t)kbase * ks) * esz;
+    bf16 *const reg = wave == 0 ? stg0 : wave == 1 ? stg1 : wave == 2 ? stg2 : stg3;
+    store_rows<C::MB, G_F32>(st.dk, a.scale, reg, (char *)a.dk + at, ks * esz, L - kbase, lane);
+    store_rows<C::MB, G_F32>(st.dv, 1.f, reg + 32 * D * 2, (char *)a.dv + at, ks * esz, L - kbase, lane);
   }
 }
 
