@@ -106,8 +106,9 @@ class WorkList:
 
     @property
     def cu_seqlens(self) -> np.ndarray:
-        cu = np.zeros(self.n_items + 1, dtype=np.int32)
-        cu[1:] = np.cumsum(self.lengths, dtype=np.int64).astype(np.int32)
+        cu = np.empty(self.n_items + 1, dtype=np.int32)
+        cu[0] = 0
+        cu[1:] = np.add.accumulate(self.lengths, 0, np.int64)
         return cu
 
     @property
