@@ -962,6 +962,32 @@ __global__ void __launch_bounds__(256, 1) bwd_dkdv_split_kernel(AttnArgs a) {
   }
 }
 
+// dK/dV and dQ of a small list in one launch: the passes do not depend on each
+// other, and each alone leaves most compute units idle.  Workgroups 0 ..
+// n_kv_wgs-1 run the shares of the split dK/dV pass, the others a 128-row dQ
+// unit each (entry b / 8 of queue b % 8, as a one-shot pass; n_kv_wgs is a
+// multiple of 8).  One workgroup a compute unit (the dK/dV registers).
+template <int D, bool G_F32>
+__global__ void __launch_bounds__(256, 1) bwd_small_kernel(AttnArgs a, int n_kv_wgs) {
+  using C = KvCfg<D>;
+  __shared__ __attribute__((aligned(16))) bf16 stages[4 * C::STAGE];
+  static_assert(4 * C::STAGE >= 8 * DqCfg<D, 4, 1>::TILE, "the dQ rings fit the dK/dV stages");
+  if ((int)blockIdx.x < n_kv_wgs) {
+    const int2 r = a.wgs[blockIdx.x];
+    for (int i = r.x; i < r.y; ++i) {
+      const KvPiece p = a.pieces[i];
+      dkdv_unit<D, G_F32, true>(a, p.item, p.tile, false, p.heads, p.g, p.first, p.count,
+                                p.slot < 0 ? nullptr : a.part + p.slot * kv_slot_floats(D), stages,
+                                stages + C::STAGE, stages + 2 * C::STAGE, stages + 3 * C::STAGE);
+      wait_lds();
+      stage_barrier();
+    }
+  } else {
+    const int b = (int)blockIdx.x - n_kv_wgs, x = b % kXcdQueues, slot = a.qoff[x] + b / kXcdQueues;
+    if (slot < a.qoff[x + 1]) dq_unit<D, G_F32, 4, 1>(a, slot, stages);
+  }
+}
+
 // Sums of the pieces of a split key tile, in piece order, and the stores.
 // Workgroup (tile, dK or dV, 32-wide head_dim block); lane layout of the
 // accumulators.  Bound by memory: each partial sum read once.
@@ -1053,7 +1079,8 @@ hipError_t launch_bwd_dq(int head_dim, bool g_f32, const AttnArgs &a, int n_unit
 
 template <int D, bool G_F32>
 static hipError_t launch_split(const AttnArgs &a, int n_wgs, hipStream_t s) {
-  bwd_dkdv_split_kernel<D, G_F32><<<dim3(n_wgs), dim3(256), 0, s>>>(a);
+  if (a.small) bwd_small_kernel<D, G_F32><<<dim3(n_wgs + kXcdQueues * a.q_longest), dim3(256), 0, s>>>(a, n_wgs);
+  else bwd_dkdv_split_kernel<D, G_F32><<<dim3(n_wgs), dim3(256), 0, s>>>(a);
   if (a.n_reduce > 0) bwd_kv_reduce_kernel<D, G_F32><<<dim3(a.n_reduce * 2 * (D / 32)), dim3(256), 0, s>>>(a);
   return hipGetLastError();
 }

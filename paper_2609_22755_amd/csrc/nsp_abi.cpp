@@ -157,6 +157,7 @@ struct HostAttnSched {
   std::vector<ItemDesc> items;
   std::vector<int4> fwd_units, kv_units;
   QUnits fwd, dq;               // what the forward and dQ passes run
+  bool small = false;           // dK/dV and dQ in one launch
   std::vector<int> kv_qoff;     // kXcdQueues + 1 entries: the dK/dV queue of XCD x is kv_units[kv_qoff[x] ..)
   std::vector<nsp::PreBlock> pre_blocks;
   std::vector<nsp::KvPiece> kv_pieces;   // split dK/dV (empty: not split)
@@ -563,8 +564,8 @@ std::vector<KvGroup> kv_groups(const nsp_worklist *wl, int j) {
   return out;
 }
 
-// The shares of at most `cap` cost (steps + kPieceCost a piece): their number,
-// and the pieces if `out` is given.
+// The shares of at most `cap` cost (steps + kPieceCost a piece; 0: a share for
+// each whole tile): their number, and the pieces if `out` is given.
 int kv_cut(const nsp_worklist *wl, const std::vector<KvGroup> &groups, int64_t cap, KvSplit *out) {
   int shares = 0;
   int64_t room = 0;
@@ -577,9 +578,9 @@ int kv_cut(const nsp_worklist *wl, const std::vector<KvGroup> &groups, int64_t c
       int parts = 0;
       do {
         const int64_t rest = steps - at;
-        if (room < kPieceCost + std::min(rest, kMinPiece)) {
+        if (cap == 0 || room < kPieceCost + std::min(rest, kMinPiece)) {
           ++shares;
-          room = cap;
+          room = cap == 0 ? kPieceCost + rest : cap;
           if (out) out->share.push_back((int)out->pieces.size());
         }
         int64_t take = std::min(rest, room - kPieceCost);
@@ -601,7 +602,28 @@ int kv_cut(const nsp_worklist *wl, const std::vector<KvGroup> &groups, int64_t c
 
 size_t noalloc_part_room(int64_t lse_elems);
 
-// The split of a list's dK/dV pass; no pieces if it is not worth one.
+// Whether a backward runs dK/dV (in shares) and dQ in one launch: at most one
+// 128-row dQ unit a compute unit, of at most kSmallSteps 64-key steps.  Longer
+// units gain nothing beside the shares, which fill the chip then, and take more
+// from key groups.  Decided from every item, whatever the mask (it settles the
+// kind of the dQ units).  Whole backward, two launches / one: four items of 64
+// .. 512 tokens 29.7 / 20.6 us, one of 256 39.1 / 28.6, of 1024 74.4 / 68.3, a
+// 1024-token node of 4 heads 53.2 / 40.9, of 2048 (32 steps) 75.1 / 74.9, of 4096
+// (64) 139 / 141.
+constexpr int64_t kSmallSteps = 16;
+
+bool small_backward(const nsp_worklist *wl) {
+  int64_t halves = 0, longest = 0;
+  for (int j = 0; j < wl->n_items; ++j) {
+    const int64_t L = wl->cu_seqlens[j + 1] - wl->cu_seqlens[j], hq = wl->q_heads[2 * j + 1] - wl->q_heads[2 * j];
+    halves += hq * ((L + nsp::kFwdBM / 2 - 1) / (nsp::kFwdBM / 2));
+    longest = std::max(longest, (L + nsp::kFwdBN - 1) / nsp::kFwdBN);
+  }
+  return halves <= kAssumedCUs && longest <= kSmallSteps;
+}
+
+// The split of a list's dK/dV pass; no pieces if it is not worth one.  A list
+// whose backward runs in one launch gets whole tiles then, one a share.
 KvSplit kv_split(const nsp_worklist *wl) {
   KvSplit sp;
   std::vector<KvGroup> groups;
@@ -635,13 +657,17 @@ KvSplit kv_split(const nsp_worklist *wl) {
   }
   // the least share that needs no more shares than compute units
   int64_t lo = std::max(kPieceCost + kMinPiece, total / kAssumedCUs), hi = whole;
-  if (whole - lo < kSplitGain) return sp;
+  auto unsplit = [&] {
+    if (small_backward(wl) && cost.size() <= (size_t)kAssumedCUs) kv_cut(wl, groups, 0, &sp);
+    return sp;
+  };
+  if (whole - lo < kSplitGain) return unsplit();
   while (lo < hi) {
     const int64_t mid = (lo + hi) / 2;
     if (kv_cut(wl, groups, mid, nullptr) <= kAssumedCUs) hi = mid;
     else lo = mid + 1;
   }
-  if (whole - lo < kSplitGain + lo / 16) return sp;
+  if (whole - lo < kSplitGain + lo / 16) return unsplit();
   kv_cut(wl, groups, lo, &sp);
   // (the allocation-free backward, whose results are the same, has to hold it)
   const size_t slot_bytes = (size_t)nsp::kv_slot_floats(wl->head_dim) * sizeof(float);
@@ -687,17 +713,23 @@ void add_split(HostAttnSched &s, const nsp_worklist *wl) {
 //  * 128 rows and two key groups, one workgroup a compute unit: a list of at most
 //    one 256-row unit a compute unit lasts as long as its longest unit, which
 //    this cuts to about a quarter.  One 4096-token node of 4 heads 82 / 60 us,
-//    16384 tokens 348 / 270 (128-row units of one group: 67, 302).  The groups'
+//    16384 tokens 348 / 270 (128-row units of one group: 67, 302).  So does a list
+//    of at most one 128-row unit a compute unit, unless it is all short: four
+//    items of 64 .. 512 tokens 11.3 (one group) / 10.0 us, 3 of 1000, D = 64, 18.2 /
+//    15.4; one of 256 tokens 9.9 / 10.2, 4 of 300 (384 units) 13.7 / 17.9.  The groups'
 //    sums are rounded in another order, so this is decided from every item of
 //    the list, whatever the call's mask; the other two kinds give the same bits.
 constexpr double kShortUnitFwd = 8, kShortUnitDq = 20;
 
 int q_unit_kind(const nsp_worklist *wl, double short_unit) {
   int64_t units[2] = {0, 0}, steps[2] = {0, 0};   // of every item, of the call's
+  int64_t halves = 0, longest = 0;                // of every item
   for (int j = 0; j < wl->n_items; ++j) {
     const int64_t L = wl->cu_seqlens[j + 1] - wl->cu_seqlens[j], hq = wl->q_heads[2 * j + 1] - wl->q_heads[2 * j];
+    halves += hq * ((L + nsp::kFwdBM / 2 - 1) / (nsp::kFwdBM / 2));
     for (int64_t m = 0; m * nsp::kFwdBM < L; ++m) {
       const int64_t n = (std::min<int64_t>(L, nsp::kFwdBM * (m + 1)) + nsp::kFwdBN - 1) / nsp::kFwdBN;
+      longest = std::max(longest, n);
       for (int c = 0; c < (selected(wl, j) ? 2 : 1); ++c) {
         units[c] += hq;
         steps[c] += hq * n;
@@ -705,6 +737,7 @@ int q_unit_kind(const nsp_worklist *wl, double short_unit) {
     }
   }
   if (units[0] <= kAssumedCUs && steps[0] > kShortUnitFwd * units[0]) return nsp::kQKeys;
+  if (halves <= kAssumedCUs && longest >= kShortUnitFwd) return nsp::kQKeys;
   return units[1] <= kAssumedCUs || steps[1] <= short_unit * units[1] ? nsp::kQHalf : nsp::kQWhole;
 }
 
@@ -777,10 +810,11 @@ HostAttnSched build_attn_schedule(const nsp_worklist *wl, bool compact = false) 
   }
   s.q_rows = qo / D;
   lpt_sort(s.fwd_units, fcost);
-  s.fwd = q_units(wl, compact ? nsp::kQWhole : q_unit_kind(wl, kShortUnitFwd));
-  const int dq_kind = compact ? nsp::kQWhole : q_unit_kind(wl, kShortUnitDq);
-  s.dq = dq_kind == s.fwd.kind ? s.fwd : q_units(wl, dq_kind);
   add_split(s, wl);
+  s.fwd = q_units(wl, compact ? nsp::kQWhole : q_unit_kind(wl, kShortUnitFwd));
+  s.small = !s.kv_wgs.empty() && small_backward(wl);
+  const int dq_kind = compact ? nsp::kQWhole : s.small ? nsp::kQHalf : q_unit_kind(wl, kShortUnitDq);
+  s.dq = dq_kind == s.fwd.kind ? s.fwd : q_units(wl, dq_kind);
   kv_balance(item_gangs, wl);
   for (const KvGang *g : kv_queue_order(item_gangs, s.kv_qoff))
     s.kv_units.insert(s.kv_units.end(), g->units.begin(), g->units.end());
@@ -989,6 +1023,7 @@ nsp::Schedule attn_schedule_at(const HostAttnSched &hs, const AttnBlob &b, char 
   s.fwd = pass(hs.fwd, b.o_fwd, b.o_fwdq);
   s.dq = pass(hs.dq, b.o_dq, b.o_dqq);
   s.kv_longest = longest(hs.kv_qoff);
+  s.small = hs.small;
   s.n_kv_units = (int)hs.kv_units.size();
   s.n_pre_blocks = (int)hs.pre_blocks.size();
   s.q_rows = hs.q_rows;
@@ -1089,15 +1124,15 @@ struct TimingState {
 };
 TimingState g_timing;
 
+bool timing_on() {
+  std::lock_guard<std::mutex> lock(g_timing.mu);
+  return g_timing.on;
+}
+
 // Run `launch` on `stream`, bracketed by timing events when timing is on.
 template <class F>
 hipError_t timed_launch(KernelId id, hipStream_t stream, F launch) {
-  bool on;
-  {
-    std::lock_guard<std::mutex> lock(g_timing.mu);
-    on = g_timing.on;
-  }
-  if (!on) return launch();
+  if (!timing_on()) return launch();
   hipEvent_t a = nullptr, b = nullptr;
   hipError_t e = hipEventCreate(&a);
   if (e == hipSuccess) e = hipEventCreate(&b);
@@ -1238,11 +1273,15 @@ nsp_status launch_backward(int D, const nsp::Schedule &s, float softmax_scale, c
     a.reduce = s.kv_reduce;
     a.n_reduce = s.n_kv_reduce;
     a.part = part;
+    // (each kernel alone while they are timed)
+    a.small = s.small && !timing_on();
+    if (a.small) set_pass(&a, s.dq);
   }
   NSP_TRY(hip_status(timed_launch(K_DKDV, stream,
                                   [&] { return nsp::launch_bwd_dkdv(D, g32, a, split ? s.n_kv_wgs : s.n_kv_units,
                                                                     stream); }),
                      "backward dK/dV launch"));
+  if (a.small) return NSP_OK;
   set_pass(&a, s.dq);
   return hip_status(timed_launch(K_DQ, stream, [&] { return nsp::launch_bwd_dq(D, g32, a, s.dq.n_units, stream); }),
                     "backward dQ launch");

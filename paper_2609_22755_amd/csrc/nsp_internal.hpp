@@ -106,6 +106,7 @@ struct Schedule {
   int2 *kv_wgs = nullptr;         // device, workgroup b runs pieces kv_wgs[b].x .. kv_wgs[b].y - 1
   KvReduce *kv_reduce = nullptr;  // device, the key tiles in several pieces
   int n_kv_wgs = 0, n_kv_reduce = 0;
+  bool small = false;             // dK/dV and dQ in one launch
   PreBlock *pre_blocks = nullptr; // device, the preprocess workgroups of the items the call computes
   int n_items = 0;
   int n_kv_units = 0, kv_longest = 0;
@@ -132,6 +133,7 @@ struct AttnArgs {
   const int2 *wgs;
   const KvReduce *reduce;
   int n_reduce;
+  bool small;             // with the split pass, dQ units (128-row ones) in the same launch
   float *part;            // split dK/dV: partial sums, kv_slot_floats a slot
   const int *qoff;        // start of each XCD's queue in `units`, and the end
   int q_longest;          // entries of the longest of them
@@ -170,8 +172,9 @@ hipError_t compute_units(int *cus);
 hipError_t launch_attn_fwd(int head_dim, bool o_f32, const AttnArgs &a, int n_units, hipStream_t s);
 hipError_t launch_bwd_preprocess(int head_dim, bool o_f32, const AttnArgs &a, int n_blocks, hipStream_t s);
 hipError_t launch_bwd_dq(int head_dim, bool g_f32, const AttnArgs &a, int n_units, hipStream_t s);
-// With a.wgs the split pass (n_units workgroups over a.pieces, then the sums of
-// the a.n_reduce tiles of a.reduce), else the units of a.units.
+// With a.wgs the split pass (n_units workgroups over a.pieces, with a.small the
+// dQ units of a.units too, then the sums of the a.n_reduce tiles of a.reduce),
+// else the units of a.units.
 hipError_t launch_bwd_dkdv(int head_dim, bool g_f32, const AttnArgs &a, int n_units, hipStream_t s);
 hipError_t launch_relayout(const void *src, void *dst, const CopyTask *tasks, int n_tasks,
                            int sum_mode, hipStream_t s);

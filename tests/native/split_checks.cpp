@@ -150,11 +150,14 @@ void check_gangs(const nsp_worklist &w, int *kinds) {
     }
     CHECK(most <= total / 8 + longest * kFwdGang * (256 / rows));
   }
-  // two key groups: decided alike for every mask
+  // two key groups, one launch for dK/dV and dQ: decided alike for every mask
   nsp_worklist all = w;
   all.item_mask = nullptr;
-  CHECK((build_attn_schedule(&all).fwd.kind == nsp::kQKeys) == (s.fwd.kind == nsp::kQKeys));
-  CHECK((s.dq.kind == nsp::kQKeys) == (s.fwd.kind == nsp::kQKeys));
+  const HostAttnSched f = build_attn_schedule(&all);
+  if (s.fwd_units.empty()) return;
+  CHECK((f.fwd.kind == nsp::kQKeys) == (s.fwd.kind == nsp::kQKeys));
+  CHECK((f.dq.kind == nsp::kQKeys) == (s.dq.kind == nsp::kQKeys));
+  CHECK(f.small == s.small && (!s.small || (s.dq.kind == nsp::kQHalf && s.kv_wgs.size() % 8 == 0)));
 }
 
 // A list near the allocation-free scratch's limits: its schedule fits as it did

@@ -5,7 +5,7 @@ On the CPU the cuts are checked against brute force on random lists
 (tests/native/split_checks.cpp).  On the GPU, at the sizes where a piece can go
 wrong (pieces that start and end inside a query tile's heads, ragged ends, an
 odd number of key tiles, one query head a KV head, a KV head with none, both
-head widths), against the float64 oracle and against the whole tiles, which the
+head widths, lists small enough for one launch with dQ), against the float64 oracle and against the whole tiles, which the
 same items run in a list of more than 4096 key tiles (the others masked out):
 float32 sums of at most 2^16 terms in another order, whose relative difference
 is bounded by about sqrt(2^16) * 2^-24 = 1.5e-5 for sums without cancellation
@@ -53,6 +53,11 @@ CASES = {
     "mha": lambda: small_worklist([2999, 65], 2, 2, 128),
     "d64": lambda: small_worklist([2049, 500], 8, 2, 64),
     "lone_kv_head": _lone_kv_head,
+    # small lists: dQ units in the same launch, with tiles cut and whole
+    "small_mixed": lambda: small_worklist([200, 64, 33, 0, 1, 513], 32, 4, 128, sp=[2, 1, 1, 1, 1, 1],
+                                          rank=[1, 0, 0, 0, 0, 0]),
+    "small_d64": lambda: small_worklist([64, 129, 256, 511], 8, 2, 64),
+    "small_whole": lambda: small_worklist([17, 31], 4, 2, 128),
 }
 
 
