@@ -155,7 +155,8 @@ struct QUnits {
 
 struct HostAttnSched {
   std::vector<ItemDesc> items;
-  std::vector<int4> fwd_units, kv_units;
+  std::vector<int4> fwd_units;  // in the order that nsp_attn_schedule reports (built for it only)
+  std::vector<int4> kv_units;
   QUnits fwd, dq;               // what the forward and dQ passes run
   bool small = false;           // dK/dV and dQ in one launch
   std::vector<int> kv_qoff;     // kXcdQueues + 1 entries: the dK/dV queue of XCD x is kv_units[kv_qoff[x] ..)
@@ -338,25 +339,32 @@ constexpr int64_t kUnitCost = 4;   // 64-key steps that starting and ending a un
 // a KV head (103 steps) 239 / 263; 32 of 2048 (576 steps) 1117 / 1244.
 constexpr int64_t kOneShotSteps = 80;
 
-void add_fwd_gangs(std::vector<KvGang> &gangs, const nsp_worklist *wl, int j, int L, int rows) {
+struct QGang {
+  int64_t cost, dur;            // of all its units; of the longest
+  int first, n;                 // units
+};
+
+void add_fwd_gangs(std::vector<QGang> &gangs, std::vector<int4> &units, const nsp_worklist *wl, int j, int L,
+                   int rows) {
   const int ql = wl->q_heads[2 * j], hq = wl->q_heads[2 * j + 1] - ql;
   const int kl = wl->kv_heads[2 * j], hkv = wl->kv_heads[2 * j + 1] - kl;
-  for (int g = 0; g < hkv; ++g) {
-    std::vector<int> heads;
-    for (int i = 0; i < hq; ++i)
-      if ((int)(((int64_t)(ql + i) * wl->hkv_total) / wl->hq_total) - kl == g) heads.push_back(i);
-    const int nq = (L + rows - 1) / rows, per = nsp::kFwdBM / rows;
-    const int most = std::min(kFwdGang * per, std::max(2 * per, nq / 4) * (int)heads.size());
-    for (int m = nq - 1, n = 0; m >= 0; --m)
-      for (int i : heads) {
-        if (n++ % most == 0) gangs.emplace_back();
-        KvGang &gang = gangs.back();
-        const int64_t steps = (std::min<int64_t>(L, (int64_t)rows * (m + 1)) + nsp::kFwdBN - 1) / nsp::kFwdBN;
-        gang.units.push_back(int4{j, m, i, g});
-        gang.steps.push_back(steps);
-        gang.cost += steps + kUnitCost;
-        gang.dur = std::max(gang.dur, steps);
+  const int nq = (L + rows - 1) / rows, per = nsp::kFwdBM / rows;
+  for (int g = 0, i0 = 0; g < hkv; ++g) {
+    // local query heads i0 .. i1-1 use KV head g (the map is monotone)
+    auto kv = [&](int i) { return (int)(((int64_t)(ql + i) * wl->hkv_total) / wl->hq_total) - kl; };
+    int i1 = i0;
+    while (i1 < hq && kv(i1) == g) ++i1;
+    const int most = std::min(kFwdGang * per, std::max(2 * per, nq / 4) * (i1 - i0));
+    for (int m = nq - 1, n = 0; m >= 0; --m) {
+      const int64_t steps = (std::min<int64_t>(L, (int64_t)rows * (m + 1)) + nsp::kFwdBN - 1) / nsp::kFwdBN;
+      for (int i = i0; i < i1; ++i) {
+        if (n++ % most == 0) gangs.push_back(QGang{0, steps, (int)units.size(), 0});
+        units.push_back(int4{j, m, i, g});
+        gangs.back().n += 1;
+        gangs.back().cost += steps + kUnitCost;
       }
+    }
+    i0 = i1;
   }
 }
 
@@ -536,9 +544,10 @@ struct KvSplit {
 // kSplitGain: the steps that the split has to gain beside a sixteenth of the
 // pass, for the sum pass; at 12 steps' gain (20 items of 300 tokens) the
 // backward takes 167 us against 176, at none (4 items of 4000) 1616 against
-// 1614.  Lists of more than kMaxSplitTiles key tiles fill the chip without.
+// 1614.  Lists of more than kMaxSplitTiles key tiles, four
+// a compute unit, leave longest-first order little to gain.
 constexpr int64_t kPieceCost = 12, kMinPiece = 4, kSplitGain = 4;
-constexpr size_t kMaxSplitTiles = 4096;
+constexpr size_t kMaxSplitTiles = 1024;
 
 // Key tiles of one local KV head of an item, longest first: their query heads
 // (first | end << 16) and steps a query tile.
@@ -744,17 +753,31 @@ int q_unit_kind(const nsp_worklist *wl, double short_unit) {
 QUnits q_units(const nsp_worklist *wl, int kind) {
   QUnits q;
   q.kind = kind;
-  ItemGangs gangs;
+  std::vector<QGang> gangs;
+  std::vector<int4> units;
   for (int j = 0; j < wl->n_items; ++j) {
     const int L = wl->cu_seqlens[j + 1] - wl->cu_seqlens[j];
-    if (L == 0 || !selected(wl, j)) continue;
-    gangs.emplace_back(j, std::vector<KvGang>());
-    add_fwd_gangs(gangs.back().second, wl, j, L, kind == nsp::kQWhole ? nsp::kFwdBM : nsp::kFwdBM / 2);
+    if (L > 0 && selected(wl, j)) add_fwd_gangs(gangs, units, wl, j, L, kind == nsp::kQWhole ? nsp::kFwdBM : nsp::kFwdBM / 2);
   }
-  int64_t steps = 0;
-  for (const KvGang *g : kv_queue_order(gangs, q.off)) {
-    q.units.insert(q.units.end(), g->units.begin(), g->units.end());
-    for (int64_t n : g->steps) steps += n;
+  // as kv_queue_order
+  std::stable_sort(gangs.begin(), gangs.end(), [](const QGang &a, const QGang &b) { return a.dur > b.dur; });
+  int64_t load[kNumXcd] = {0}, steps = 0;
+  std::vector<uint8_t> queue(gangs.size());
+  int count[kNumXcd] = {0};
+  for (size_t i = 0; i < gangs.size(); ++i) {
+    const int x = (int)(std::min_element(load, load + kNumXcd) - load);
+    load[x] += gangs[i].cost;
+    count[x] += gangs[i].n;
+    queue[i] = (uint8_t)x;
+    steps += gangs[i].cost - kUnitCost * gangs[i].n;
+  }
+  q.off.assign(kNumXcd + 1, 0);
+  for (int x = 0; x < kNumXcd; ++x) q.off[x + 1] = q.off[x] + count[x];
+  std::vector<int> at(q.off.begin(), q.off.end() - 1);
+  q.units.resize(units.size());
+  for (size_t i = 0; i < gangs.size(); ++i) {
+    std::copy_n(units.begin() + gangs[i].first, gangs[i].n, q.units.begin() + at[queue[i]]);
+    at[queue[i]] += gangs[i].n;
   }
   if (kind != nsp::kQWhole) steps /= 2;          // of 256-row units: two 128-row ones are one
   q.one_shot = steps <= kOneShotSteps * kAssumedCUs;
@@ -764,8 +787,12 @@ QUnits q_units(const nsp_worklist *wl, int kind) {
 // `compact`: 256-row units and large preprocess blocks whatever the list, for a
 // schedule that has to fit a limited space (the results are the same bits: lists
 // that split their dK/dV or take key groups are too small to need it).
-HostAttnSched build_attn_schedule(const nsp_worklist *wl, bool compact = false) {
+// `report`: for nsp_attn_schedule, the forward / dQ units in reported order and
+// the whole dK/dV units, which the passes of some lists do not run.
+HostAttnSched build_attn_schedule(const nsp_worklist *wl, bool compact = false, bool report = false) {
   HostAttnSched s;
+  add_split(s, wl);
+  const bool whole_kv = report || s.kv_wgs.empty();
   const int D = wl->head_dim;
   int64_t qo = 0, ko = 0, lo = 0;
   std::vector<int64_t> fcost;
@@ -794,15 +821,19 @@ HostAttnSched build_attn_schedule(const nsp_worklist *wl, bool compact = false) 
       for (int i = 0; i < hq; ++i)
         for (int t = 0; t < L; t += pre_rows)
           s.pre_blocks.push_back(nsp::PreBlock{j, i, t, std::min(pre_rows, L - t)});
-      const int nq = (L + nsp::kFwdBM - 1) / nsp::kFwdBM;
-      for (int m = 0; m < nq; ++m)
-        for (int i = 0; i < hq; ++i) {
-          const int g = (int)(((int64_t)(ql + i) * wl->hkv_total) / wl->hq_total) - kl;
-          s.fwd_units.push_back(int4{j, m, i, g});
-          fcost.push_back(std::min<int64_t>(L, (int64_t)nsp::kFwdBM * (m + 1)));
-        }
-      item_gangs.emplace_back(j, std::vector<KvGang>());
-      add_kv_gangs(item_gangs.back().second, wl, j, L, 0);
+      if (report) {
+        const int nq = (L + nsp::kFwdBM - 1) / nsp::kFwdBM;
+        for (int m = 0; m < nq; ++m)
+          for (int i = 0; i < hq; ++i) {
+            const int g = (int)(((int64_t)(ql + i) * wl->hkv_total) / wl->hq_total) - kl;
+            s.fwd_units.push_back(int4{j, m, i, g});
+            fcost.push_back(std::min<int64_t>(L, (int64_t)nsp::kFwdBM * (m + 1)));
+          }
+      }
+      if (whole_kv) {
+        item_gangs.emplace_back(j, std::vector<KvGang>());
+        add_kv_gangs(item_gangs.back().second, wl, j, L, 0);
+      }
     }
     qo += (int64_t)L * hq * D;
     ko += (int64_t)L * hkv * D;
@@ -810,7 +841,6 @@ HostAttnSched build_attn_schedule(const nsp_worklist *wl, bool compact = false) 
   }
   s.q_rows = qo / D;
   lpt_sort(s.fwd_units, fcost);
-  add_split(s, wl);
   s.fwd = q_units(wl, compact ? nsp::kQWhole : q_unit_kind(wl, kShortUnitFwd));
   s.small = !s.kv_wgs.empty() && small_backward(wl);
   const int dq_kind = compact ? nsp::kQWhole : s.small ? nsp::kQHalf : q_unit_kind(wl, kShortUnitDq);
@@ -1476,7 +1506,7 @@ nsp_status nsp_attn_schedule(const nsp_worklist *wl, int32_t which, int32_t *uni
   NSP_TRY(validate_worklist(wl, nullptr));
   if (which != NSP_SCHED_FWD && which != NSP_SCHED_KV) return fail(NSP_EINVAL, "unknown schedule %d", which);
   if (!n_units) return fail(NSP_EINVAL, "n_units is NULL");
-  const HostAttnSched hs = build_attn_schedule(wl);
+  const HostAttnSched hs = build_attn_schedule(wl, false, true);
   const std::vector<int4> &u = which == NSP_SCHED_FWD ? hs.fwd_units : hs.kv_units;
   *n_units = (int64_t)u.size();
   if (!units && capacity == 0) return NSP_OK;
@@ -1496,7 +1526,7 @@ nsp_status nsp_attn_kv_queues(const nsp_worklist *wl, int32_t *queue_off) {
   g_last_error.clear();
   NSP_TRY(validate_worklist(wl, nullptr));
   if (!queue_off) return fail(NSP_EINVAL, "queue_off is NULL");
-  const HostAttnSched hs = build_attn_schedule(wl);
+  const HostAttnSched hs = build_attn_schedule(wl, false, true);
   for (int x = 0; x <= kNumXcd; ++x) queue_off[x] = hs.kv_qoff[x];
   return NSP_OK;
 }

@@ -122,7 +122,7 @@ void check_list(const nsp_worklist &w, const std::vector<uint8_t> &mask, int *n_
 }
 
 void check_gangs(const nsp_worklist &w, int *kinds) {
-  const HostAttnSched s = build_attn_schedule(&w);
+  const HostAttnSched s = build_attn_schedule(&w, false, true);
   auto key = [](const int4 &u) { return std::make_tuple(u.x, u.y, u.z, u.w); };
   for (const QUnits *q : {&s.fwd, &s.dq}) {
     kinds[q->kind] += 1;
@@ -153,8 +153,10 @@ void check_gangs(const nsp_worklist &w, int *kinds) {
   // two key groups, one launch for dK/dV and dQ: decided alike for every mask
   nsp_worklist all = w;
   all.item_mask = nullptr;
-  const HostAttnSched f = build_attn_schedule(&all);
+  const HostAttnSched f = build_attn_schedule(&all, false, true);
   if (s.fwd_units.empty()) return;
+  const HostAttnSched d = build_attn_schedule(&w);   // what the passes take
+  CHECK(d.fwd.units.size() == s.fwd.units.size() && d.kv_units.size() == (d.kv_wgs.empty() ? s.kv_units.size() : 0));
   CHECK((f.fwd.kind == nsp::kQKeys) == (s.fwd.kind == nsp::kQKeys));
   CHECK((f.dq.kind == nsp::kQKeys) == (s.dq.kind == nsp::kQKeys));
   CHECK(f.small == s.small && (!s.small || (s.dq.kind == nsp::kQHalf && s.kv_wgs.size() % 8 == 0)));

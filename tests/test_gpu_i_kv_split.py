@@ -6,7 +6,7 @@ On the CPU the cuts are checked against brute force on random lists
 wrong (pieces that start and end inside a query tile's heads, ragged ends, an
 odd number of key tiles, one query head a KV head, a KV head with none, both
 head widths, lists small enough for one launch with dQ), against the float64 oracle and against the whole tiles, which the
-same items run in a list of more than 4096 key tiles (the others masked out):
+same items run in a list of more than 1024 key tiles (the others masked out):
 float32 sums of at most 2^16 terms in another order, whose relative difference
 is bounded by about sqrt(2^16) * 2^-24 = 1.5e-5 for sums without cancellation
 (P and dS themselves are computed alike, bit for bit).
@@ -30,8 +30,8 @@ SUM_REL = 1.5e-5
 
 
 def padded(wl):
-    """The work list with more than 4096 one-token items behind it, masked out."""
-    k = 4096 // wl.hkv_total + 1
+    """The work list with more than 1024 one-token key tiles behind it, masked out."""
+    k = 1024 // wl.hkv_total + 1
     return dataclasses.replace(
         wl, lengths=np.concatenate([wl.lengths, np.ones(k, np.int32)]), sp=np.concatenate([wl.sp, np.ones(k, np.int32)]),
         q_heads=np.concatenate([wl.q_heads, np.tile([[0, wl.hq_total]], (k, 1))]),
