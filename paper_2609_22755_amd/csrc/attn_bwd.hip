@@ -116,7 +116,10 @@ struct DqCfg {
   // the tiles of a group are loaded by its first NL waves, as in the forward
   static constexpr int NL = 4;
   static constexpr int LPW = 2 * TileLoader<D, BN, NL>::PER_WAVE;   // loads per loading wave and tile
-  static constexpr int PER_CU = NW == 4 ? 2 : 1;                    // workgroups a compute unit holds
+  // workgroups a compute unit holds (a third of head_dim 64 fits once it is
+  // held to 168 registers: whole backward, 200 items of 300 tokens 200 -> 188 us,
+  // 300 of 100 104 -> 98; the forward gains nothing from a third)
+  static constexpr int PER_CU = NW == 4 ? (D == 64 ? 3 : 2) : 1;
   static_assert((RB == 8 && KG == 1) || RB == 4, "256-row units, or 128-row ones of one or two key groups");
 };
 
@@ -347,7 +350,7 @@ __device__ __forceinline__ void dq_unit(const AttnArgs &a, int slot, bf16 *smem)
 // dQ pass over the per-XCD queues (a.qoff), as the dK/dV pass: with queue heads
 // persistent workgroups, without one workgroup per unit.
 template <int D, bool G_F32, int RB, int KG>
-__global__ void __launch_bounds__(64 * RB * KG, (RB * KG == 4 ? 2 : 1)) bwd_dq_kernel(AttnArgs a, int *heads) {
+__global__ void __launch_bounds__(64 * RB * KG, (RB * KG == 4 ? (D == 64 ? 3 : 2) : 1)) bwd_dq_kernel(AttnArgs a, int *heads) {
   __shared__ __attribute__((aligned(16))) bf16 smem[KG * 8 * DqCfg<D, RB, KG>::TILE];
   __shared__ int s_slot;
   UnitQueue q(heads, a.qoff, &s_slot);
