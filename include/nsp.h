@@ -459,7 +459,10 @@ nsp_status nsp_sp_tree_worklist(const nsp_plan_params *prm, const int64_t *lengt
  * kernel alone.  nsp_timing_query waits for the recorded events, folds them
  * into per-kernel totals and returns the launch count and total milliseconds
  * since the last nsp_timing_reset for one kernel name: "attn_fwd",
- * "bwd_preprocess", "bwd_dkdv", "bwd_dq" or "relayout".
+ * "bwd_preprocess", "bwd_dkdv", "bwd_dq" or "relayout".  (A backward runs
+ * "bwd_preprocess", "bwd_dkdv" with the sums of a split pass, "bwd_dq"; lists of
+ * shorter items "bwd_dq", which takes in the preprocess, then "bwd_dkdv"; small
+ * lists "bwd_preprocess", then both passes in one launch, counted as "bwd_dkdv".)
  * Errors: NSP_EINVAL (unknown name or NULL outputs), NSP_EHIP.
  */
 nsp_status nsp_timing_enable(int32_t enable);

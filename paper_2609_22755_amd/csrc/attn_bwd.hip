@@ -5,10 +5,12 @@
 //   dS = P * (dP - Delta), dQ = scale * dS K, dK = scale * dS^T Q, dV = P^T dO,
 // with dK/dV summed over the local query heads that share a KV head.
 //
-// Three passes, deterministic (no atomics; every output element is written
-// by exactly one lane):
-//   preprocess : -Delta per (item, head, row) and lse*log2(e), float32,
-//                layout of lse (-Delta starts the dP product chains).
+// Two passes, deterministic (no atomics on data; every output element is
+// written by exactly one lane), dQ first: it leaves -Delta per (item, head,
+// row) and lse*log2(e), float32, in the layout of lse (-Delta starts the dP
+// product chains) for the dK/dV pass.  Small lists run both in one launch,
+// after a preprocess pass for those two; lists of long units, and calls whose dQ
+// overwrites an input, run preprocess, dK/dV, dQ.
 //   dK/dV      : unit = (item, KV head, 128-key tile); four waves, each owning
 //                32 keys whose K and V rows stay in registers.  The unit loops
 //                over the 64-row query tiles at or past its diagonal -- up
@@ -40,41 +42,45 @@
 namespace nsp {
 namespace {
 
-constexpr int kQueueSlots = 64;  // queue-head ints the preprocess resets (the workspace holds 256 bytes)
-constexpr int kKvQueue0 = 0;     // heads of the dK/dV pass's queues: slots 0..7
+constexpr int kKvQueue0 = 0;     // heads of the dK/dV pass's queues: slots 0..7 (the workspace holds 256 bytes)
 constexpr int kDqQueue0 = 8;     // heads of the dQ pass's queues: slots 8..15
+
+__global__ void bwd_reset_kernel(int *heads) {
+  if (threadIdx.x < kXcdQueues) heads[threadIdx.x] = 0;
+}
 
 // ------------------------------------------------------------ preprocess --
 
 // -Delta[t] = -sum_d dO[t,i,d] * O[t,i,d], and lse2 = lse * log2(e) (the
-// backward works in base 2).  Workgroup b covers the tokens of
-// a.pre_blocks[b] for one local query head (only the items the call computes
-// have blocks): one group of D/8 lanes per token, U tokens per lane group in
-// flight; consecutive lane groups take consecutive tokens, so that their
-// LSE / Delta entries are adjacent.  Block 0 also resets the unit-queue heads
-// that the passes after it on the same stream take their units from (a call
-// with no rows to process has no units either).
+// backward works in base 2), for the lists whose dK/dV and dQ run in one launch
+// and for calls that run dQ last (in the others the dQ pass runs first and
+// leaves both for the dK/dV pass).  Workgroup b covers dQ unit b, `rows` tokens
+// of one query head: one group of D/8 lanes per token, U tokens per lane group
+// in flight; consecutive lane groups take consecutive tokens, so that their
+// LSE / Delta entries are adjacent.  It also zeroes the queue heads of the passes
+// that follow.
 template <int D, bool O_F32>
-__global__ void __launch_bounds__(256) bwd_preprocess_kernel(AttnArgs a) {
-  if (blockIdx.x == 0 && threadIdx.x < kQueueSlots) a.queue[threadIdx.x] = 0;
+__global__ void __launch_bounds__(256) bwd_preprocess_kernel(AttnArgs a, int rows) {
   constexpr int LPR = D / 8;                 // lanes per token
   constexpr int TPP = 256 / LPR;             // tokens per pass of the workgroup
   constexpr int U = 4;                       // passes in flight
-  const PreBlock pb = a.pre_blocks[blockIdx.x];
-  const ItemDesc it = a.items[pb.item];
+  if (blockIdx.x == 0 && threadIdx.x < kDqQueue0 + kXcdQueues) a.queue[threadIdx.x] = 0;
+  const int4 un = a.units[blockIdx.x];
+  const ItemDesc it = a.items[un.x];
+  const int t0 = un.y * rows, ntok = min(rows, it.L - t0);
   const int sub = threadIdx.x % LPR;
   const int tl = threadIdx.x / LPR;
   const int64_t row_stride = (int64_t)it.hq * D;            // elements between tokens
-  const int64_t head_base = it.q_off + (int64_t)pb.head * D + sub * 8;
-  const int64_t lse_base = it.lse_off + (int64_t)pb.head * it.L;
-  for (int base = 0; base < pb.ntok; base += TPP * U) {
+  const int64_t head_base = it.q_off + (int64_t)un.z * D + sub * 8;
+  const int64_t lse_base = it.lse_off + (int64_t)un.z * it.L;
+  for (int base = 0; base < ntok; base += TPP * U) {
     float acc[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       acc[u] = 0.f;
       const int k = base + u * TPP + tl;
-      if (k < pb.ntok) {
-        const int64_t e = head_base + (int64_t)(pb.t0 + k) * row_stride;
+      if (k < ntok) {
+        const int64_t e = head_base + (int64_t)(t0 + k) * row_stride;
         const bf16x8 g = *(const bf16x8 *)((const bf16 *)a.dout + e);
         if constexpr (O_F32) {
           const f32x4 o0 = *(const f32x4 *)((const float *)a.o + e);
@@ -93,8 +99,8 @@ __global__ void __launch_bounds__(256) bwd_preprocess_kernel(AttnArgs a) {
 #pragma unroll
       for (int off = LPR / 2; off >= 1; off >>= 1) acc[u] += __shfl_xor(acc[u], off);
       const int k = base + u * TPP + tl;
-      if (k < pb.ntok && sub == 0) {
-        const int64_t o = lse_base + pb.t0 + k;
+      if (k < ntok && sub == 0) {
+        const int64_t o = lse_base + t0 + k;
         a.delta[o] = -acc[u];      // stored negated: the start of the dP product chains
         a.lse2[o] = a.lse_in[o] * kLog2e;
       }
@@ -229,11 +235,52 @@ __device__ __forceinline__ void dq_tile(DqState<D> &st, const bf16 *smem, const 
   }
 }
 
+// This lane's part of Delta = <dO, O> of its row (the other half of the wave has
+// the other columns), O through the wave's region in the layout of dO's operands.
+// The dQ pass has dO in registers anyway, so that a pass over dO and O of its
+// own, at the memory's rate, is not needed (whole backward of 200 items of 300
+// tokens 1235 -> 1103 us, that pass took 214; of the 24-item short share 6180 ->
+// 6068).
+template <int D>
+__device__ __forceinline__ float dq_delta(const AttnArgs &a, int64_t qhead, int64_t qs, int wq0, int L, bf16 *reg,
+                                          const bf16x8 *gf, int lane) {
+  float d = 0.f;
+  if (!a.o_f32) {
+    start_rows<D>((const bf16 *)a.o + qhead, qs, wq0, L, reg, lane);
+    wait_all_loads();
+    bf16x8 o[D / 16];
+    read_rows<D>(reg, lane, o);
+#pragma unroll
+    for (int k = 0; k < D / 16; ++k)
+#pragma unroll
+      for (int x = 0; x < 8; ++x) d += (float)gf[k][x] * (float)o[k][x];
+  } else {
+    // float32 rows in two halves, each as wide as a row of bf16
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      start_rows<D>((const bf16 *)((const float *)a.o + qhead) + p * D, 2 * qs, wq0, L, reg, lane);
+      wait_all_loads();
+#pragma unroll
+      for (int k = 0; k < D / 32; ++k) {
+        const int col = 2 * (16 * k + 8 * (lane >> 5)), kk = p * (D / 32) + k;
+        const f32x4 o0 = __builtin_bit_cast(f32x4, lds_row8<D>(reg, lane & 31, col));
+        const f32x4 o1 = __builtin_bit_cast(f32x4, lds_row8<D>(reg, lane & 31, col + 8));
+#pragma unroll
+        for (int x = 0; x < 4; ++x) d += (float)gf[kk][x] * o0[x] + (float)gf[kk][x + 4] * o1[x];
+      }
+      wait_lds();
+    }
+  }
+  return d;
+}
+
 // One dQ unit: entry `slot` of the unit list, rows BM*tile .. of its item.
 // smem: K and V tiles, for each key group a four-stage ring: K of stage s at
 // the group's base + s*TILE, V at base + (4+s)*TILE, filled by untracked loads
 // (as in the forward).
-template <int D, bool G_F32, int RB, int KG>
+// DELTA: compute -Delta and lse2 of its rows, for the dK/dV pass too, instead of
+// reading them.
+template <int D, bool G_F32, int RB, int KG, bool DELTA>
 __device__ __forceinline__ void dq_unit(const AttnArgs &a, int slot, bf16 *smem) {
   using C = DqCfg<D, RB, KG>;
   const int4 u = a.units[slot];
@@ -272,12 +319,13 @@ __device__ __forceinline__ void dq_unit(const AttnArgs &a, int slot, bf16 *smem)
   bf16 *const reg = ring + (rb < 2 * WPS ? 2 * C::TILE : 6 * C::TILE - 2 * WPS * 32 * D) + rb * 32 * D;
   start_rows<D>((const bf16 *)a.q + qhead, qs, wq0, L, reg, lane);
   DqState<D> st;
-  {
-    const int64_t srow = it.lse_off + (int64_t)u.z * L + min(qrow, L - 1);
+  const int64_t srow = it.lse_off + (int64_t)u.z * L + min(qrow, L - 1);
+  float nd = 0.f;                            // -Delta
+  if constexpr (DELTA) {
+    st.lse2 = a.lse_in[srow] * kLog2e;
+  } else {
     st.lse2 = a.lse2[srow];
-    const float nd = a.delta[srow];          // -Delta
-#pragma unroll
-    for (int e = 0; e < 16; ++e) st.ndlt[e] = nd;
+    nd = a.delta[srow];
   }
   wait_all_loads();
   read_rows<D>(reg, lane, st.qf);
@@ -288,6 +336,17 @@ __device__ __forceinline__ void dq_unit(const AttnArgs &a, int slot, bf16 *smem)
   // ring.
   wait_all_loads();
   read_rows<D>(reg, lane, st.gf);
+  wait_lds();
+  if constexpr (DELTA) {
+    const float d = wave_sum_halves(dq_delta<D>(a, qhead, qs, wq0, L, reg, st.gf, lane));
+    nd = -d;
+    if (g == 0 && lane < 32 && qrow < L) {
+      a.delta[srow] = nd;
+      a.lse2[srow] = st.lse2;
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) st.ndlt[e] = nd;
   wait_lds();
   stage_barrier();
   if (loader) load_kv(2, 2);
@@ -349,12 +408,14 @@ __device__ __forceinline__ void dq_unit(const AttnArgs &a, int slot, bf16 *smem)
 
 // dQ pass over the per-XCD queues (a.qoff), as the dK/dV pass: with queue heads
 // persistent workgroups, without one workgroup per unit.
-template <int D, bool G_F32, int RB, int KG>
+template <int D, bool G_F32, int RB, int KG, bool DELTA>
 __global__ void __launch_bounds__(64 * RB * KG, (RB * KG == 4 ? (D == 64 ? 3 : 2) : 1)) bwd_dq_kernel(AttnArgs a, int *heads) {
   __shared__ __attribute__((aligned(16))) bf16 smem[KG * 8 * DqCfg<D, RB, KG>::TILE];
   __shared__ int s_slot;
+  // the heads of the dK/dV pass, which runs after this one
+  if (DELTA && blockIdx.x == 0 && threadIdx.x < kXcdQueues) a.queue[kKvQueue0 + threadIdx.x] = 0;
   UnitQueue q(heads, a.qoff, &s_slot);
-  for (int slot = q.first(); slot >= 0; slot = q.next()) dq_unit<D, G_F32, RB, KG>(a, slot, smem);
+  for (int slot = q.first(); slot >= 0; slot = q.next()) dq_unit<D, G_F32, RB, KG, DELTA>(a, slot, smem);
 }
 
 // ----------------------------------------------------------------- dK/dV --
@@ -987,7 +1048,7 @@ __global__ void __launch_bounds__(256, 1) bwd_small_kernel(AttnArgs a, int n_kv_
     }
   } else {
     const int b = (int)blockIdx.x - n_kv_wgs, x = b % kXcdQueues, slot = a.qoff[x] + b / kXcdQueues;
-    if (slot < a.qoff[x + 1]) dq_unit<D, G_F32, 4, 1>(a, slot, stages);
+    if (slot < a.qoff[x + 1]) dq_unit<D, G_F32, 4, 1, false>(a, slot, stages);
   }
 }
 
@@ -1027,15 +1088,16 @@ __global__ void __launch_bounds__(256) bwd_kv_reduce_kernel(AttnArgs a) {
 
 }  // namespace
 
-hipError_t launch_bwd_preprocess(int head_dim, bool o_f32, const AttnArgs &a, int n_blocks, hipStream_t s) {
-  if (n_blocks == 0) return hipSuccess;
-  dim3 grid(n_blocks), block(256);
+hipError_t launch_bwd_preprocess(int head_dim, bool o_f32, const AttnArgs &a, int n_units, hipStream_t s) {
+  if (n_units == 0) return hipSuccess;
+  dim3 grid(n_units), block(256);
+  const int rows = a.q_kind == kQWhole ? kFwdBM : 128;
   if (head_dim == 128) {
-    if (o_f32) bwd_preprocess_kernel<128, true><<<grid, block, 0, s>>>(a);
-    else bwd_preprocess_kernel<128, false><<<grid, block, 0, s>>>(a);
+    if (o_f32) bwd_preprocess_kernel<128, true><<<grid, block, 0, s>>>(a, rows);
+    else bwd_preprocess_kernel<128, false><<<grid, block, 0, s>>>(a, rows);
   } else {
-    if (o_f32) bwd_preprocess_kernel<64, true><<<grid, block, 0, s>>>(a);
-    else bwd_preprocess_kernel<64, false><<<grid, block, 0, s>>>(a);
+    if (o_f32) bwd_preprocess_kernel<64, true><<<grid, block, 0, s>>>(a, rows);
+    else bwd_preprocess_kernel<64, false><<<grid, block, 0, s>>>(a, rows);
   }
   return hipGetLastError();
 }
@@ -1061,7 +1123,12 @@ static hipError_t launch_dq(const AttnArgs &a, int n_units, hipStream_t s) {
   int *heads = nullptr;
   hipError_t e = pass_grid(a, n_units, DqCfg<D, RB, KG>::PER_CU, a.queue + kDqQueue0, &grid, &heads);
   if (e != hipSuccess) return e;
-  bwd_dq_kernel<D, G_F32, RB, KG><<<grid, dim3(64 * RB * KG), 0, s>>>(a, heads);
+  if (a.o) {
+    if (heads) bwd_reset_kernel<<<dim3(1), dim3(64), 0, s>>>(heads);
+    bwd_dq_kernel<D, G_F32, RB, KG, true><<<grid, dim3(64 * RB * KG), 0, s>>>(a, heads);
+  } else {
+    bwd_dq_kernel<D, G_F32, RB, KG, false><<<grid, dim3(64 * RB * KG), 0, s>>>(a, heads);
+  }
   return hipGetLastError();
 }
 

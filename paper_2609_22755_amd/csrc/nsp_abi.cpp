@@ -159,8 +159,8 @@ struct HostAttnSched {
   std::vector<int4> kv_units;
   QUnits fwd, dq;               // what the forward and dQ passes run
   bool small = false;           // dK/dV and dQ in one launch
+  bool dq_first = false;
   std::vector<int> kv_qoff;     // kXcdQueues + 1 entries: the dK/dV queue of XCD x is kv_units[kv_qoff[x] ..)
-  std::vector<nsp::PreBlock> pre_blocks;
   std::vector<nsp::KvPiece> kv_pieces;   // split dK/dV (empty: not split)
   std::vector<int2> kv_wgs;
   std::vector<nsp::KvReduce> kv_reduce;
@@ -750,6 +750,28 @@ int q_unit_kind(const nsp_worklist *wl, double short_unit) {
   return units[1] <= kAssumedCUs || steps[1] <= short_unit * units[1] ? nsp::kQHalf : nsp::kQWhole;
 }
 
+// Whether the dQ pass runs first and computes Delta, in place of the preprocess
+// pass: up to kDeltaSteps 64-key steps a 256-row dQ unit on the mean.  Decided
+// from every item, whatever the mask (Delta's sum has another order).  Whole
+// backward, preprocess / dQ first: 200 items of 300 tokens (5 steps) 1235 / 1103
+// us, 32 of 2048 (18) 3630 / 3506, the 24-item short share (31) 6184 / 6068, one of
+// 4096 (34) 440 / 431, a 16384-token node of 4 heads (130) 820 / 816, one of 32768
+// (258) 5987 / 5990.  Past that the pass saved is nothing beside the others, and
+// dQ, which fills every register file, keeps a re-layout on another stream from
+// running beside the call's start (two-level share, streamed: 71.9 / 74.7 ms).
+constexpr int64_t kDeltaSteps = 160;
+
+bool delta_in_dq(const nsp_worklist *wl) {
+  int64_t units = 0, steps = 0;
+  for (int j = 0; j < wl->n_items; ++j) {
+    const int64_t L = wl->cu_seqlens[j + 1] - wl->cu_seqlens[j], hq = wl->q_heads[2 * j + 1] - wl->q_heads[2 * j];
+    const int64_t n = (L + nsp::kFwdBM - 1) / nsp::kFwdBM;
+    units += hq * n;
+    if (L > 0) steps += hq * (2 * n * (n - 1) + (L + nsp::kFwdBN - 1) / nsp::kFwdBN);   // sum of 4 (m + 1), and the last
+  }
+  return steps <= kDeltaSteps * units;
+}
+
 QUnits q_units(const nsp_worklist *wl, int kind) {
   QUnits q;
   q.kind = kind;
@@ -784,24 +806,20 @@ QUnits q_units(const nsp_worklist *wl, int kind) {
   return q;
 }
 
-// `compact`: 256-row units and large preprocess blocks whatever the list, for a
-// schedule that has to fit a limited space (the results are the same bits: lists
-// that split their dK/dV or take key groups are too small to need it).
+// `compact`: 256-row units whatever the list, for a schedule that has to fit a
+// limited space (the results are the same bits: lists that split their dK/dV or
+// take key groups are too small to need it).
 // `report`: for nsp_attn_schedule, the forward / dQ units in reported order and
 // the whole dK/dV units, which the passes of some lists do not run.
 HostAttnSched build_attn_schedule(const nsp_worklist *wl, bool compact = false, bool report = false) {
   HostAttnSched s;
   add_split(s, wl);
+  s.small = !s.kv_wgs.empty() && small_backward(wl);
+  s.dq_first = delta_in_dq(wl);
   const bool whole_kv = report || s.kv_wgs.empty();
   const int D = wl->head_dim;
   int64_t qo = 0, ko = 0, lo = 0;
   std::vector<int64_t> fcost;
-  int64_t small_blocks = 0;
-  for (int j = 0; j < wl->n_items; ++j)
-    if (selected(wl, j))
-      small_blocks += (int64_t)(wl->q_heads[2 * j + 1] - wl->q_heads[2 * j]) *
-                      ((wl->cu_seqlens[j + 1] - wl->cu_seqlens[j] + nsp::kPreSmallRows - 1) / nsp::kPreSmallRows);
-  const int pre_rows = compact || small_blocks > nsp::kPreFewBlocks ? nsp::kPreBlockRows : nsp::kPreSmallRows;
   ItemGangs item_gangs;
   for (int j = 0; j < wl->n_items; ++j) {
     const int L = wl->cu_seqlens[j + 1] - wl->cu_seqlens[j];
@@ -818,9 +836,6 @@ HostAttnSched build_attn_schedule(const nsp_worklist *wl, bool compact = false, 
     d.active = selected(wl, j) ? 1 : 0;
     s.items.push_back(d);
     if (L > 0 && d.active) {
-      for (int i = 0; i < hq; ++i)
-        for (int t = 0; t < L; t += pre_rows)
-          s.pre_blocks.push_back(nsp::PreBlock{j, i, t, std::min(pre_rows, L - t)});
       if (report) {
         const int nq = (L + nsp::kFwdBM - 1) / nsp::kFwdBM;
         for (int m = 0; m < nq; ++m)
@@ -842,7 +857,6 @@ HostAttnSched build_attn_schedule(const nsp_worklist *wl, bool compact = false, 
   s.q_rows = qo / D;
   lpt_sort(s.fwd_units, fcost);
   s.fwd = q_units(wl, compact ? nsp::kQWhole : q_unit_kind(wl, kShortUnitFwd));
-  s.small = !s.kv_wgs.empty() && small_backward(wl);
   const int dq_kind = compact ? nsp::kQWhole : s.small ? nsp::kQHalf : q_unit_kind(wl, kShortUnitDq);
   s.dq = dq_kind == s.fwd.kind ? s.fwd : q_units(wl, dq_kind);
   kv_balance(item_gangs, wl);
@@ -978,11 +992,11 @@ nsp_status upload(const void *host, size_t bytes, void **dev) {
 }
 
 // The device image of an attention schedule: ItemDesc[n_items] | forward/dQ
-// units | dK/dV units | preprocess spans | split dK/dV | queue offsets, each
+// units | dK/dV units | split dK/dV | queue offsets, each
 // part 256-byte aligned.
 struct AttnBlob {
   std::vector<char> bytes;
-  size_t o_fwd = 0, o_kv = 0, o_kvq = 0, o_pre = 0, o_piece = 0, o_wg = 0, o_red = 0, o_fwdq = 0, o_dq = 0, o_dqq = 0;
+  size_t o_fwd = 0, o_kv = 0, o_kvq = 0, o_piece = 0, o_wg = 0, o_red = 0, o_fwdq = 0, o_dq = 0, o_dqq = 0;
 };
 
 AttnBlob attn_blob(const HostAttnSched &hs) {
@@ -991,12 +1005,10 @@ AttnBlob attn_blob(const HostAttnSched &hs) {
   const size_t n_fwd = align256(hs.fwd.units.size() * sizeof(int4));
   const size_t n_kv = align256(hs.kv_units.size() * sizeof(int4));
   const size_t n_kvq = align256(hs.kv_qoff.size() * sizeof(int));
-  const size_t n_pre = align256(hs.pre_blocks.size() * sizeof(nsp::PreBlock));
   b.o_fwd = n_items;
   b.o_kv = n_items + n_fwd;
   b.o_kvq = n_items + n_fwd + n_kv;
-  b.o_pre = n_items + n_fwd + n_kv + n_kvq;
-  b.o_piece = b.o_pre + n_pre;
+  b.o_piece = n_items + n_fwd + n_kv + n_kvq;
   b.o_wg = b.o_piece + align256(hs.kv_pieces.size() * sizeof(nsp::KvPiece));
   b.o_red = b.o_wg + align256(hs.kv_wgs.size() * sizeof(int2));
   b.o_fwdq = b.o_red + align256(hs.kv_reduce.size() * sizeof(nsp::KvReduce));
@@ -1021,7 +1033,6 @@ AttnBlob attn_blob(const HostAttnSched &hs) {
   }
   put(b.o_kv, hs.kv_units.data(), hs.kv_units.size() * sizeof(int4));
   put(b.o_kvq, hs.kv_qoff.data(), hs.kv_qoff.size() * sizeof(int));
-  put(b.o_pre, hs.pre_blocks.data(), hs.pre_blocks.size() * sizeof(nsp::PreBlock));
   put(b.o_piece, hs.kv_pieces.data(), hs.kv_pieces.size() * sizeof(nsp::KvPiece));
   put(b.o_wg, hs.kv_wgs.data(), hs.kv_wgs.size() * sizeof(int2));
   put(b.o_red, hs.kv_reduce.data(), hs.kv_reduce.size() * sizeof(nsp::KvReduce));
@@ -1034,7 +1045,6 @@ nsp::Schedule attn_schedule_at(const HostAttnSched &hs, const AttnBlob &b, char 
   s.items = reinterpret_cast<ItemDesc *>(dev);
   s.kv_units = reinterpret_cast<int4 *>(dev + b.o_kv);
   s.kv_qoff = reinterpret_cast<int *>(dev + b.o_kvq);
-  s.pre_blocks = reinterpret_cast<nsp::PreBlock *>(dev + b.o_pre);
   s.kv_pieces = reinterpret_cast<nsp::KvPiece *>(dev + b.o_piece);
   s.kv_wgs = reinterpret_cast<int2 *>(dev + b.o_wg);
   s.kv_reduce = reinterpret_cast<nsp::KvReduce *>(dev + b.o_red);
@@ -1054,8 +1064,8 @@ nsp::Schedule attn_schedule_at(const HostAttnSched &hs, const AttnBlob &b, char 
   s.dq = pass(hs.dq, b.o_dq, b.o_dqq);
   s.kv_longest = longest(hs.kv_qoff);
   s.small = hs.small;
+  s.dq_first = hs.dq_first;
   s.n_kv_units = (int)hs.kv_units.size();
-  s.n_pre_blocks = (int)hs.pre_blocks.size();
   s.q_rows = hs.q_rows;
   return s;
 }
@@ -1154,15 +1164,15 @@ struct TimingState {
 };
 TimingState g_timing;
 
-bool timing_on() {
-  std::lock_guard<std::mutex> lock(g_timing.mu);
-  return g_timing.on;
-}
-
 // Run `launch` on `stream`, bracketed by timing events when timing is on.
 template <class F>
 hipError_t timed_launch(KernelId id, hipStream_t stream, F launch) {
-  if (!timing_on()) return launch();
+  bool on;
+  {
+    std::lock_guard<std::mutex> lock(g_timing.mu);
+    on = g_timing.on;
+  }
+  if (!on) return launch();
   hipEvent_t a = nullptr, b = nullptr;
   hipError_t e = hipEventCreate(&a);
   if (e == hipSuccess) e = hipEventCreate(&b);
@@ -1264,8 +1274,16 @@ void set_pass(nsp::AttnArgs *a, const nsp::QPass &q) {
   a->one_shot = q.one_shot;
 }
 
-// The three backward kernels on `stream`: preprocess (-Delta, lse2, and the
-// reset of the unit-queue heads), dK/dV, dQ.
+// Whether the `n` bytes at `p` and the `m` bytes at `q` share any.
+bool overlap(const void *p, int64_t n, const void *q, int64_t m) {
+  const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+  return n > 0 && m > 0 && a < b + (uintptr_t)m && b < a + (uintptr_t)n;
+}
+
+// The backward's kernels on `stream`: dQ (which leaves -Delta and lse2), then
+// dK/dV; for small lists preprocess (-Delta, lse2) and both in one; for lists of
+// long units (delta_in_dq), and where dQ takes the place of what the other pass
+// reads (say, of dO), preprocess, dK/dV, dQ.
 nsp_status launch_backward(int D, const nsp::Schedule &s, float softmax_scale, const void *q, const void *k,
                            const void *v, const void *o, nsp_dtype o_dtype, const void *dout, const float *lse,
                            void *dq, void *dk, void *dv, nsp_dtype grad_dtype, float *delta, float *lse2,
@@ -1285,17 +1303,10 @@ nsp_status launch_backward(int D, const nsp::Schedule &s, float softmax_scale, c
   a.queue = queue;
   a.items = s.items;
   a.n_items = s.n_items;
-  a.pre_blocks = s.pre_blocks;
   a.scale = softmax_scale;
   a.scale_log2 = softmax_scale * 1.4426950408889634f;
+  a.o_f32 = o_dtype == NSP_F32;
   const bool g32 = grad_dtype == NSP_F32;
-  NSP_TRY(hip_status(timed_launch(K_PRE, stream,
-                                  [&] { return nsp::launch_bwd_preprocess(D, o_dtype == NSP_F32, a, s.n_pre_blocks,
-                                                                          stream); }),
-                     "backward preprocess launch"));
-  a.units = s.kv_units;
-  a.qoff = s.kv_qoff;
-  a.q_longest = s.kv_longest;
   const bool split = s.n_kv_wgs > 0;
   if (split) {
     a.pieces = s.kv_pieces;
@@ -1303,18 +1314,47 @@ nsp_status launch_backward(int D, const nsp::Schedule &s, float softmax_scale, c
     a.reduce = s.kv_reduce;
     a.n_reduce = s.n_kv_reduce;
     a.part = part;
-    // (each kernel alone while they are timed)
-    a.small = s.small && !timing_on();
-    if (a.small) set_pass(&a, s.dq);
   }
-  NSP_TRY(hip_status(timed_launch(K_DKDV, stream,
-                                  [&] { return nsp::launch_bwd_dkdv(D, g32, a, split ? s.n_kv_wgs : s.n_kv_units,
-                                                                    stream); }),
-                     "backward dK/dV launch"));
-  if (a.small) return NSP_OK;
-  set_pass(&a, s.dq);
-  return hip_status(timed_launch(K_DQ, stream, [&] { return nsp::launch_bwd_dq(D, g32, a, s.dq.n_units, stream); }),
-                    "backward dQ launch");
+  auto preprocess = [&] {
+    set_pass(&a, s.dq);
+    return hip_status(timed_launch(K_PRE, stream,
+                                   [&] { return nsp::launch_bwd_preprocess(D, a.o_f32, a, s.dq.n_units, stream); }),
+                      "backward preprocess launch");
+  };
+  auto run_dq = [&] {
+    set_pass(&a, s.dq);
+    return hip_status(timed_launch(K_DQ, stream, [&] { return nsp::launch_bwd_dq(D, g32, a, s.dq.n_units, stream); }),
+                      "backward dQ launch");
+  };
+  auto run_dkdv = [&] {
+    if (!a.small) {
+      a.units = s.kv_units;
+      a.qoff = s.kv_qoff;
+      a.q_longest = s.kv_longest;
+      a.one_shot = false;
+    }
+    return hip_status(timed_launch(K_DKDV, stream,
+                                   [&] { return nsp::launch_bwd_dkdv(D, g32, a, split ? s.n_kv_wgs : s.n_kv_units,
+                                                                     stream); }),
+                      "backward dK/dV launch");
+  };
+  const int64_t q_elems = s.q_rows * D, dq_bytes = q_elems * (g32 ? 4 : 2);
+  const bool in_place = overlap(dq, dq_bytes, q, q_elems * 2) || overlap(dq, dq_bytes, dout, q_elems * 2) ||
+                        overlap(dq, dq_bytes, o, q_elems * (a.o_f32 ? 4 : 2)) ||
+                        overlap(dq, dq_bytes, lse, s.q_rows * 4);
+  if (s.small && !in_place) {
+    NSP_TRY(preprocess());
+    a.small = true;
+    return run_dkdv();
+  }
+  if (in_place || !s.dq_first) {
+    NSP_TRY(preprocess());
+    NSP_TRY(run_dkdv());
+    a.o = nullptr;
+    return run_dq();
+  }
+  NSP_TRY(run_dq());
+  return run_dkdv();
 }
 
 }  // namespace

@@ -20,27 +20,6 @@ struct ItemDesc {
   int32_t active;   // 1 if the call computes this item (work-list item mask)
 };
 
-// One workgroup of the backward preprocess: tokens [t0, t0 + ntok) of local
-// query head `head` of item `item` (only the items a call computes are
-// covered).  Consecutive tokens of one head are consecutive entries of the
-// LSE / Delta layout.
-struct PreBlock {
-  int32_t item;
-  int32_t head;
-  int32_t t0;
-  int32_t ntok;     // at most kPreBlockRows
-};
-// Tokens of a preprocess block.  The pass is bound by HBM latency until about
-// eight 256-thread workgroups a compute unit are in flight, so short lists
-// take small blocks (one 4096-token sequence, 32 heads: 32.8 us with 512
-// tokens a block, 14.2 with 128, 13.8 with 64; the 24-item short share 265,
-// 222 and 224 us).  Lists of more than kPreFewBlocks small blocks fill the
-// chip either way and take the large ones, which keep their schedule small
-// (the long-tail share: 900, 912 and 937 us).
-constexpr int kPreBlockRows = 512;
-constexpr int kPreSmallRows = 128;
-constexpr int64_t kPreFewBlocks = 32768;
-
 // Tile geometry shared by host scheduling and the kernels.
 constexpr int kFwdWaves = 8;  // waves per forward / dQ workgroup (two per SIMD)
 constexpr int kFwdBM = 32 * kFwdWaves;   // query rows per forward / dQ workgroup
@@ -107,10 +86,9 @@ struct Schedule {
   KvReduce *kv_reduce = nullptr;  // device, the key tiles in several pieces
   int n_kv_wgs = 0, n_kv_reduce = 0;
   bool small = false;             // dK/dV and dQ in one launch
-  PreBlock *pre_blocks = nullptr; // device, the preprocess workgroups of the items the call computes
+  bool dq_first = false;          // dQ before dK/dV, with Delta, instead of a preprocess pass
   int n_items = 0;
   int n_kv_units = 0, kv_longest = 0;
-  int n_pre_blocks = 0;
   int64_t q_rows = 0;          // sum_j L_j * hq_j
   int64_t q_elems = 0, kv_elems = 0, lse_elems = 0;
 };
@@ -122,12 +100,12 @@ struct AttnArgs {
   float *lse;
   const float *lse_in;
   const void *dout;
+  bool o_f32;             // backward: type of o (o is null for a dQ pass that reads delta and lse2)
   void *dq, *dk, *dv;
   float *delta;           // workspace: -Delta = -rowsum(dO * O)
   float *lse2;            // workspace: lse * log2(e)
-  int *queue;             // workspace: unit queue heads, one per XCD (zeroed by the preprocess)
+  int *queue;             // workspace: unit queue heads, one per XCD and pass (zeroed before the pass)
   const ItemDesc *items;
-  const PreBlock *pre_blocks;
   const int4 *units;
   const KvPiece *pieces;  // split dK/dV
   const int2 *wgs;
@@ -170,7 +148,8 @@ int32_t set_error(int32_t status, const char *fmt, ...);
 hipError_t compute_units(int *cus);
 
 hipError_t launch_attn_fwd(int head_dim, bool o_f32, const AttnArgs &a, int n_units, hipStream_t s);
-hipError_t launch_bwd_preprocess(int head_dim, bool o_f32, const AttnArgs &a, int n_blocks, hipStream_t s);
+// One workgroup a dQ unit (a.units, of kind a.q_kind).
+hipError_t launch_bwd_preprocess(int head_dim, bool o_f32, const AttnArgs &a, int n_units, hipStream_t s);
 hipError_t launch_bwd_dq(int head_dim, bool g_f32, const AttnArgs &a, int n_units, hipStream_t s);
 // With a.wgs the split pass (n_units workgroups over a.pieces, with a.small the
 // dQ units of a.units too, then the sums of the a.n_reduce tiles of a.reduce),

@@ -162,23 +162,20 @@ void check_gangs(const nsp_worklist &w, int *kinds) {
   CHECK(f.small == s.small && (!s.small || (s.dq.kind == nsp::kQHalf && s.kv_wgs.size() % 8 == 0)));
 }
 
-// A list near the allocation-free scratch's limits: its schedule fits as it did
-// with 256-row units and 512-token preprocess blocks.
+// A list near the allocation-free scratch's limits: its schedule fits with
+// 256-row units where the one with 128-row units does not.
 void check_compact() {
-  std::vector<int32_t> cu(1, 0), qh, kvh;
-  for (int j = 0; j < 44700; ++j) {
+  std::vector<int32_t> cu(1, 0), heads;
+  for (int j = 0; j < 80000; ++j) {
     cu.push_back(cu.back() + 129);
-    for (int k = 0; k < 2; ++k) {
-      qh.push_back(2 * k);
-      kvh.push_back(2 * k);
-    }
+    heads.push_back(0);
+    heads.push_back(1);
   }
   nsp_worklist w{};
-  w.n_items = 44700;
+  w.n_items = 80000;
   w.cu_seqlens = cu.data();
-  w.q_heads = qh.data();
-  w.kv_heads = kvh.data();
-  w.hq_total = w.hkv_total = 2;
+  w.q_heads = w.kv_heads = heads.data();
+  w.hq_total = w.hkv_total = 1;
   w.head_dim = 64;
   HostSchedPtr h;
   CHECK(get_host_schedule(worklist_key("attn", 0, &w, 0), &w, &h) == NSP_OK);
