@@ -544,10 +544,15 @@ struct KvSplit {
 // kSplitGain: the steps that the split has to gain beside a sixteenth of the
 // pass, for the sum pass; at 12 steps' gain (20 items of 300 tokens) the
 // backward takes 167 us against 176, at none (4 items of 4000) 1616 against
-// 1614.  Lists of more than kMaxSplitTiles key tiles, four
-// a compute unit, leave longest-first order little to gain.
+// 1614.
+// kMaxSplitTiles, two key tiles a compute unit: past that the queues, which even
+// out XCDs that run a few percent apart and read each query tile once for a gang,
+// make up for what whole tiles leave idle.  dK/dV of one head-sharded sequence of
+// 4 / 1 heads, whole / shares: 384 tiles 4969 / 4113 us, 448 5975 / 5577, 478 6459 /
+// 6361, 552 8924 / 9849 (8864 / 8837 on another card), 594 10368 / 9874, 704 13500 /
+// 13956, 768 15962 / 16565; one of 32 / 4 heads, 640 tiles 5772 / 5912.
 constexpr int64_t kPieceCost = 12, kMinPiece = 4, kSplitGain = 4;
-constexpr size_t kMaxSplitTiles = 1024;
+constexpr size_t kMaxSplitTiles = 2 * kAssumedCUs;
 
 // Key tiles of one local KV head of an item, longest first: their query heads
 // (first | end << 16) and steps a query tile.
