@@ -170,7 +170,9 @@ nsp_status nsp_varlen_attn_bwd(const nsp_worklist *wl, float softmax_scale, int3
  * Allocation-free variant of nsp_varlen_attn_bwd, for callers that cannot
  * allocate device memory: code being captured into a HIP graph, tight
  * serving loops, harnesses that forbid allocation.  Same arguments, results
- * (bit for bit) and errors as nsp_varlen_attn_bwd, without the workspace:
+ * (bit for bit; of a list of some 170000 items, all but a few of them empty, up
+ * to the order of float32 sums: its schedule fits in a shorter form only) and
+ * errors as nsp_varlen_attn_bwd, without the workspace:
  * the backward workspace and the work list's unit schedule live in a
  * file-scope device array of NSP_NOALLOC_SCRATCH_BYTES that the library
  * holds on every GPU it runs on until the process ends; the call allocates

@@ -811,14 +811,16 @@ QUnits q_units(const nsp_worklist *wl, int kind) {
   return q;
 }
 
-// `compact`: 256-row units whatever the list, for a schedule that has to fit a
-// limited space (the results are the same bits: lists that split their dK/dV or
-// take key groups are too small to need it).
+// `compact`: 256-row units and whole dK/dV tiles whatever the list, each pass in
+// a launch of its own: the shortest schedule, for one that has to fit a limited
+// space.  The results are the same bits but for lists that would split their dK/dV
+// or take key groups (whose other items, some 170000, are empty ones): there
+// float32 sums take another order.
 // `report`: for nsp_attn_schedule, the forward / dQ units in reported order and
 // the whole dK/dV units, which the passes of some lists do not run.
 HostAttnSched build_attn_schedule(const nsp_worklist *wl, bool compact = false, bool report = false) {
   HostAttnSched s;
-  add_split(s, wl);
+  if (!compact) add_split(s, wl);
   s.small = !s.kv_wgs.empty() && small_backward(wl);
   s.dq_first = delta_in_dq(wl);
   const bool whole_kv = report || s.kv_wgs.empty();
@@ -1239,12 +1241,22 @@ nsp::LruCache<HostSched> &host_schedule_cache() {
   return *c;
 }
 
+// Compact where the schedule of the call does not fit the scratch, or, for a list
+// whose results that changes, where the unmasked call's does not: a masked call
+// gives its bits.
 nsp_status get_host_schedule(const std::string &key, const nsp_worklist *wl, HostSchedPtr *out) {
   return host_schedule_cache().get(key, out, [&](HostSchedPtr *made) {
     auto h = std::make_shared<HostSched>();
     h->hs = build_attn_schedule(wl);
     h->blob = attn_blob(h->hs);
-    if (h->blob.bytes.size() > nsp::kScratchSchedBytes) {
+    bool compact = h->blob.bytes.size() > nsp::kScratchSchedBytes;
+    if (!compact && wl->item_mask &&
+        (h->hs.dq.kind == nsp::kQKeys || !h->hs.kv_wgs.empty())) {
+      nsp_worklist all = *wl;
+      all.item_mask = nullptr;
+      compact = attn_blob(build_attn_schedule(&all)).bytes.size() > nsp::kScratchSchedBytes;
+    }
+    if (compact) {
       h->hs = build_attn_schedule(wl, true);
       h->blob = attn_blob(h->hs);
     }

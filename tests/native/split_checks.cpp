@@ -121,6 +121,12 @@ void check_list(const nsp_worklist &w, const std::vector<uint8_t> &mask, int *n_
   }
 }
 
+// What a schedule's passes assume of each other.
+void check_passes(const HostAttnSched &s) {
+  CHECK(!s.small || (s.dq.kind == nsp::kQHalf && !s.kv_wgs.empty()));
+  CHECK(s.kv_wgs.empty() || s.kv_units.empty());
+}
+
 void check_gangs(const nsp_worklist &w, int *kinds) {
   const HostAttnSched s = build_attn_schedule(&w, false, true);
   auto key = [](const int4 &u) { return std::make_tuple(u.x, u.y, u.z, u.w); };
@@ -156,15 +162,64 @@ void check_gangs(const nsp_worklist &w, int *kinds) {
   const HostAttnSched f = build_attn_schedule(&all, false, true);
   if (s.fwd_units.empty()) return;
   const HostAttnSched d = build_attn_schedule(&w);   // what the passes take
+  check_passes(d);
+  check_passes(build_attn_schedule(&w, true));
   CHECK(d.fwd.units.size() == s.fwd.units.size() && d.kv_units.size() == (d.kv_wgs.empty() ? s.kv_units.size() : 0));
   CHECK((f.fwd.kind == nsp::kQKeys) == (s.fwd.kind == nsp::kQKeys));
   CHECK((f.dq.kind == nsp::kQKeys) == (s.dq.kind == nsp::kQKeys));
   CHECK(f.small == s.small && (!s.small || (s.dq.kind == nsp::kQHalf && s.kv_wgs.size() % 8 == 0)));
 }
 
-// A list near the allocation-free scratch's limits: its schedule fits with
-// 256-row units where the one with 128-row units does not.
+// Lists near the allocation-free scratch's limits, whose schedules fit with
+// 256-row units where the ones with 128-row units do not: of many short items, and
+// of two items among empty ones, small enough for one launch (or for key groups).
+// Of those a masked call takes the compact schedule too, and the longest such list
+// that 256-row units alone allow (items, units and queues, 256 bytes for the
+// blocks of a preprocess pass of its own) still fits.
 void check_compact() {
+  struct { int L, hq, hkv; bool small; } lone[] = {{300, 8, 2, true}, {512, 32, 4, true}, {4096, 4, 1, false}};
+  for (auto &c : lone) {
+    const int most = 174762;                           // as many empty items as the scratch describes
+    std::vector<int32_t> cu(most + 1, c.L + 64), qh(2 * most), kvh(2 * most);
+    std::vector<uint8_t> second(most, 0);
+    cu[0] = 0;
+    cu[1] = c.L;
+    second[1] = 1;
+    for (int j = 0; j < most; ++j) {
+      qh[2 * j + 1] = c.hq;
+      kvh[2 * j + 1] = c.hkv;
+    }
+    nsp_worklist w{};
+    w.n_items = 2;
+    w.cu_seqlens = cu.data();
+    w.q_heads = qh.data();
+    w.kv_heads = kvh.data();
+    w.hq_total = c.hq;
+    w.hkv_total = c.hkv;
+    w.head_dim = 128;
+    auto items = [](int n) { return align256(n * sizeof(ItemDesc)); };
+    const size_t full = attn_blob(build_attn_schedule(&w)).bytes.size() - items(2);
+    const size_t least = align256((size_t)16 * c.hq * ((c.L + 255) / 256 + 1)) +
+                         align256((size_t)16 * c.hkv * ((c.L + 127) / 128 + 1)) + 2 * 256;
+    CHECK(least < full);
+    int lo = most, hi = most;                           // the first list whose full schedule is too long, the last that fits
+    while (items(lo - 1) + full > nsp::kScratchSchedBytes) --lo;
+    while (items(hi) + least > nsp::kScratchSchedBytes) --hi;
+    CHECK(lo <= hi);
+    for (int n : {lo - 1, lo, hi}) {
+      w.n_items = n;
+      HostSchedPtr h, m;
+      w.item_mask = nullptr;
+      CHECK(get_host_schedule(worklist_key("attn", 0, &w, 0), &w, &h) == NSP_OK);
+      w.item_mask = second.data();
+      CHECK(get_host_schedule(worklist_key("attn", 0, &w, 0), &w, &m) == NSP_OK);
+      for (const HostSched *x : {h.get(), m.get()}) {
+        check_passes(x->hs);
+        CHECK(x->blob.bytes.size() <= nsp::kScratchSchedBytes);
+        CHECK(x->hs.small == (n < lo && c.small) && (n < lo || x->hs.dq.kind == nsp::kQWhole));
+      }
+    }
+  }
   std::vector<int32_t> cu(1, 0), heads;
   for (int j = 0; j < 80000; ++j) {
     cu.push_back(cu.back() + 129);
