@@ -331,9 +331,21 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs &a, int slot, bf16 *smem
   st.l_part = 0.f;
   const float c = a.scale_log2;
 
+  f32x16 sa, sb;
+  // The second group starts from the maxima of the item's first 32 keys too, so
+  // that both scale P alike before its bf16 rounding and O is that of one group up
+  // to the order of its float32 sums (and a first block of -inf scores does not
+  // leave the group without a maximum).
+  if constexpr (KG == 2) {
+    if (g == 1 && halves > 1) {
+      sa = f32x16{};
+#pragma unroll
+      for (int k = 0; k < C::KS; ++k) sa = mfma32x32x16(lds_b128_at(smem, ad.k[k] - rbase), st.qf[k], sa);
+      fwd_update_max<D>(st, fwd_block_max(sa, c));
+    }
+  }
   // scores of the group's first 32 keys (g = 0: every wave with rows in the
   // item has keys there)
-  f32x16 sa, sb;
   if (halves > g) {
     sa = f32x16{};
 #pragma unroll
