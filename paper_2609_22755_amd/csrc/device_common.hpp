@@ -314,14 +314,22 @@ __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane
 __device__ __forceinline__ void wait_lds() { wait_loads_le<63>(); }
 
 // Per-XCD unit queues of a pass: queue x holds the units off[x] .. off[x+1]-1
-// of the unit list.  Workgroup b starts with entry b / 8 of queue b % 8 (it
-// starts on XCD b % 8).  Without heads that is all; with them (ints in device
-// memory, zero before the pass; the head of queue x counts the entries taken
-// after the first ones) a workgroup goes on until every queue is empty.  It
-// drains the queue of its own XCD first -- keeping the gangs of the order, and
-// their L2 reuse, on one XCD -- then takes what is left in the others: XCDs run
-// at different speeds, and a fixed unit-to-XCD map would leave the fast ones
-// idle at the end.
+// of the unit list.  Without heads workgroup b runs entry b / 8 of queue b % 8:
+// workgroups go to the XCDs in turn, so that a queue's units share one.  With
+// heads (ints in device memory, zero before the pass; entries taken) a workgroup
+// takes units until every queue is empty.  It drains the queue of its own XCD
+// first -- keeping the gangs of the order, and their L2 reuse, on one XCD -- then
+// takes what is left in the others: XCDs run at different speeds, and a fixed
+// unit-to-XCD map would leave the fast ones idle at the end.
+//
+// The first unit too comes from the queue of the XCD that the workgroup runs on,
+// not from queue b % 8: which XCD workgroup 0 goes to depends on the hardware
+// queue of the stream (XCD 7 on one stream of a process that uses two), and the
+// leading units of the gangs then ran on another XCD than the rest of them.  dK/dV
+// of one sequence of 4 / 1 heads (D = 128) on such a stream, entry b / 8 / fetched:
+// 513 key tiles 8648 / 7574 us, 594 11722 / 10098, 704 14658 / 13364; forward of
+// 594 4856 / 4746.  Where workgroup 0 is on XCD 0, 594 tiles: 10129 / 10117 and
+// 4737 / 4745 (the fetch).
 //
 // One wave fetches.  The atomics go to memory past the XCDs' L2, about 1 us
 // each, so the eight heads are read together to see which queue has units
@@ -346,8 +354,6 @@ struct UnitQueue {
   __device__ __forceinline__ UnitQueue(int *heads_, const int *off_, int *s_slot_)
       : heads(heads_), off(off_), s_slot(s_slot_), empty(0) {}
   __device__ __forceinline__ int count(int x) const { return off[x + 1] - off[x]; }
-  // entries of queue x that the workgroups start with
-  __device__ __forceinline__ int started(int x) const { return ((int)gridDim.x - x + kXcdQueues - 1) / kXcdQueues; }
 
   // The next unit of the own queue, or of the first one after it that is not
   // empty (-1: none).  By a whole wave: lane x looks at queue x.
@@ -358,22 +364,22 @@ struct UnitQueue {
       if (!(empty >> y & 1)) {
         int k = 0;
         if (lane == 0) k = atomicAdd(heads + y, 1);
-        k = started(y) + __builtin_amdgcn_readfirstlane(k);
+        k = __builtin_amdgcn_readfirstlane(k);
         if (k < count(y)) return off[y] + k;
         empty |= 1u << y;
       }
       const int x = lane & 7;
       const int h = __hip_atomic_load(heads + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const unsigned left = (unsigned)__ballot(started(x) + h < count(x)) & 0xffu & ~empty;
+      const unsigned left = (unsigned)__ballot(h < count(x)) & 0xffu & ~empty;
       if (left == 0) return -1;
       y = (own + __builtin_ctz((left | left << kXcdQueues) >> own)) % kXcdQueues;
     }
   }
   // The workgroup's first unit (-1: none).
   __device__ __forceinline__ int first() {
+    if (heads) return next();
     const int x = (int)blockIdx.x % kXcdQueues, i = (int)blockIdx.x / kXcdQueues;
-    if (i < count(x)) return off[x] + i;
-    return next();
+    return i < count(x) ? off[x] + i : -1;
   }
   // Its next unit (-1: none).  Also the barrier between a unit's last LDS
   // accesses and the next unit's first; stores to memory stay in flight across
