@@ -6,8 +6,9 @@
 // runs exactly the unmasked call's pieces of its items; the workspace that the
 // query asks for and the allocation-free scratch hold the slots.  And the gangs of
 // the forward / dQ units: the unit list, or its halves, on queues of about equal
-// work, of a kind that changes results only with the whole list.  Built with
-// g++ from the library's host sources; prints "split checks ok".
+// work, of a kind that changes results only with the whole list, and, on the lists
+// of the file that the program is given, well balanced.  Built with g++
+// from the library's host sources; prints "split checks ok".
 #include "nsp_abi.cpp"
 
 #include <cstdlib>
@@ -170,6 +171,94 @@ void check_gangs(const nsp_worklist &w, int *kinds) {
   CHECK(f.small == s.small && (!s.small || (s.dq.kind == nsp::kQHalf && s.kv_wgs.size() % 8 == 0)));
 }
 
+// Whether a pass runs persistent workgroups: more units than the chip holds.
+bool persistent(const QUnits &q, int head_dim, bool dq) {
+  const int per_cu = q.kind != nsp::kQHalf ? 1 : dq && head_dim == 64 ? 3 : 2;
+  return (int)q.units.size() > per_cu * kAssumedCUs && !q.one_shot;
+}
+
+// The lists of the GPU tests that stand for persistent passes run them: the kind
+// of their forward and dQ units, and whether those and dK/dV are persistent.
+void check_tested_lists() {
+  struct {
+    int L, n, sp, hq, hkv, D, fwd, dq;
+    bool q_pers, kv_pers;
+  } lists[] = {
+      {256, 80, 1, 32, 4, 128, nsp::kQHalf, nsp::kQHalf, false, true},
+      {700, 130, 1, 8, 2, 64, nsp::kQHalf, nsp::kQHalf, true, true},
+      {700, 130, 1, 8, 2, 128, nsp::kQHalf, nsp::kQHalf, true, true},
+      {2560, 14, 1, 8, 2, 128, nsp::kQWhole, nsp::kQWhole, true, true},
+      {16384, 2, 8, 16, 2, 128, nsp::kQKeys, nsp::kQKeys, true, false},
+  };
+  for (auto &t : lists) {
+    std::vector<int32_t> cu(1, 0), qh, kvh;
+    for (int j = 0; j < t.n; ++j) {
+      cu.push_back(cu.back() + t.L);
+      qh.insert(qh.end(), {0, t.hq / t.sp});
+      kvh.insert(kvh.end(), {0, std::max(1, t.hkv / t.sp)});
+    }
+    std::vector<uint8_t> mask(t.n, 0);
+    mask[0] = 1;
+    nsp_worklist w{};
+    w.n_items = t.n;
+    w.cu_seqlens = cu.data();
+    w.q_heads = qh.data();
+    w.kv_heads = kvh.data();
+    w.hq_total = t.hq;
+    w.hkv_total = t.hkv;
+    w.head_dim = t.D;
+    const HostAttnSched s = build_attn_schedule(&w);
+    CHECK(s.fwd.kind == t.fwd && s.dq.kind == t.dq && !s.small);
+    CHECK(persistent(s.fwd, t.D, false) == t.q_pers && persistent(s.dq, t.D, true) == t.q_pers);
+    CHECK((s.kv_units.size() > (size_t)kAssumedCUs) == t.kv_pers && s.kv_wgs.empty() == t.kv_pers);
+    w.item_mask = mask.data();
+    const HostAttnSched m = build_attn_schedule(&w);
+    CHECK(!persistent(m.fwd, t.D, false) && !persistent(m.dq, t.D, true) && m.kv_units.size() <= (size_t)kAssumedCUs);
+  }
+}
+
+// The queues that the forward and dQ passes run end within 1% of an even split by
+// the model of a persistent pass, on the lists of a file: name, heads, head_dim,
+// items (length, query heads, KV heads, whether the call has them).
+void check_balance(const char *path) {
+  FILE *f = std::fopen(path, "r");
+  CHECK(f);
+  char name[64];
+  int n = 0, n_lists = 0;
+  nsp_worklist w{};
+  while (std::fscanf(f, "%63s %d %d %d %d", name, &w.hq_total, &w.hkv_total, &w.head_dim, &n) == 5) {
+    std::vector<int32_t> cu(1, 0), qh(2 * n), kvh(2 * n);
+    std::vector<uint8_t> mask(n);
+    for (int j = 0; j < n; ++j) {
+      int L = 0, on = 0;
+      CHECK(std::fscanf(f, "%d %d %d %d %d %d", &L, &qh[2 * j], &qh[2 * j + 1], &kvh[2 * j], &kvh[2 * j + 1], &on) == 6);
+      cu.push_back(cu.back() + L);
+      mask[j] = (uint8_t)on;
+    }
+    w.n_items = n;
+    w.cu_seqlens = cu.data();
+    w.q_heads = qh.data();
+    w.kv_heads = kvh.data();
+    w.item_mask = mask.data();
+    const HostAttnSched s = build_attn_schedule(&w);
+    for (const QUnits *q : {&s.fwd, &s.dq}) {
+      CHECK(q->kind == nsp::kQWhole);
+      std::vector<int64_t> steps;
+      int64_t total = 0;
+      for (const int4 &u : q->units) {
+        steps.push_back((std::min(cu[u.x + 1] - cu[u.x], 256 * (u.y + 1)) + 63) / 64);
+        total += steps.back();
+      }
+      const double over = (double)kv_model_makespan(steps, q->off) * kAssumedCUs / (double)total;
+      if (over > 1.01) std::fprintf(stderr, "%s: %zu units end at %.4f of an even split\n", name, steps.size(), over);
+      CHECK(over <= 1.01);
+    }
+    ++n_lists;
+  }
+  std::fclose(f);
+  CHECK(n_lists > 0);
+}
+
 // Lists near the allocation-free scratch's limits, whose schedules fit with
 // 256-row units where the ones with 128-row units do not: of many short items, and
 // of two items among empty ones, small enough for one launch (or for key groups).
@@ -240,8 +329,10 @@ void check_compact() {
 
 }  // namespace
 
-int main() {
+int main(int argc, char **argv) {
   check_compact();
+  check_tested_lists();
+  if (argc > 1) check_balance(argv[1]);
   int n_split = 0, kinds[3] = {0, 0, 0};
   for (int rep = 0; rep < 400; ++rep) {
     static const int heads[][2] = {{32, 4}, {8, 2}, {16, 16}, {4, 1}, {12, 6}};

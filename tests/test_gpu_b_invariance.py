@@ -192,24 +192,31 @@ def test_empty_and_unit_items_interleaved():
             assert rel_l2(to_np(out[g]), r) < 1e-2
 
 
-def test_persistent_passes_on_concurrent_streams():
+@pytest.mark.parametrize("lengths,hq,hkv,D", [
+    ([256] * 80, 32, 4, 128),       # dK/dV persistent; the others one workgroup a unit
+    ([700] * 130, 8, 2, 64),        # 128-row units, persistent; dK/dV too
+    ([2560] * 14, 8, 2, 128),       # 256-row units, persistent; dK/dV too
+])
+def test_persistent_passes_on_concurrent_streams(lengths, hq, hkv, D):
     """Two calls at once on two new streams (each with its own buffers and
-    workspace) while the persistent passes run -- more units than compute
-    units in all three -- reproduce the default-stream results bit for bit:
-    each stream takes its forward counters from its own block, each backward
-    its queue heads from its own workspace."""
+    workspace) while the persistent passes run reproduce the default-stream
+    results bit for bit: each stream takes its forward counters from its own
+    block, each backward its queue heads from its own workspace.  (Which passes
+    of these lists are persistent is checked on the host, in
+    native/split_checks.cpp.)"""
     import torch
-    wl = small_worklist([256] * 80, 32, 4, 128)
+    wl = small_worklist(lengths, hq, hkv, D)
+    scale = 1.0 / np.sqrt(D)
     inp = draw_attention_inputs(wl, 31)
-    ref = all_bits(run_attention(wl, *inp, SCALE))
+    ref = all_bits(run_attention(wl, *inp, scale))
     q, k, v, do = (nsp.to_device_bf16(x) for x in inp)
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]
     bufs = [nsp.alloc_like_worklist(wl) for _ in streams]
     torch.cuda.synchronize()
     for rep in range(2):
         for s, b in zip(streams, bufs):
-            nsp.nsp_varlen_attn_fwd(wl, q, k, v, b["o"], b["lse"], SCALE, stream=s)
-            nsp.nsp_varlen_attn_bwd(wl, q, k, v, b["o"], do, b["lse"], b["dq"], b["dk"], b["dv"], b["ws"], SCALE,
+            nsp.nsp_varlen_attn_fwd(wl, q, k, v, b["o"], b["lse"], scale, stream=s)
+            nsp.nsp_varlen_attn_bwd(wl, q, k, v, b["o"], do, b["lse"], b["dq"], b["dk"], b["dv"], b["ws"], scale,
                                     stream=s)
         torch.cuda.synchronize()
         for b in bufs:

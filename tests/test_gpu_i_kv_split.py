@@ -5,9 +5,9 @@ On the CPU the cuts are checked against brute force on random lists
 (tests/native/split_checks.cpp).  On the GPU, at the sizes where a piece can go
 wrong (pieces that start and end inside a query tile's heads, ragged ends, an
 odd number of key tiles, one query head a KV head, a KV head with none, both
-head widths, lists small enough for one launch with dQ), against the float64 oracle and against the whole tiles, which the
-same items run in a list of more than 1024 key tiles (the others masked out):
-float32 sums of at most 2^16 terms in another order, whose relative difference
+head widths, lists small enough for one launch with dQ), against the float64
+oracle and against the whole tiles, which the same items run in a list of more
+than 512 key tiles, the most that shares go up to (the others masked out): float32 sums of at most 2^16 terms in another order, whose relative difference
 is bounded by about sqrt(2^16) * 2^-24 = 1.5e-5 for sums without cancellation
 (P and dS themselves are computed alike, bit for bit).
 """
@@ -20,7 +20,7 @@ import numpy as np
 import pytest
 
 from paper_2609_22755_amd import nsp
-from paper_2609_22755_amd.workloads import draw_attention_inputs, small_worklist
+from paper_2609_22755_amd.workloads import draw_attention_inputs, make_config, small_worklist
 
 from gpu_util import GRAD_REL_L2, oracle_full, rel_l2, report, require_gpu, run_attention, to_np
 
@@ -30,8 +30,8 @@ SUM_REL = 1.5e-5
 
 
 def padded(wl):
-    """The work list with more than 1024 one-token key tiles behind it, masked out."""
-    k = 1024 // wl.hkv_total + 1
+    """The work list with more than 512 one-token key tiles behind it, masked out."""
+    k = 512 // wl.hkv_total + 1
     return dataclasses.replace(
         wl, lengths=np.concatenate([wl.lengths, np.ones(k, np.int32)]), sp=np.concatenate([wl.sp, np.ones(k, np.int32)]),
         q_heads=np.concatenate([wl.q_heads, np.tile([[0, wl.hq_total]], (k, 1))]),
@@ -54,7 +54,7 @@ CASES = {
     "d64": lambda: small_worklist([2049, 500], 8, 2, 64),
     "lone_kv_head": _lone_kv_head,
     # small lists: dQ units in the same launch, with tiles cut and whole
-    "small_mixed": lambda: small_worklist([200, 64, 33, 0, 1, 513], 32, 4, 128, sp=[2, 1, 1, 1, 1, 1],
+    "small_mixed": lambda: small_worklist([200, 64, 33, 0, 1, 257], 32, 4, 128, sp=[2, 1, 1, 1, 1, 1],
                                           rank=[1, 0, 0, 0, 0, 0]),
     "small_d64": lambda: small_worklist([64, 129, 256, 511], 8, 2, 64),
     "small_whole": lambda: small_worklist([17, 31], 4, 2, 128),
@@ -73,7 +73,19 @@ def test_split_cuts_on_random_lists(tmp_path):
            "-L", os.path.join(ROCM, "lib"), "-lamdhip64", f"-Wl,-rpath,{os.path.join(ROCM, 'lib')}"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
-    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    # the shares whose forward and dQ queues are checked for balance: the two of the
+    # full-size tests, and each SP level's item-masked call of the long-tail one
+    lists = tmp_path / "lists.txt"
+    with open(lists, "w") as f:
+        for name in ("longtail_4level", "maxctx_relayout"):
+            wl = make_config(name).wl
+            levels = sorted(set(int(x) for x in wl.sp)) if name == "longtail_4level" else []
+            for sp in [0] + levels:
+                f.write(f"{name}_sp{sp} {wl.hq_total} {wl.hkv_total} {wl.head_dim} {wl.n_items}\n")
+                for j in range(wl.n_items):
+                    f.write(" ".join(str(int(x)) for x in (wl.lengths[j], *wl.q_heads[j], *wl.kv_heads[j],
+                                                           sp in (0, int(wl.sp[j])))) + "\n")
+    r = subprocess.run([exe, str(lists)], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and "split checks ok" in r.stdout, r.stdout + r.stderr
 
 

@@ -80,3 +80,51 @@ def test_unit_kinds(name):
     else:
         assert torch.equal(o.view(torch.int32), f32["o"].view(torch.int32))
         assert torch.equal(lse.view(torch.int32), f32["lse"].view(torch.int32))
+
+
+PERSISTENT = {
+    # more units than the compute units hold workgroups, in all three passes of
+    # the first three lists (checked on the host, in native/split_checks.cpp); two
+    # key groups, with dK/dV in shares
+    "half_d64": ([700] * 130, None, 8, 2, 64),
+    "half_d128": ([700] * 130, None, 8, 2, 128),
+    "whole": ([2560] * 14, None, 8, 2, 128),
+    "keys": ([16384, 16384], [8, 8], 16, 2, 128),
+}
+
+
+@pytest.mark.parametrize("name", sorted(PERSISTENT))
+def test_persistent_units_against_masked_calls(name):
+    """A workgroup that runs unit after unit leaves the results of workgroups that
+    run one: some items of the list, each alone in a masked call of at most one
+    workgroup a compute unit, bit for bit."""
+    import torch
+    require_gpu()
+    lengths, sp, hq, hkv, D = PERSISTENT[name]
+    wl = small_worklist(lengths, hq, hkv, D, sp=sp)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(900 + len(name))
+    scale = 1.0 / np.sqrt(D)
+    sizes = (wl.q_elems(), wl.kv_elems(), wl.kv_elems(), wl.q_elems())
+    q, k, v, do = (torch.randn(n, generator=g, device="cuda").to(torch.bfloat16) for n in sizes)
+
+    def call(w):
+        b = nsp.alloc_like_worklist(w, grad_dtype=torch.float32)
+        for n in ("o", "lse", "dq", "dk", "dv"):
+            b[n].fill_(float("nan"))
+        nsp.nsp_varlen_attn_fwd(w, q, k, v, b["o"], b["lse"], scale)
+        nsp.nsp_varlen_attn_bwd(w, q, k, v, b["o"], do, b["lse"], b["dq"], b["dk"], b["dv"], b["ws"], scale)
+        torch.cuda.synchronize()
+        return b
+
+    full = call(wl)
+    at = {n: np.concatenate([[0], np.cumsum(wl.lengths.astype(np.int64) * per)])
+          for n, per in (("o", wl.hq * D), ("lse", wl.hq), ("dq", wl.hq * D), ("dk", wl.hkv * D), ("dv", wl.hkv * D))}
+    for j in sorted({0, wl.n_items // 2, wl.n_items - 1}):
+        mask = np.zeros(wl.n_items, np.uint8)
+        mask[j] = 1
+        one = call(wl.select(mask))
+        for n, off in at.items():
+            a, b = (t[n][off[j]:off[j + 1]] for t in (full, one))
+            wide = torch.int16 if a.dtype == torch.bfloat16 else torch.int32
+            assert bool(torch.isfinite(a).all()) and torch.equal(a.view(wide), b.view(wide)), (n, j)

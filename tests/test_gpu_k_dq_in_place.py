@@ -5,6 +5,8 @@ own.  dK/dV take P and dS from the same lse and Delta up to the order of Delta's
 float32 sum of D products: |dDelta| <= D * 2^-24 * sum |dO O|, far below the
 bfloat16 rounding of dS (2^-9), so the two calls agree within one rounding of dS
 and one of the result on each side, 2^-8 in the 2-norm."""
+import functools
+
 import numpy as np
 import pytest
 
@@ -17,12 +19,21 @@ pytestmark = pytest.mark.gpu
 
 LISTS = {
     # name: (lengths, hq, hkv, head_dim): both passes in one launch; two key
-    # groups and split key tiles; 128-row units; persistent 256-row units
+    # groups and split key tiles; 128-row units, one workgroup a unit and
+    # persistent; persistent 256-row units
     "small": ([130, 1, 64], 4, 2, 128),
     "keys": ([1280, 130], 4, 2, 64),
     "short": ([300] * 20 + [33], 8, 2, 128),
-    "long": ([2304] * 8 + [2177], 8, 2, 128),
+    "short_persistent": ([700] * 130, 8, 2, 64),
+    "long": ([2560] * 14, 8, 2, 128),
 }
+
+
+@functools.lru_cache(maxsize=1)
+def inputs(name):
+    lengths, hq, hkv, D = LISTS[name]
+    wl = small_worklist(lengths, hq, hkv, D)
+    return wl, draw_attention_inputs(wl, 700 + len(name))
 
 
 @pytest.mark.parametrize("over", ["q", "dout", "o", "o32"])
@@ -30,10 +41,8 @@ LISTS = {
 def test_dq_over_an_input(name, over):
     import torch
     require_gpu()
-    lengths, hq, hkv, D = LISTS[name]
-    wl = small_worklist(lengths, hq, hkv, D)
-    inp = draw_attention_inputs(wl, 700 + len(name))
-    scale = 1.0 / np.sqrt(D)
+    wl, inp = inputs(name)
+    scale = 1.0 / np.sqrt(wl.head_dim)
     dt = torch.float32 if over == "o32" else torch.bfloat16
     ref = run_attention(wl, *inp, scale, o_dtype=dt, g_dtype=dt)
     q, k, v, do = (nsp.to_device_bf16(x) for x in inp)
