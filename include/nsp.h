@@ -300,7 +300,7 @@ nsp_status nsp_recompute_plan(const nsp_worklist *wl, int64_t budget_bytes, nsp_
  *   gangs, and the queues are laid out one after another (see
  *   nsp_attn_kv_queues).  The persistent dK/dV pass takes its own XCD's
  *   queue first, the others' once it is empty; a one-shot grid (no more
- *   units than compute units) runs entry b / 8 of queue b % 8 in workgroup b.
+ *   units than compute units) runs unit b in workgroup b.
  *   Items with L_j = 0 or outside wl->item_mask contribute no units.
  *   units     out, capacity x 4 int32 in the order above (may be NULL if
  *             capacity = 0: a size query)

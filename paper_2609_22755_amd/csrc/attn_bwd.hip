@@ -982,8 +982,12 @@ __device__ __forceinline__ void dkdv_unit(const AttnArgs &a, int item, int tile,
 }
 
 // dK/dV pass over the per-XCD queues (a.qoff): with queue heads (more units
-// than compute units) one persistent workgroup per compute unit, without one
-// workgroup per unit.
+// than compute units) one persistent workgroup per compute unit; without,
+// workgroup b runs unit b, so that the units go round the XCDs whatever queues
+// they are in.  (A gang of 32 pairs is one queue's: with entry b / 8 of queue
+// b % 8 its 64 units shared the 32 compute units of an XCD while others had none.
+// One item of a masked call, 32 / 4 heads, dK/dV by queue / by unit: 4096 tokens
+// 907 / 649 us, 7000 1547 / 1174; 16384 of 4 / 1 heads 1695 / 1320.)
 template <int D, bool G_F32>
 __global__ void __launch_bounds__(256, 1) bwd_dkdv_kernel(AttnArgs a, int *heads) {
   using C = KvCfg<D>;
@@ -995,7 +999,7 @@ __global__ void __launch_bounds__(256, 1) bwd_dkdv_kernel(AttnArgs a, int *heads
   __shared__ __attribute__((aligned(16))) bf16 stg3[C::STAGE];
   __shared__ int s_slot;
   UnitQueue q(heads, a.qoff, &s_slot);
-  for (int slot = q.first(); slot >= 0; slot = q.next()) {
+  for (int slot = heads ? q.first() : (int)blockIdx.x; slot >= 0; slot = q.next()) {
     const int4 u = a.units[slot];
     dkdv_unit<D, G_F32, false>(a, u.x, u.y & kKvTileMask, (u.y & kKvDescending) != 0, u.z, u.w, 0, 0, nullptr, stg0,
                                stg1, stg2, stg3);
@@ -1165,6 +1169,7 @@ hipError_t launch_bwd_dkdv(int head_dim, bool g_f32, const AttnArgs &a, int n_un
   int *heads = nullptr;
   hipError_t e = pass_grid(a, n_units, 1, a.queue + kKvQueue0, &grid, &heads);
   if (e != hipSuccess) return e;
+  if (!heads) grid = dim3(n_units);
   if (head_dim == 128) {
     if (g_f32) bwd_dkdv_kernel<128, true><<<grid, block, 0, s>>>(a, heads);
     else bwd_dkdv_kernel<128, false><<<grid, block, 0, s>>>(a, heads);
