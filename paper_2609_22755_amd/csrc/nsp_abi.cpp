@@ -733,26 +733,44 @@ void add_split(HostAttnSched &s, const nsp_worklist *wl) {
 //    15.4; one of 256 tokens 9.9 / 10.2, 4 of 300 (384 units) 13.7 / 17.9.  The groups'
 //    sums are rounded in another order, so this is decided from every item of
 //    the list, whatever the call's mask; the other two kinds give the same bits.
-constexpr double kShortUnitFwd = 8, kShortUnitDq = 20;
+//  At head_dim 64 a compute unit holds three dQ workgroups of 128 rows, and a long
+//  unit shares it with two others for as long as these last: a list whose longest
+//  unit takes more than half of a compute unit's share of the pass keeps 256-row
+//  units (dQ, 256-row / 128-row units, 8 / 2 heads, W: share, steps: 150 items of 100
+//  tokens and one of 9000, W 92, longest 141, 156 / 234 us; 100 of 700 and two of 9000
+//  with one head here, W 92, 141, 164 / 237; 232 of 300 and one of 20000 with one head,
+//  W 114, 313, 309 / 497; 32 / 4 heads, 48 of 700 and such a one, W 284, 313, 424 / 551;
+//  102 of 700 and two of 9000, W 368, 141, 619 / 549), unless the pass runs one
+//  workgroup a unit (one_shot; 228 of 100 and one of 9000 with one head, W 25, 141,
+//  138 / 117) or nearly all units are very short, kTinyUnit steps on the mean (32 / 4
+//  heads, 695 of 100 and one of 20000 of four heads, W 371, 313, 867 / 567).  At
+//  head_dim 128, two workgroups, the same lists lose up to 10%.
+constexpr double kShortUnitFwd = 8, kShortUnitDq = 20, kTinyUnit = 5;
 
-int q_unit_kind(const nsp_worklist *wl, double short_unit) {
+int q_unit_kind(const nsp_worklist *wl, bool dq) {
   int64_t units[2] = {0, 0}, steps[2] = {0, 0};   // of every item, of the call's
-  int64_t halves = 0, longest = 0;                // of every item
+  int64_t longest[2] = {0, 0};
+  int64_t halves = 0;                             // of every item
   for (int j = 0; j < wl->n_items; ++j) {
     const int64_t L = wl->cu_seqlens[j + 1] - wl->cu_seqlens[j], hq = wl->q_heads[2 * j + 1] - wl->q_heads[2 * j];
     halves += hq * ((L + nsp::kFwdBM / 2 - 1) / (nsp::kFwdBM / 2));
     for (int64_t m = 0; m * nsp::kFwdBM < L; ++m) {
       const int64_t n = (std::min<int64_t>(L, nsp::kFwdBM * (m + 1)) + nsp::kFwdBN - 1) / nsp::kFwdBN;
-      longest = std::max(longest, n);
       for (int c = 0; c < (selected(wl, j) ? 2 : 1); ++c) {
         units[c] += hq;
         steps[c] += hq * n;
+        longest[c] = std::max(longest[c], n);
       }
     }
   }
   if (units[0] <= kAssumedCUs && steps[0] > kShortUnitFwd * units[0]) return nsp::kQKeys;
-  if (halves <= kAssumedCUs && longest >= kShortUnitFwd) return nsp::kQKeys;
-  return units[1] <= kAssumedCUs || steps[1] <= short_unit * units[1] ? nsp::kQHalf : nsp::kQWhole;
+  if (halves <= kAssumedCUs && longest[0] >= kShortUnitFwd) return nsp::kQKeys;
+  if (units[1] <= kAssumedCUs) return nsp::kQHalf;
+  if (steps[1] > (dq ? kShortUnitDq : kShortUnitFwd) * units[1]) return nsp::kQWhole;
+  if (dq && wl->head_dim == 64 && 2 * longest[1] * kAssumedCUs > steps[1] && steps[1] > kOneShotSteps * kAssumedCUs &&
+      steps[1] > kTinyUnit * units[1])
+    return nsp::kQWhole;
+  return nsp::kQHalf;
 }
 
 // Whether the dQ pass runs first and computes Delta, in place of the preprocess
@@ -863,8 +881,8 @@ HostAttnSched build_attn_schedule(const nsp_worklist *wl, bool compact = false, 
   }
   s.q_rows = qo / D;
   lpt_sort(s.fwd_units, fcost);
-  s.fwd = q_units(wl, compact ? nsp::kQWhole : q_unit_kind(wl, kShortUnitFwd));
-  const int dq_kind = compact ? nsp::kQWhole : s.small ? nsp::kQHalf : q_unit_kind(wl, kShortUnitDq);
+  s.fwd = q_units(wl, compact ? nsp::kQWhole : q_unit_kind(wl, false));
+  const int dq_kind = compact ? nsp::kQWhole : s.small ? nsp::kQHalf : q_unit_kind(wl, true);
   s.dq = dq_kind == s.fwd.kind ? s.fwd : q_units(wl, dq_kind);
   kv_balance(item_gangs, wl);
   for (const KvGang *g : kv_queue_order(item_gangs, s.kv_qoff))

@@ -217,6 +217,36 @@ void check_tested_lists() {
   }
 }
 
+// Lists of short items and a few long ones: 128-row dQ units at head_dim 64 only
+// where the long ones do not end the pass.
+void check_long_units() {
+  struct {
+    int L, n, long_L, n_long, long_hq, hq, hkv, D, dq;
+  } lists[] = {
+      {100, 150, 9000, 1, 8, 8, 2, 64, nsp::kQWhole},   {100, 150, 9000, 1, 8, 8, 2, 128, nsp::kQHalf},
+      {700, 100, 9000, 2, 1, 8, 2, 64, nsp::kQWhole},   {300, 232, 20000, 1, 1, 8, 2, 64, nsp::kQWhole},
+      {100, 228, 9000, 1, 1, 8, 2, 64, nsp::kQHalf},    {700, 102, 9000, 2, 4, 32, 4, 64, nsp::kQHalf},
+      {100, 695, 20000, 1, 4, 32, 4, 64, nsp::kQHalf},  {700, 102, 9000, 0, 1, 32, 4, 64, nsp::kQHalf},
+  };
+  for (auto &t : lists) {
+    std::vector<int32_t> cu(1, 0), qh, kvh;
+    for (int j = 0; j < t.n + t.n_long; ++j) {
+      cu.push_back(cu.back() + (j < t.n ? t.L : t.long_L));
+      qh.insert(qh.end(), {0, j < t.n ? t.hq : t.long_hq});
+      kvh.insert(kvh.end(), {0, t.hkv});
+    }
+    nsp_worklist w{};
+    w.n_items = t.n + t.n_long;
+    w.cu_seqlens = cu.data();
+    w.q_heads = qh.data();
+    w.kv_heads = kvh.data();
+    w.hq_total = t.hq;
+    w.hkv_total = t.hkv;
+    w.head_dim = t.D;
+    CHECK(build_attn_schedule(&w).dq.kind == t.dq);
+  }
+}
+
 // The queues that the forward and dQ passes run end within 1% of an even split by
 // the model of a persistent pass, on the lists of a file: name, heads, head_dim,
 // items (length, query heads, KV heads, whether the call has them).
@@ -332,6 +362,7 @@ void check_compact() {
 int main(int argc, char **argv) {
   check_compact();
   check_tested_lists();
+  check_long_units();
   if (argc > 1) check_balance(argv[1]);
   int n_split = 0, kinds[3] = {0, 0, 0};
   for (int rep = 0; rep < 400; ++rep) {
