@@ -134,9 +134,10 @@ nsp_status nsp_varlen_attn_fwd(const nsp_worklist *wl, float softmax_scale, int3
  * if the work list is invalid): -Delta[t] = -<dO[t], O[t]> and lse*log2(e)
  * (float32, laid out like lse, each part 256-byte aligned), 256 bytes of
  * unit-queue heads for the persistent passes and room for float32 partial
- * sums of dK/dV (512 KiB * head_dim, the same for every list: a list whose
- * dK/dV units would leave compute units idle has them cut into pieces; decided
- * from every item, whatever item_mask).  A call uses the workspace
+ * sums of dK/dV (512 KiB * head_dim: a list whose dK/dV
+ * units would leave compute units idle has them cut into pieces; decided from every
+ * item, whatever item_mask.  The room is the same for every list, so that a
+ * workspace serves every list of no more rows).  A call uses the workspace
  * from its first kernel to its last, so two calls that run at the same time
  * need two workspaces. */
 size_t nsp_varlen_attn_bwd_workspace(const nsp_worklist *wl);
@@ -158,6 +159,9 @@ size_t nsp_varlen_attn_bwd_workspace(const nsp_worklist *wl);
  * Deterministic: no atomics on data, every output element written by one
  * lane, so results are bitwise repeatable run to run (dQ is a pass of its own
  * that recomputes S and dP, instead of float32 atomics from the dK/dV pass).
+ * dq may be the buffer of q or dout (bf16 gradients), or lie over o or lse: it is
+ * then written when nothing reads these any more, and Delta may be summed in
+ * another order than with a dq of its own (float32 sums of head_dim products).
  * Errors: as the forward, plus NSP_EWORKSPACE.
  */
 nsp_status nsp_varlen_attn_bwd(const nsp_worklist *wl, float softmax_scale, int32_t causal,
@@ -251,10 +255,12 @@ nsp_status nsp_recompute_plan(const nsp_worklist *wl, int64_t budget_bytes, nsp_
                               int64_t *saved_bytes);
 
 /*
- * The work units of the attention calls for a work list, in launch order
- * (host only; no device work).  A dK/dV pass that is split (see
- * nsp_varlen_attn_bwd_workspace) runs the same key tiles cut into pieces of
- * equal shares instead, one share per compute unit.  This is the schedule step between the
+ * The work units of the attention calls for a work list (host only; no device
+ * work), longest first.  The dK/dV pass launches its units in this order; one
+ * that is split (see nsp_varlen_attn_bwd_workspace) runs the same key tiles cut
+ * into pieces of equal shares instead, one share per compute unit.  The forward
+ * and dQ passes run theirs, or each as two of 128 rows, in gangs on per-XCD queues
+ * (below); that order is not reported.  This is the schedule step between the
  * work list and the kernels: it balances items of very different L_j over
  * the compute units (Design, NSP Executor: the per-GPU compute of one SP-tree
  * share; Background: the quadratic cost of long sequences), and it is

@@ -6,8 +6,9 @@
 // (the paper's FlashAttention compute step; Background, Sequence Packing and
 // Sequence Parallelism).
 //
-// Work unit: (item, query head, 256-row query tile); eight waves (two per
-// SIMD), each owning 32 query rows.  The wave computes S^T = K Q^T so that
+// Work unit: (item, query head, 256-row query tile; 128 rows for lists of short
+// units or of few, see q_unit_kind in the schedule builder); eight waves (two per
+// SIMD; four for 128 rows), each owning 32 query rows.  The wave computes S^T = K Q^T so that
 // each lane owns one query row (the MFMA column) -- softmax statistics then
 // live in a lane and need a single exchange between the two lane halves -- and
 // O^T = V^T P^T, whose B operand is P^T straight from the S^T accumulator, and
@@ -457,9 +458,9 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs &a, int slot, bf16 *smem
 }
 
 // The forward pass over the per-XCD queues (a.qoff).  With queue heads (a.queue:
-// kXcdQueues heads and a count of workgroups done, zero at launch), one
-// persistent workgroup per compute unit, and the last workgroup to finish sets
-// them back to zero for the next launch on the same stream.  Without
+// kXcdQueues heads and a count of workgroups done, zero at launch), as many
+// persistent workgroups as the compute units hold (PER_CU each), and the last
+// workgroup to finish sets them back to zero for the next launch on the same stream.  Without
 // (a.queue == nullptr), one workgroup per unit.
 template <int D, bool O_F32, int RB, int KG>
 __global__ void __launch_bounds__(64 * RB * KG, RB * KG == 4 ? 2 : 1) attn_fwd_kernel(AttnArgs a) {

@@ -215,6 +215,30 @@ int64_t max_stream_bytes(const nsp_worklist *wl) {
   return 2 * 2 * L * wl->head_dim;
 }
 
+// One local KV head of an item: the local query heads that use it (a contiguous
+// range, first | end << 16; 0 if there are none) and their number.
+struct KvGroup {
+  int item, g, heads;
+  int64_t w;
+};
+
+std::vector<KvGroup> kv_groups(const nsp_worklist *wl, int j) {
+  std::vector<KvGroup> out;
+  const int ql = wl->q_heads[2 * j], hq = wl->q_heads[2 * j + 1] - ql;
+  const int kl = wl->kv_heads[2 * j], hkv = wl->kv_heads[2 * j + 1] - kl;
+  for (int g = 0; g < hkv; ++g) {
+    int i0 = hq, i1 = 0;
+    for (int i = 0; i < hq; ++i)
+      if ((int)(((int64_t)(ql + i) * wl->hkv_total) / wl->hq_total) - kl == g) {
+        i0 = std::min(i0, i);
+        i1 = std::max(i1, i + 1);
+      }
+    if (i1 <= i0) i0 = i1 = 0;
+    out.push_back(KvGroup{j, g, i0 | (i1 << 16), (int64_t)(i1 - i0)});
+  }
+  return out;
+}
+
 // dK/dV gangs.  The unit of key tile n streams the Q / dO tiles of its
 // group's query heads from the tile's diagonal (query tile 2n) to the item
 // end, and the units of an item's key tiles stream the same tiles: they hit
@@ -242,8 +266,6 @@ struct KvGang {
 using ItemGangs = std::vector<std::pair<int, std::vector<KvGang>>>;
 
 void add_kv_gangs(std::vector<KvGang> &gangs, const nsp_worklist *wl, int j, int L, int K) {
-  const int ql = wl->q_heads[2 * j], hq = wl->q_heads[2 * j + 1] - ql;
-  const int kl = wl->kv_heads[2 * j], hkv = wl->kv_heads[2 * j + 1] - kl;
   const int nk = (L + nsp::kBwdBN - 1) / nsp::kBwdBN;
   const int nqt = (L + nsp::kBwdBM - 1) / nsp::kBwdBM;
   auto tiles = [&](int n) { return (int64_t)nqt - (int64_t)n * nsp::kBwdBN / nsp::kBwdBM; };
@@ -253,18 +275,13 @@ void add_kv_gangs(std::vector<KvGang> &gangs, const nsp_worklist *wl, int j, int
   };
   std::vector<Tile> firsts, mids, leads, tails;
   K = std::min(K, nk / 2);
-  for (int g = 0; g < hkv; ++g) {
-    int i0 = hq, i1 = 0;   // local query heads of KV head g: contiguous range
-    for (int i = 0; i < hq; ++i) {
-      const int gi = (int)(((int64_t)(ql + i) * wl->hkv_total) / wl->hq_total) - kl;
-      if (gi == g) { i0 = std::min(i0, i); i1 = std::max(i1, i + 1); }
-    }
-    if (i1 <= i0) i0 = i1 = 0;   // no query head: the unit writes zeros
-    const int64_t w = std::max(1, i1 - i0);
-    for (int n = 0; n < K; ++n) leads.push_back(Tile{g, n, i0 | (i1 << 16), w});
-    for (int n = K; n < nk / 2; ++n) firsts.push_back(Tile{g, n, i0 | (i1 << 16), w});
-    for (int n = nk - K; n < nk; ++n) tails.push_back(Tile{g, n, i0 | (i1 << 16), w});
-    if (nk & 1) mids.push_back(Tile{g, nk / 2, i0 | (i1 << 16), w});
+  for (const KvGroup &gr : kv_groups(wl, j)) {
+    const int g = gr.g;
+    const int64_t w = std::max<int64_t>(1, gr.w);   // (no query head: the unit writes zeros)
+    for (int n = 0; n < K; ++n) leads.push_back(Tile{g, n, gr.heads, w});
+    for (int n = K; n < nk / 2; ++n) firsts.push_back(Tile{g, n, gr.heads, w});
+    for (int n = nk - K; n < nk; ++n) tails.push_back(Tile{g, n, gr.heads, w});
+    if (nk & 1) mids.push_back(Tile{g, nk / 2, gr.heads, w});
   }
   for (size_t p0 = 0; p0 < firsts.size(); p0 += nsp::kKvGang) {
     const size_t p1 = std::min(firsts.size(), p0 + (size_t)nsp::kKvGang);
@@ -548,35 +565,13 @@ struct KvSplit {
 // kMaxSplitTiles, two key tiles a compute unit: past that the queues, which even
 // out XCDs that run a few percent apart and read each query tile once for a gang,
 // make up for what whole tiles leave idle.  dK/dV of one head-sharded sequence of
-// 4 / 1 heads, whole / shares: 384 tiles 4969 / 4113 us, 448 5975 / 5577, 478 6459 /
-// 6361, 552 8924 / 9849 (8864 / 8837 on another card), 594 10368 / 9874, 704 13500 /
-// 13956, 768 15962 / 16565; one of 32 / 4 heads, 640 tiles 5772 / 5912.
+// 4 / 1 heads, whole / shares: 320 tiles 3767 / 2812 us, 384 4904 / 4141, 448 6016 /
+// 5691, 478 6509 / 6522, 512 6978 / 6999, 552 8771 / 8791, 594 10484 / 10224, 640 11666
+// / 11905, 704 13762 / 14524, 768 15960 / 17176; one of 32 / 4 heads, 384 tiles 2600 /
+// 2080, 448 3010 / 2832, 512 3525 / 3522, 560 4609 / 4603, 640 5701 / 6123, 704 7115 /
+// 7505.
 constexpr int64_t kPieceCost = 12, kMinPiece = 4, kSplitGain = 4;
 constexpr size_t kMaxSplitTiles = 2 * kAssumedCUs;
-
-// Key tiles of one local KV head of an item, longest first: their query heads
-// (first | end << 16) and steps a query tile.
-struct KvGroup {
-  int item, g, heads;
-  int64_t w;
-};
-
-std::vector<KvGroup> kv_groups(const nsp_worklist *wl, int j) {
-  std::vector<KvGroup> out;
-  const int ql = wl->q_heads[2 * j], hq = wl->q_heads[2 * j + 1] - ql;
-  const int kl = wl->kv_heads[2 * j], hkv = wl->kv_heads[2 * j + 1] - kl;
-  for (int g = 0; g < hkv; ++g) {
-    int i0 = hq, i1 = 0;
-    for (int i = 0; i < hq; ++i)
-      if ((int)(((int64_t)(ql + i) * wl->hkv_total) / wl->hq_total) - kl == g) {
-        i0 = std::min(i0, i);
-        i1 = std::max(i1, i + 1);
-      }
-    if (i1 <= i0) i0 = i1 = 0;
-    out.push_back(KvGroup{j, g, i0 | (i1 << 16), (int64_t)(i1 - i0)});
-  }
-  return out;
-}
 
 // The shares of at most `cap` cost (steps + kPieceCost a piece; 0: a share for
 // each whole tile): their number, and the pieces if `out` is given.
@@ -746,11 +741,12 @@ void add_split(HostAttnSched &s, const nsp_worklist *wl) {
 //  heads, 695 of 100 and one of 20000 of four heads, W 371, 313, 867 / 567).  At
 //  head_dim 128, two workgroups, the same lists lose up to 10%.
 constexpr double kShortUnitFwd = 8, kShortUnitDq = 20, kTinyUnit = 5;
+constexpr int64_t kKeysLongest = 8;   // the least longest unit for key groups with at most one 128-row unit a CU
 
 int q_unit_kind(const nsp_worklist *wl, bool dq) {
   int64_t units[2] = {0, 0}, steps[2] = {0, 0};   // of every item, of the call's
   int64_t longest[2] = {0, 0};
-  int64_t halves = 0;                             // of every item
+  int64_t halves = 0;                             // 128-row units of every item
   for (int j = 0; j < wl->n_items; ++j) {
     const int64_t L = wl->cu_seqlens[j + 1] - wl->cu_seqlens[j], hq = wl->q_heads[2 * j + 1] - wl->q_heads[2 * j];
     halves += hq * ((L + nsp::kFwdBM / 2 - 1) / (nsp::kFwdBM / 2));
@@ -764,7 +760,7 @@ int q_unit_kind(const nsp_worklist *wl, bool dq) {
     }
   }
   if (units[0] <= kAssumedCUs && steps[0] > kShortUnitFwd * units[0]) return nsp::kQKeys;
-  if (halves <= kAssumedCUs && longest[0] >= kShortUnitFwd) return nsp::kQKeys;
+  if (halves <= kAssumedCUs && longest[0] >= kKeysLongest) return nsp::kQKeys;
   if (units[1] <= kAssumedCUs) return nsp::kQHalf;
   if (steps[1] > (dq ? kShortUnitDq : kShortUnitFwd) * units[1]) return nsp::kQWhole;
   if (dq && wl->head_dim == 64 && 2 * longest[1] * kAssumedCUs > steps[1] && steps[1] > kOneShotSteps * kAssumedCUs &&

@@ -134,7 +134,7 @@ struct CopyTask {
 
 // Device scratch of the allocation-free backward: a schedule region, 256
 // bytes of unit-queue heads, then -Delta and lse*log2(e) (float32, each part
-// 256-byte aligned).
+// 256-byte aligned), then the partial sums of a split dK/dV pass.
 constexpr size_t kScratchBytes = size_t(96) << 20;
 constexpr size_t kScratchSchedBytes = size_t(8) << 20;
 // The address of the current device's scratch (looked up once per device).
