@@ -684,26 +684,54 @@ KvSplit kv_split(const nsp_worklist *wl) {
   return sp;
 }
 
+// The first pieces of at most kAssumedCUs shares, and the end: consecutive pieces,
+// the longest share as short as whole pieces allow.
+std::vector<int> even_shares(const std::vector<nsp::KvPiece> &pieces) {
+  auto cut = [&](int64_t cap) {
+    std::vector<int> share;
+    int64_t room = 0;
+    for (size_t k = 0; k < pieces.size(); ++k) {
+      const int64_t c = pieces[k].count + kPieceCost;
+      if (share.empty() || room < c) {
+        share.push_back((int)k);
+        room = cap;
+      }
+      room -= c;
+    }
+    share.push_back((int)pieces.size());
+    return share;
+  };
+  int64_t lo = 0, hi = 0;
+  for (const nsp::KvPiece &p : pieces) {
+    lo = std::max(lo, p.count + kPieceCost);
+    hi += p.count + kPieceCost;
+  }
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) / 2;
+    if (cut(mid).size() - 1 <= (size_t)kAssumedCUs) hi = mid;
+    else lo = mid + 1;
+  }
+  return cut(lo);
+}
+
 // The pieces of the call's items, workgroup by workgroup: consecutive shares
 // on one XCD (workgroup b starts on XCD b % 8), whose key tiles read the same
-// Q / dO rows.
+// Q / dO rows.  A masked call shares out its own pieces anew: the unmasked call's
+// shares would leave the tiles of its short items to the few workgroups that hold
+// them (one item of 190 tokens, 32 / 4 heads, of a list of 13: eight tiles in one
+// share, backward 244 us, shared out anew 60).
 void add_split(HostAttnSched &s, const nsp_worklist *wl) {
   const KvSplit sp = kv_split(wl);
   if (sp.pieces.empty()) return;
-  std::vector<int> shares;                    // with pieces of the call's items
-  for (size_t i = 0; i + 1 < sp.share.size(); ++i)
-    for (int k = sp.share[i]; k < sp.share[i + 1]; ++k)
-      if (selected(wl, sp.pieces[k].item)) {
-        shares.push_back((int)i);
-        break;
-      }
-  const int n = (int)shares.size();
+  std::vector<nsp::KvPiece> mine;
+  for (const nsp::KvPiece &p : sp.pieces)
+    if (selected(wl, p.item)) mine.push_back(p);
+  const std::vector<int> share = mine.size() == sp.pieces.size() ? sp.share : even_shares(mine);
+  const int n = mine.empty() ? 0 : (int)share.size() - 1;
   for (int b = 0; b < (n + kNumXcd - 1) / kNumXcd * kNumXcd; ++b) {
     const int x = b % kNumXcd, lo = (int)((int64_t)n * x / kNumXcd), hi = (int)((int64_t)n * (x + 1) / kNumXcd);
     const int first = (int)s.kv_pieces.size(), i = lo + b / kNumXcd;
-    if (i < hi)
-      for (int k = sp.share[shares[i]]; k < sp.share[shares[i] + 1]; ++k)
-        if (selected(wl, sp.pieces[k].item)) s.kv_pieces.push_back(sp.pieces[k]);
+    if (i < hi) s.kv_pieces.insert(s.kv_pieces.end(), mine.begin() + share[i], mine.begin() + share[i + 1]);
     s.kv_wgs.push_back(int2{first, (int)s.kv_pieces.size()});
   }
   for (const nsp::KvReduce &r : sp.reduce)

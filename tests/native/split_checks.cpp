@@ -3,7 +3,7 @@
 // tile in exactly one piece, in order; a tile in several pieces has one slot
 // for each, consecutive and its own, and one entry in the sum pass; no more
 // shares than compute units and none much longer than the mean; a masked call
-// runs exactly the unmasked call's pieces of its items; the workspace that the
+// runs exactly the unmasked call's pieces of its items, shared out evenly; the workspace that the
 // query asks for and the allocation-free scratch hold the slots.  And the gangs of
 // the forward / dQ units: the unit list, or its halves, on queues of about equal
 // work, of a kind that changes results only with the whole list, and, on the lists
@@ -108,10 +108,20 @@ void check_list(const nsp_worklist &w, const std::vector<uint8_t> &mask, int *n_
     for (const nsp::KvReduce &r : sp.reduce) sums_want += selected(&m, r.item);
     CHECK(s.kv_pieces.size() == want && s.kv_reduce.size() == sums_want);
     int at = 0;
+    int64_t own = 0, piece = 0, share = 0;
     for (const int2 &wg : s.kv_wgs) {
       CHECK(wg.x == at && wg.y >= at);
       at = wg.y;
+      int64_t c = 0;
+      for (int k = wg.x; k < wg.y; ++k) {
+        c += s.kv_pieces[k].count + kPieceCost;
+        piece = std::max<int64_t>(piece, s.kv_pieces[k].count + kPieceCost);
+      }
+      own += c;
+      share = std::max(share, c);
     }
+    // a masked call uses the chip too
+    if (pass) CHECK(share <= own / kAssumedCUs + piece && s.kv_wgs.size() <= (size_t)kAssumedCUs);
     CHECK(at == (int)want && s.kv_wgs.size() % 8 == 0);
     for (const nsp::KvPiece &p : s.kv_pieces) {
       CHECK(selected(&m, p.item));
